@@ -230,3 +230,60 @@ def test_learned_start_beats_cold_cg(ctx):
     net.close()
     fl.close()
     sys_.close()
+
+
+# (nin, nh, nout, M) at the edges of the 32- and 64-wide tiles, the 64- and
+# 128-deep slices and the 16-byte loads of the product kernels: widths that are
+# odd, one past a tile and wider than one tile on every layer, rows that leave
+# a short last slice; the last one takes the weight gradients in tiles of 64.  The bars are those of the tests above: they
+# come from one BF16 step of an activation, whatever the shape.
+EDGES = [(13, 65, 1, 257), (3, 64, 66, 300), (70, 130, 5, 515), (4, 1, 2, 64), (12, 200, 3, 1025),
+         (12, 1030, 3, 140)]
+
+
+@pytest.mark.parametrize("nin,nh,nout,M", EDGES)
+def test_products_at_tile_edges(ctx, nin, nh, nout, M):
+    p, x, t, nm = _problem(nin, nh, nout, M, 14)
+    net = _make(ctx, nin, nh, nout, p, nm)
+    # a pointer that is not 16-byte aligned takes the same path to the same values
+    xs = torch.zeros(x.size + 1, dtype=torch.float32, device="cuda")[1:].view(M, nin)
+    xs.copy_(torch.from_numpy(x))
+    y = torch.zeros((M, nout), dtype=torch.float32, device="cuda")
+    lg.ib_mlp_forward(ctx, net, xs, y)
+    ref = oracle.mlp_forward(p, x.astype(np.float64), nin, nh, nout, bf16=True, **_onm(nm))
+    got = y.cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(got - ref)) <= 1e-3 * np.max(np.abs(ref))
+    g, loss = lg.ib_mlp_grad(ctx, net, xs, torch.from_numpy(t).cuda())
+    lref, gref = oracle.mlp_loss_grad(p, x.astype(np.float64), t.astype(np.float64), nin, nh, nout, bf16=True,
+                                      **_onm(nm))
+    assert abs(loss - lref) <= 1e-5 * lref
+    o = 0
+    for s in [nh * nin, nh, nh * nh, nh, nout * nh, nout]:
+        a, b = g[o:o + s].astype(np.float64), gref[o:o + s]
+        assert np.linalg.norm(a - b) <= 5e-4 * np.linalg.norm(b), (o, s)
+        o += s
+    net.close()
+
+
+def test_training_gathers_the_shuffled_rows(ctx):
+    """One epoch of ib_mlp_train equals ib_mlp_train_step on the rows of the
+    documented shuffle, bit for bit (the same kernels on the same values)."""
+    nin, nh, nout, M, batch, seed = 12, 40, 3, 333, 100, 77
+    p, x, t, nm = _problem(nin, nh, nout, M, 15)
+    xd, td = torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda()
+    a, b = _make(ctx, nin, nh, nout, p, nm), _make(ctx, nin, nh, nout, p, nm)
+    la = lg.ib_mlp_train(ctx, a, xd, td, 1, batch, 1e-3, seed)
+    mask, st, perm = (1 << 64) - 1, seed, list(range(M))
+    for i in range(M - 1, 0, -1):
+        st = z = (st + 0x9e3779b97f4a7c15) & mask
+        z = ((z ^ (z >> 30)) * 0xbf58476d1ce4e5b9) & mask
+        z = ((z ^ (z >> 27)) * 0x94d049bb133111eb) & mask
+        j = (z ^ (z >> 31)) % (i + 1)
+        perm[i], perm[j] = perm[j], perm[i]
+    for b0 in range(0, M - batch + 1, batch):
+        ix = torch.tensor(perm[b0:b0 + batch], device="cuda")
+        lg.ib_mlp_train_step(ctx, b, xd[ix].contiguous(), td[ix].contiguous(), 1e-3)
+    assert la == lg.ib_mlp_last_loss(b, batch)
+    assert np.array_equal(lg.ib_mlp_get_params(a), lg.ib_mlp_get_params(b))
+    a.close()
+    b.close()

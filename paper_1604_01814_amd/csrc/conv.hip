@@ -414,6 +414,8 @@ static int run_box_conv(lgfib_ctx *ctx, const BoxPlan &plan, const Spectrum &spe
         ProfScope ps(ctx, "k_xfwd", st);
         if (fast && fast_x_ok(g)) {
             if ((rc = launch_fast_xfwd(g, (const float *)f, (float2 *)X1, (const float2 *)tw0, st))) return rc;
+        } else if (!fast && fast_x64_ok(g, f)) {
+            if ((rc = launch_fast_xfwd_f64(g, (const double *)f, (double2 *)X1, (const double2 *)tw0, st))) return rc;
         } else {
             hipLaunchKernelGGL(k_xfwd<Real>, dim3((nrows + 2 * npx - 1) / (2 * npx), ncomp), dim3(kFftThreads),
                                sizeof(C) * npx * g.P0, st, g, p0, npx, f, X1, (const C *)tw0);
@@ -467,6 +469,9 @@ static int run_box_conv(lgfib_ctx *ctx, const BoxPlan &plan, const Spectrum &spe
         ProfScope ps(ctx, "k_xinv", st);
         if (fast && fast_x_ok(g)) {
             if ((rc = launch_fast_xinv(g, (const float2 *)X1, (float *)u, accumulate, (const float2 *)tw0, st)))
+                return rc;
+        } else if (!fast && fast_x64_ok(g, u)) {
+            if ((rc = launch_fast_xinv_f64(g, (const double2 *)X1, (double *)u, accumulate, (const double2 *)tw0, st)))
                 return rc;
         } else {
             hipLaunchKernelGGL(k_xinv<Real>, dim3((nrows + 2 * npx - 1) / (2 * npx), ncomp), dim3(kFftThreads),

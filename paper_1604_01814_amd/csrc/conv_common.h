@@ -47,6 +47,12 @@ bool fast_z64_size(int P);
 int launch_fast_zconv_f64(const BoxGeo &g, double2 *X2, const double *ghat, double scale, const double2 *tw,
                           hipStream_t st);
 int launch_fast_yinv(const BoxGeo &g, const float2 *X2, float2 *X1, const float2 *tw, hipStream_t st);
+// the x passes in FP64; f and u move sixteen bytes at a time, so p (the field)
+// has to be aligned to them
+bool fast_x64_ok(const BoxGeo &g, const void *p);
+int launch_fast_xfwd_f64(const BoxGeo &g, const double *f, double2 *X1, const double2 *tw, hipStream_t st);
+int launch_fast_xinv_f64(const BoxGeo &g, const double2 *X1, double *u, int accumulate, const double2 *tw,
+                         hipStream_t st);
 // the y passes in FP64 for the specialised lengths that fit (fast_y64_size)
 bool fast_y64_size(int P);
 int launch_fast_yfwd_f64(const BoxGeo &g, const double2 *X1, double2 *X2, const double2 *tw, hipStream_t st);

@@ -16,12 +16,13 @@ using C32 = float2;
 // Pencils per workgroup: the largest power of two <= 16 whose LDS footprint
 // (half twiddle table + pencils [+ kernel spectrum column]) fits in 64 KiB.
 constexpr int kLdsBudget = 65536;
-constexpr int np_fit(int P, int extra_per_pencil) {
+// x passes; es = bytes per real
+constexpr int np_fit_x(int P, int es = 4) {
     int np = 16;
-    while (np > 1 && (P / 2 + np * P) * 8 + np * extra_per_pencil > kLdsBudget) np /= 2;
+    while (np > 1 && (P / 2 + np * P) * 2 * es > kLdsBudget) np /= 2;
     return np;
 }
-template <int P> constexpr int np_rows() { return np_fit(P, 0); }
+template <int P, int es = 4> constexpr int np_rows() { return np_fit_x(P, es); }
 // y passes: pencils plus the inverse pass's last-stage twiddle table;
 // es = bytes per real
 constexpr int np_fit_y(int P, int es = 4) {
@@ -71,7 +72,6 @@ template <bool NT, typename V> __device__ __forceinline__ void st_vec(V *p, V v)
     else *p = v;
 }
 template <typename R> using Vec2 = R __attribute__((ext_vector_type(2)));
-using Vec4f = float __attribute__((ext_vector_type(4)));
 template <bool NT, typename C> __device__ __forceinline__ C ld_pencil(const C *p) {
     using R = typename RealOf<C>::T;
     const Vec2<R> v = ld_vec<NT>(reinterpret_cast<const Vec2<R> *>(p));
@@ -84,17 +84,14 @@ template <bool NT, typename C> __device__ __forceinline__ void st_pencil(C *p, C
     w.y = v.y;
     st_vec<NT>(reinterpret_cast<Vec2<R> *>(p), w);
 }
-template <bool NT> __device__ __forceinline__ float4 ld_f4(const float *p) {
-    const Vec4f v = ld_vec<NT>(reinterpret_cast<const Vec4f *>(p));
-    return make_float4(v.x, v.y, v.z, v.w);
+// sixteen bytes: four floats or two doubles
+template <typename R> constexpr int kRun = 16 / (int)sizeof(R);
+template <typename R> using Run16 = R __attribute__((ext_vector_type(16 / sizeof(R))));
+template <bool NT, typename R> __device__ __forceinline__ Run16<R> ld_run(const R *p) {
+    return ld_vec<NT>(reinterpret_cast<const Run16<R> *>(p));
 }
-template <bool NT> __device__ __forceinline__ void st_f4(float *p, float4 v) {
-    Vec4f w;
-    w.x = v.x;
-    w.y = v.y;
-    w.z = v.z;
-    w.w = v.w;
-    st_vec<NT>(reinterpret_cast<Vec4f *>(p), w);
+template <bool NT, typename R> __device__ __forceinline__ void st_run(R *p, Run16<R> v) {
+    st_vec<NT>(reinterpret_cast<Run16<R> *>(p), v);
 }
 
 template <typename C>
@@ -137,19 +134,24 @@ constexpr int fast_kxp(int P) { return (P / 2 + 1 + 15) / 16 * 16; }
 // ------------------------------------------------------------------- pass 1
 // A workgroup owns a chunk of the B*B box rows of one block row (by, bz) of one
 // component; the block row's slot table is staged in LDS once, rows come in
-// tiles of 2*NP (two real rows per complex pencil), and data moves as float4
-// (four consecutive x of one block row segment).
-template <int P, int NPMAX>
-__device__ __forceinline__ void xfwd_body(const BoxGeo &g, const float *__restrict__ f, C32 *__restrict__ X1,
-                                                       const C32 *__restrict__ twg, int nchunks, int T, int bid) {
-    constexpr int NP = np_rows<P>() < NPMAX ? np_rows<P>() : NPMAX;
+// tiles of 2*NP (two real rows per complex pencil), and data moves in sixteen
+// bytes (four floats or two doubles of consecutive x of one block row segment).
+// C is float2 (the FP32 path) or double2 (FP64).
+template <typename C, int P, int NPMAX>
+__device__ __forceinline__ void xfwd_body(const BoxGeo &g, const typename RealOf<C>::T *__restrict__ f,
+                                          C *__restrict__ X1, const C *__restrict__ twg, int nchunks, int T, int bid) {
+    using R = typename RealOf<C>::T;
+    using V = Run16<R>;
+    constexpr int W = kRun<R>;
+    constexpr int XNP = np_rows<P, (int)sizeof(R)>();
+    constexpr int NP = XNP < NPMAX ? XNP : NPMAX;
     constexpr int N = P / 2;
-    constexpr int N4 = N / 4;
-    constexpr int NL = NP * N4;   // float4 loads per row of pencils
+    constexpr int NW = N / W;
+    constexpr int NL = NP * NW;   // sixteen-byte loads per row of pencils
     constexpr int E = (NL + kFftThreads - 1) / kFftThreads;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    C32 *tw = reinterpret_cast<C32 *>(smem_raw);
-    C32 *s = tw + P / 2;
+    C *tw = reinterpret_cast<C *>(smem_raw);
+    C *s = tw + P / 2;
     int *slot = reinterpret_cast<int *>(s + NP * P);   // [nb0] element offsets or -1
     const int lb = g.lb, B = 1 << lb, bm = B - 1;
     const int chunk = bid % nchunks;
@@ -163,22 +165,22 @@ __device__ __forceinline__ void xfwd_body(const BoxGeo &g, const float *__restri
         slot[bx] = sl >= 0 ? (sl << (3 * lb)) : -1;
     }
     lds_barrier();
-    const float *fc = f + ((size_t)c * g.nsrc << (3 * lb));
+    const R *fc = f + ((size_t)c * g.nsrc << (3 * lb));
     const int nrows = g.N1 * g.N2;
-    float4 pa[E], pb[E];
+    V pa[E], pb[E];
     auto load = [&](int q0) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int idx = threadIdx.x + e * kFftThreads;
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+            V a = V{}, b = V{};
             if (NL % kFftThreads == 0 || idx < NL) {
-                const int p = idx / N4, x = 4 * (idx % N4);
+                const int p = idx / NW, x = W * (idx % NW);
                 const int q = q0 + 2 * p;                 // even row of the pair
                 const int off = slot[x >> lb];
                 if (off >= 0) {
-                    const float *src = fc + off + (((q >> lb) << (2 * lb)) | ((q & bm) << lb) | (x & bm));
-                    a = ld_f4<nt_on(kNtXfwdLd)>(src);
-                    b = ld_f4<nt_on(kNtXfwdLd)>(src + B);   // row q + 1 (same z)
+                    const R *src = fc + off + (((q >> lb) << (2 * lb)) | ((q & bm) << lb) | (x & bm));
+                    a = ld_run<nt_on(kNtXfwdLd)>(src);
+                    b = ld_run<nt_on(kNtXfwdLd)>(src + B);   // row q + 1 (same z)
                 }
             }
             pa[e] = a;
@@ -193,40 +195,35 @@ __device__ __forceinline__ void xfwd_body(const BoxGeo &g, const float *__restri
         for (int e = 0; e < E; ++e) {
             const int idx = threadIdx.x + e * kFftThreads;
             if (NL % kFftThreads == 0 || idx < NL) {
-                C32 *d = s + (idx / N4) * P + 4 * (idx % N4);
-                d[0] = C32{pa[e].x, pb[e].x};
-                d[1] = C32{pa[e].y, pb[e].y};
-                d[2] = C32{pa[e].z, pb[e].z};
-                d[3] = C32{pa[e].w, pb[e].w};
+                C *d = s + (idx / NW) * P + W * (idx % NW);
+#pragma unroll
+                for (int w = 0; w < W; ++w) d[w] = C{pa[e][w], pb[e][w]};
             }
         }
         lds_barrier();
         if (i + 1 < T) load(q0 + 2 * NP);
-        sfft<C32, P, NP, P, 1, false, false, N, 0>(s, tw);   // x >= N is zero padding
-        // two consecutive frequencies per thread, one 16-byte store per row
+        sfft<C, P, NP, P, 1, false, false, N, 0>(s, tw);   // x >= N is zero padding
+        // KP consecutive frequencies per thread, one 16-byte store per row
         // (Kxp is even and rows start 16-byte aligned); the row length is a
         // compile-time constant of P (checked on the host), so the index
         // split below needs no integer division at run time
-        constexpr int Kxp = fast_kxp(P), Kx = P / 2 + 1, Kh = Kxp / 2;
+        constexpr int KP = W / 2;
+        constexpr int Kxp = fast_kxp(P), Kx = P / 2 + 1, Kh = Kxp / KP;
         for (int idx = threadIdx.x; idx < NP * Kh; idx += kFftThreads) {
-            const int p = idx / Kh, k = 2 * (idx - p * Kh);
-            float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
-            if (k < Kx) {
-                const C32 zk = s[p * P + k];
-                const C32 zm = s[p * P + (k == 0 ? 0 : P - k)];
-                va.x = 0.5f * (zk.x + zm.x), va.y = 0.5f * (zk.y - zm.y);
-                vb.x = 0.5f * (zk.y + zm.y), vb.y = 0.5f * (zm.x - zk.x);
-            }
-            if (k + 1 < Kx) {
-                const C32 zk = s[p * P + k + 1];
-                const C32 zm = s[p * P + P - k - 1];
-                va.z = 0.5f * (zk.x + zm.x), va.w = 0.5f * (zk.y - zm.y);
-                vb.z = 0.5f * (zk.y + zm.y), vb.w = 0.5f * (zm.x - zk.x);
-            }
+            const int p = idx / Kh, k = KP * (idx - p * Kh);
+            V va = V{}, vb = V{};
+#pragma unroll
+            for (int h = 0; h < KP; ++h)
+                if (k + h < Kx) {
+                    const C zk = s[p * P + k + h];
+                    const C zm = s[p * P + (k + h == 0 ? 0 : P - k - h)];
+                    va[2 * h] = (R)0.5 * (zk.x + zm.x), va[2 * h + 1] = (R)0.5 * (zk.y - zm.y);
+                    vb[2 * h] = (R)0.5 * (zk.y + zm.y), vb[2 * h + 1] = (R)0.5 * (zm.x - zk.x);
+                }
             const int q = q0 + 2 * p;
             const int row = ((bz << lb) + (q >> lb)) * g.N1 + (by << lb) + (q & bm);
-            st_f4<nt_on(kNtXfwdSt)>(reinterpret_cast<float *>(X1 + ((size_t)c * nrows + row) * Kxp + k), va);
-            st_f4<nt_on(kNtXfwdSt)>(reinterpret_cast<float *>(X1 + ((size_t)c * nrows + row + 1) * Kxp + k), vb);
+            st_run<nt_on(kNtXfwdSt)>(reinterpret_cast<R *>(X1 + ((size_t)c * nrows + row) * Kxp + k), va);
+            st_run<nt_on(kNtXfwdSt)>(reinterpret_cast<R *>(X1 + ((size_t)c * nrows + row + 1) * Kxp + k), vb);
         }
         lds_barrier();
     }
@@ -443,19 +440,24 @@ __device__ __forceinline__ void yinv_body(const BoxGeo &g, const C *__restrict__
 
 // ------------------------------------------------------------------- pass 5
 // Complex-to-real rows; same block-row decomposition as pass 1, cropped to the
-// target blocks of the block row and stored as float4.
-template <int P, int NPMAX>
-__device__ __forceinline__ void xinv_body(const BoxGeo &g, const C32 *__restrict__ X1, float *__restrict__ u,
-                                                       int accumulate, const C32 *__restrict__ twg, int nchunks, int T, int bid) {
-    constexpr int NP = np_rows<P>() < NPMAX ? np_rows<P>() : NPMAX;
+// target blocks of the block row and stored in sixteen bytes.
+template <typename C, int P, int NPMAX>
+__device__ __forceinline__ void xinv_body(const BoxGeo &g, const C *__restrict__ X1,
+                                          typename RealOf<C>::T *__restrict__ u, int accumulate,
+                                          const C *__restrict__ twg, int nchunks, int T, int bid) {
+    using R = typename RealOf<C>::T;
+    using V = Run16<R>;
+    constexpr int W = kRun<R>, KP = W / 2;
+    constexpr int XNP = np_rows<P, (int)sizeof(R)>();
+    constexpr int NP = XNP < NPMAX ? XNP : NPMAX;
     constexpr int Ph = P / 2;
     constexpr int Kx = Ph + 1;
-    constexpr int KH = (Kx + 1) / 2;   // frequency pairs; a row holds Kxp >= Kx + 1 entries
+    constexpr int KH = (Kx + KP - 1) / KP;   // runs of KP frequencies; a row holds Kxp >= Kx + 1 entries
     constexpr int NL = NP * KH;
     constexpr int E = (NL + kFftThreads - 1) / kFftThreads;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    C32 *tw = reinterpret_cast<C32 *>(smem_raw);
-    C32 *s = tw + P / 2;
+    C *tw = reinterpret_cast<C *>(smem_raw);
+    C *s = tw + P / 2;
     int *slot = reinterpret_cast<int *>(s + NP * P);
     const int lb = g.lb, B = 1 << lb, bm = B - 1;
     const int chunk = bid % nchunks;
@@ -472,24 +474,24 @@ __device__ __forceinline__ void xinv_body(const BoxGeo &g, const C32 *__restrict
     const int Kxp = g.Kxp;
     const size_t xbase = (size_t)c * nrows;
     auto rowidx = [&](int q) { return ((bz << lb) + (q >> lb)) * g.N1 + (by << lb) + (q & bm); };
-    // two consecutive frequencies per 16-byte load (rows start 16-byte aligned)
-    float4 pa[E], pb[E];
+    // KP consecutive frequencies per 16-byte load (rows start 16-byte aligned)
+    V pa[E], pb[E];
     auto load = [&](int q0) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int idx = threadIdx.x + e * kFftThreads;
-            float4 xa = make_float4(0.f, 0.f, 0.f, 0.f), xb = xa;
+            V xa = V{}, xb = V{};
             if (NL % kFftThreads == 0 || idx < NL) {
-                const int p = idx / KH, k = 2 * (idx % KH);
+                const int p = idx / KH, k = KP * (idx % KH);
                 const int ra = rowidx(q0 + 2 * p);
-                xa = ld_f4<nt_on(kNtXinvLd)>(reinterpret_cast<const float *>(X1 + (xbase + ra) * Kxp + k));
-                xb = ld_f4<nt_on(kNtXinvLd)>(reinterpret_cast<const float *>(X1 + (xbase + ra + 1) * Kxp + k));
+                xa = ld_run<nt_on(kNtXinvLd)>(reinterpret_cast<const R *>(X1 + (xbase + ra) * Kxp + k));
+                xb = ld_run<nt_on(kNtXinvLd)>(reinterpret_cast<const R *>(X1 + (xbase + ra + 1) * Kxp + k));
             }
             pa[e] = xa;
             pb[e] = xb;
         }
     };
-    float *uc = u + ((size_t)c * g.ntgt << (3 * lb));
+    R *uc = u + ((size_t)c * g.ntgt << (3 * lb));
     const int q00 = chunk * T * 2 * NP;
     load(q00);
     for (int i = 0; i < T; ++i) {
@@ -498,44 +500,43 @@ __device__ __forceinline__ void xinv_body(const BoxGeo &g, const C32 *__restrict
         for (int e = 0; e < E; ++e) {
             const int idx = threadIdx.x + e * kFftThreads;
             if (NL % kFftThreads == 0 || idx < NL) {
-                const int p = idx / KH, k0 = 2 * (idx % KH);
+                const int p = idx / KH, k0 = KP * (idx % KH);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
+                for (int h = 0; h < KP; ++h) {
                     const int k = k0 + h;
-                    if (h == 1 && k >= Kx) break;
-                    C32 xa = h ? C32{pa[e].z, pa[e].w} : C32{pa[e].x, pa[e].y};
-                    C32 xb = h ? C32{pb[e].z, pb[e].w} : C32{pb[e].x, pb[e].y};
+                    if (h > 0 && k >= Kx) break;
+                    C xa = C{pa[e][2 * h], pa[e][2 * h + 1]};
+                    C xb = C{pb[e][2 * h], pb[e][2 * h + 1]};
                     if (k == 0 || k == Ph) {
-                        xa.y = 0.f;
-                        xb.y = 0.f;
+                        xa.y = 0;
+                        xb.y = 0;
                     }
                     // Z = Xa + i Xb at k;  conj(Xa) + i conj(Xb) at P - k
-                    s[p * P + k] = C32{xa.x - xb.y, xa.y + xb.x};
-                    if (k > 0 && k < Ph) s[p * P + P - k] = C32{xa.x + xb.y, xb.x - xa.y};
+                    s[p * P + k] = C{xa.x - xb.y, xa.y + xb.x};
+                    if (k > 0 && k < Ph) s[p * P + P - k] = C{xa.x + xb.y, xb.x - xa.y};
                 }
             }
         }
         lds_barrier();
         if (i + 1 < T) load(q0 + 2 * NP);
-        sfft<C32, P, NP, P, 1, false, true, 0, Ph>(s, tw);   // only x < P/2 is kept
-        constexpr int N4 = Ph / 4;
-        for (int idx = threadIdx.x; idx < NP * N4; idx += kFftThreads) {
-            const int p = idx / N4, x = 4 * (idx % N4);
+        sfft<C, P, NP, P, 1, false, true, 0, Ph>(s, tw);   // only x < P/2 is kept
+        constexpr int NW = Ph / W;
+        for (int idx = threadIdx.x; idx < NP * NW; idx += kFftThreads) {
+            const int p = idx / NW, x = W * (idx % NW);
             const int off = slot[x >> lb];
             if (off < 0) continue;
-            const C32 *v = s + p * P + x;
+            const C *v = s + p * P + x;
             const int q = q0 + 2 * p;
-            float *dst = uc + off + (((q >> lb) << (2 * lb)) | ((q & bm) << lb) | (x & bm));
-            float4 a = make_float4(v[0].x, v[1].x, v[2].x, v[3].x);
-            float4 b = make_float4(v[0].y, v[1].y, v[2].y, v[3].y);
+            R *dst = uc + off + (((q >> lb) << (2 * lb)) | ((q & bm) << lb) | (x & bm));
+            V a, b;
+#pragma unroll
+            for (int w = 0; w < W; ++w) a[w] = v[w].x, b[w] = v[w].y;
             if (accumulate) {
-                const float4 oa = *reinterpret_cast<const float4 *>(dst);
-                const float4 ob = *reinterpret_cast<const float4 *>(dst + B);
-                a = make_float4(a.x + oa.x, a.y + oa.y, a.z + oa.z, a.w + oa.w);
-                b = make_float4(b.x + ob.x, b.y + ob.y, b.z + ob.z, b.w + ob.w);
+                a += *reinterpret_cast<const V *>(dst);
+                b += *reinterpret_cast<const V *>(dst + B);
             }
-            st_f4<nt_on(kNtXinvSt)>(dst, a);
-            st_f4<nt_on(kNtXinvSt)>(dst + B, b);
+            st_run<nt_on(kNtXinvSt)>(dst, a);
+            st_run<nt_on(kNtXinvSt)>(dst + B, b);
         }
         lds_barrier();
     }
@@ -543,10 +544,11 @@ __device__ __forceinline__ void xinv_body(const BoxGeo &g, const C32 *__restrict
 
 
 // Kernels of the single apply: one workgroup per tile (group).
-template <int P, int NPMAX>
-__global__ __launch_bounds__(kFftThreads) void kf_xfwd(BoxGeo g, const float *__restrict__ f, C32 *__restrict__ X1,
-                                                       const C32 *__restrict__ twg, int nchunks, int T) {
-    xfwd_body<P, NPMAX>(g, f, X1, twg, nchunks, T, (int)blockIdx.x);
+template <typename C, int P, int NPMAX>
+__global__ __launch_bounds__(kFftThreads) void kf_xfwd(BoxGeo g, const typename RealOf<C>::T *__restrict__ f,
+                                                       C *__restrict__ X1, const C *__restrict__ twg, int nchunks,
+                                                       int T) {
+    xfwd_body<C, P, NPMAX>(g, f, X1, twg, nchunks, T, (int)blockIdx.x);
 }
 template <typename C, int P, int NPMAX>
 __global__ __launch_bounds__(kFftThreads) void kf_yfwd(BoxGeo g, const C *__restrict__ X1, C *__restrict__ X2,
@@ -568,10 +570,11 @@ __global__ __launch_bounds__(kFftThreads) void kf_yinv(BoxGeo g, const C *__rest
                                                        const C *__restrict__ twg, int ntiles, int T) {
     yinv_body<C, P, NPMAX>(g, X2, X1, twg, ntiles, T, (int)blockIdx.x);
 }
-template <int P, int NPMAX>
-__global__ __launch_bounds__(kFftThreads) void kf_xinv(BoxGeo g, const C32 *__restrict__ X1, float *__restrict__ u,
-                                                       int accumulate, const C32 *__restrict__ twg, int nchunks, int T) {
-    xinv_body<P, NPMAX>(g, X1, u, accumulate, twg, nchunks, T, (int)blockIdx.x);
+template <typename C, int P, int NPMAX>
+__global__ __launch_bounds__(kFftThreads) void kf_xinv(BoxGeo g, const C *__restrict__ X1,
+                                                       typename RealOf<C>::T *__restrict__ u, int accumulate,
+                                                       const C *__restrict__ twg, int nchunks, int T) {
+    xinv_body<C, P, NPMAX>(g, X1, u, accumulate, twg, nchunks, T, (int)blockIdx.x);
 }
 
 
@@ -588,7 +591,7 @@ __device__ __forceinline__ void kb_item(const FastJob *__restrict__ jobs, const 
     const FastJob &J = jobs[k];
     const int bid = item - start[k];
     if constexpr (PASS == kPassXF)
-        xfwd_body<P, NPMAX>(J.g, (const float *)J.in, (C32 *)J.out, J.tw, J.n, J.T, bid);
+        xfwd_body<C32, P, NPMAX>(J.g, (const float *)J.in, (C32 *)J.out, J.tw, J.n, J.T, bid);
     else if constexpr (PASS == kPassYF)
         yfwd_body<C32, P, NPMAX>(J.g, (const C32 *)J.in, (C32 *)J.out, J.tw, J.n, J.T, bid);
     else if constexpr (PASS == kPassZ)
@@ -596,7 +599,7 @@ __device__ __forceinline__ void kb_item(const FastJob *__restrict__ jobs, const 
     else if constexpr (PASS == kPassYI)
         yinv_body<C32, P, NPMAX>(J.g, (const C32 *)J.in, (C32 *)J.out, J.tw, J.n, J.T, bid);
     else
-        xinv_body<P, NPMAX>(J.g, (const C32 *)J.in, (float *)J.out, J.acc, J.tw, J.n, J.T, bid);
+        xinv_body<C32, P, NPMAX>(J.g, (const C32 *)J.in, (float *)J.out, J.acc, J.tw, J.n, J.T, bid);
 }
 
 // persistent form: workgroups pull items from *queue until all are taken; the
@@ -643,7 +646,7 @@ bool fast_size(int P) {
     }
 }
 
-int fast_np_rows(int P) { return np_fit(P, 0); }
+int fast_np_rows(int P) { return np_fit_x(P); }
 int fast_np_cols(int P) { return np_fit_y(P); }
 int fast_np_zconv(int P) { return np_fit_z(P); }
 int fast_np_zconv_f64(int P) { return np_fit_z(P, 8); }
@@ -700,6 +703,10 @@ static int x_tiles(const BoxGeo &g, int NP, int *T, bool inv) {
 
 static int x_np_cap(bool fwd);
 static int x_np(int P, bool fwd) { return std::min(fast_np_rows(P), x_np_cap(fwd)); }
+// FP64 x passes: pencils per workgroup (four measured faster than two, 136
+// against 174 us forward on the 640-point rows of the plate box, equal inverse)
+constexpr int kX64NP = 4;
+static int x64_np(int P) { return std::min(np_fit_x(P, 8), kX64NP); }
 
 bool fast_x_ok(const BoxGeo &g) {
     // the x passes move frequencies in pairs: a spectrum row needs room for
@@ -711,13 +718,13 @@ bool fast_x_ok(const BoxGeo &g) {
 template <int P, bool FWD, typename... Args>
 static void launch_x_np(int cap, dim3 grid, size_t sm, hipStream_t st, Args... args) {
     if constexpr (FWD) {
-        if (cap == 4) hipLaunchKernelGGL((kf_xfwd<P, 4>), grid, dim3(kFftThreads), sm, st, args...);
-        else if (cap == 8) hipLaunchKernelGGL((kf_xfwd<P, 8>), grid, dim3(kFftThreads), sm, st, args...);
-        else hipLaunchKernelGGL((kf_xfwd<P, 16>), grid, dim3(kFftThreads), sm, st, args...);
+        if (cap == 4) hipLaunchKernelGGL((kf_xfwd<C32, P, 4>), grid, dim3(kFftThreads), sm, st, args...);
+        else if (cap == 8) hipLaunchKernelGGL((kf_xfwd<C32, P, 8>), grid, dim3(kFftThreads), sm, st, args...);
+        else hipLaunchKernelGGL((kf_xfwd<C32, P, 16>), grid, dim3(kFftThreads), sm, st, args...);
     } else {
-        if (cap == 4) hipLaunchKernelGGL((kf_xinv<P, 4>), grid, dim3(kFftThreads), sm, st, args...);
-        else if (cap == 8) hipLaunchKernelGGL((kf_xinv<P, 8>), grid, dim3(kFftThreads), sm, st, args...);
-        else hipLaunchKernelGGL((kf_xinv<P, 16>), grid, dim3(kFftThreads), sm, st, args...);
+        if (cap == 4) hipLaunchKernelGGL((kf_xinv<C32, P, 4>), grid, dim3(kFftThreads), sm, st, args...);
+        else if (cap == 8) hipLaunchKernelGGL((kf_xinv<C32, P, 8>), grid, dim3(kFftThreads), sm, st, args...);
+        else hipLaunchKernelGGL((kf_xinv<C32, P, 16>), grid, dim3(kFftThreads), sm, st, args...);
     }
 }
 
@@ -860,6 +867,47 @@ int launch_fast_zconv_f64(const BoxGeo &g, double2 *X2, const double *ghat, doub
     }
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
+}
+
+// The x passes in FP64 (the drivers' and the dense build's convolutions): the
+// same kernels on double2 pencils, bound by HBM as the FP32 ones.  Plate box:
+// 522 -> 136 us forward, 643 -> 156 us inverse against the general passes
+// (run-time radices, one 8-byte load at a time); the 16^3-cell cube 13 -> 4.5
+// and 14 -> 4.1 us.  No length is better off on the general passes, which
+// stay for lengths without a specialised pass and fields that are not 16-byte
+// aligned.
+bool fast_x64_ok(const BoxGeo &g, const void *p) {
+    return ((size_t)p & 15) == 0 && fast_size(g.P0) && g.Kxp == fast_kxp(g.P0) && (g.B * g.B) % (2 * x64_np(g.P0)) == 0 && g.nb1 <= 128;
+}
+
+template <int P, bool FWD, typename... Args> static void launch_x64(dim3 grid, size_t sm, hipStream_t st, Args... args) {
+    if constexpr (FWD) hipLaunchKernelGGL((kf_xfwd<double2, P, kX64NP>), grid, dim3(kFftThreads), sm, st, args...);
+    else hipLaunchKernelGGL((kf_xinv<double2, P, kX64NP>), grid, dim3(kFftThreads), sm, st, args...);
+}
+
+template <bool FWD, typename... Args>
+static int launch_fast_x_f64(const BoxGeo &g, hipStream_t st, Args... args) {
+    const int NP = x64_np(g.P0);
+    int T = 1;
+    const int nchunks = x_tiles(g, NP, &T, !FWD);
+    const dim3 grid(nchunks * g.nb1 * g.nb2 * g.ncomp);
+    const size_t sm = sizeof(double2) * (size_t)(g.P0 / 2 + NP * g.P0) + sizeof(int) * (size_t)g.nb0;
+    switch (g.P0) {
+#define X(n) case n: launch_x64<n, FWD>(grid, sm, st, g, args..., nchunks, T); break;
+        LGF_FAST_SIZES(X)
+#undef X
+    default: break;
+    }
+    LGF_HIP(hipGetLastError());
+    return LGFIB_OK;
+}
+
+int launch_fast_xfwd_f64(const BoxGeo &g, const double *f, double2 *X1, const double2 *tw, hipStream_t st) {
+    return launch_fast_x_f64<true>(g, st, f, X1, tw);
+}
+int launch_fast_xinv_f64(const BoxGeo &g, const double2 *X1, double *u, int accumulate, const double2 *tw,
+                         hipStream_t st) {
+    return launch_fast_x_f64<false>(g, st, X1, u, accumulate, tw);
 }
 
 // The y passes in FP64: the same kernels on double2 pencils (at most 8 per

@@ -357,3 +357,35 @@ def test_if_apply_zero_is_identity(ctx):
     ud = torch.zeros_like(fd)
     lg.lgf_if_apply(ctx, 0.0, B, blocks, blocks, fd, ud)
     assert torch.equal(ud, fd)
+
+
+# (B, blocks per axis): x lengths 16 to 1024 in every radix family of the FP64
+# x passes, block rows with few pencils (B = 4) and many (B = 32), and one
+# length (400) that has no specialised pass
+@pytest.mark.parametrize("B,nb", [(4, (2, 3, 1)), (8, (1, 2, 3)), (8, (3, 1, 2)), (8, (5, 2, 1)), (8, (9, 1, 1)),
+                                  (16, (6, 2, 1)), (16, (10, 1, 2)), (16, (20, 2, 1)), (8, (25, 1, 1)),
+                                  (32, (15, 1, 1)), (32, (16, 1, 1))])
+def test_poisson_fp64_x_passes_match_the_general_path(ctx, B, nb):
+    """FP64 fields that start 16-byte aligned take the specialised x passes,
+    others the general ones.  Two FP64 transforms of the same data differ by a
+    few roundings per stage (about log2(P0 P1 P2) <= 25 of them): 1e-13 of the
+    largest value; sources and targets in different orders, some blocks
+    missing, two components, with and without accumulation."""
+    g = np.random.Generator(np.random.PCG64(1604 + B + nb[0]))
+    box = workloads.sort_blocks(np.array(list(np.ndindex(*nb)), dtype=np.int32)) - 2
+    src = box[g.permutation(len(box))][:max(1, len(box) - 1)]
+    tgt = box[g.permutation(len(box))]
+    t = lg.lgf_table_build(ctx, lg.LGF_KIND_L, 0.0, _span_ext(src, tgt, B))
+    fs, us = (2, len(src), B, B, B), (2, len(tgt), B, B, B)
+    f0, u0 = torch.from_numpy(g.standard_normal(fs)).cuda(), torch.from_numpy(g.standard_normal(us)).cuda()
+    out = []
+    for off in (0, 1):   # 0: aligned; 1: eight bytes past a 16-byte boundary
+        f = torch.zeros(f0.numel() + 2, dtype=torch.float64, device="cuda")[off:off + f0.numel()].view(fs)
+        u = torch.zeros(u0.numel() + 2, dtype=torch.float64, device="cuda")[off:off + u0.numel()].view(us)
+        f.copy_(f0)
+        for acc in (False, True):
+            u.copy_(u0)
+            lg.lgf_poisson_apply(ctx, t, B, src, tgt, f, u, accumulate=acc)
+            out.append(u.cpu().numpy() - (u0.cpu().numpy() if acc else 0.0))
+    for u in out[1:]:
+        assert _relerr(u, out[0]) <= 1e-13

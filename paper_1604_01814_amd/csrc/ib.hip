@@ -87,6 +87,14 @@ struct IbPlan {
     DevBuf i_ptr, i_col, i_val;
     DevBuf r_ptr, r_col, r_val;
     int64_t nnz = 0;
+    // with the gradient folded in (ib_plan_grad, built for force systems):
+    // i_low[e]: the cell below entry e's face along its component, -1 outside
+    // the blocks;  R and G^T R as one operator whose rows are the nfr faces and
+    // then the ncr cells that some marker reaches: s_row[q] is row q's face, or
+    // the number of faces plus its cell
+    bool grad = false;
+    int nfr = 0, ncr = 0;
+    DevBuf i_low, s_row, s_ptr, s_col, s_val;
 };
 
 struct IbKey {
@@ -263,6 +271,87 @@ static int build_ib_plan(lgfib_ctx *ctx, int kernel, const double *X, int NL, in
     return LGFIB_OK;
 }
 
+// The operators of the force Schur complement with the staggered gradient
+// folded in.  (G d)^(k)(n) = d(n) - d(n - e_k) reads, for entry e of I, the
+// face's cell and the cell below it; c = G^T u has face (n, k) add to c(n) and
+// subtract from c(n - e_k), so G^T R has two entries for each one of R.
+static int ib_plan_grad(IbPlan &p) {
+    if (p.grad) return LGFIB_OK;
+    const int B = p.B, B3 = B * B * B;
+    const int64_t nc = (int64_t)p.nblk * B3, nrows = 3ll * p.NL;
+    const size_t nnz = (size_t)p.nnz, nmap = (size_t)p.nb[0] * p.nb[1] * p.nb[2];
+    std::vector<int32_t> iptr(nrows + 1), icol(std::max<size_t>(nnz, 1)), low(std::max<size_t>(nnz, 1), -1), map(nmap),
+        blk(3 * (size_t)p.nblk), dptr(nc + 1, 0);
+    std::vector<double> ival(std::max<size_t>(nnz, 1));
+    LGF_HIP(hipMemcpy(iptr.data(), p.i_ptr.p, 4 * iptr.size(), hipMemcpyDeviceToHost));
+    LGF_HIP(hipMemcpy(icol.data(), p.i_col.p, 4 * icol.size(), hipMemcpyDeviceToHost));
+    LGF_HIP(hipMemcpy(ival.data(), p.i_val.p, 8 * ival.size(), hipMemcpyDeviceToHost));
+    LGF_HIP(hipMemcpy(map.data(), p.map.p, 4 * nmap, hipMemcpyDeviceToHost));
+    if (p.nblk) LGF_HIP(hipMemcpy(blk.data(), p.blocks.p, 4 * blk.size(), hipMemcpyDeviceToHost));
+    const int step[3] = {1, B, B * B};
+    for (int64_t row = 0; row < nrows; ++row) {
+        const int k = (int)(row % 3);
+        for (int32_t e = iptr[row]; e < iptr[row + 1]; ++e) {
+            const int64_t cell = icol[e] - k * nc;
+            const int b = (int)(cell / B3), loc = (int)(cell % B3);
+            if (loc / step[k] % B > 0) {
+                low[e] = (int32_t)(cell - step[k]);
+            } else {
+                int q[3];
+                for (int a = 0; a < 3; ++a) q[a] = blk[3 * b + a] - p.lo[a] - (a == k);
+                const int sb = q[k] < 0 ? -1 : map[((size_t)q[2] * p.nb[1] + q[1]) * p.nb[0] + q[0]];
+                if (sb >= 0) low[e] = (int32_t)((int64_t)sb * B3 + loc + (B - 1) * step[k]);
+            }
+            dptr[cell + 1]++;
+            if (low[e] >= 0) dptr[low[e] + 1]++;
+        }
+    }
+    for (int64_t c = 0; c < nc; ++c) dptr[c + 1] += dptr[c];
+    std::vector<int32_t> rptr(3 * nc + 1), col(std::max<size_t>(nnz + dptr[nc], 1)), fill(dptr.begin(), dptr.end() - 1);
+    std::vector<double> val(col.size());
+    LGF_HIP(hipMemcpy(rptr.data(), p.r_ptr.p, 4 * rptr.size(), hipMemcpyDeviceToHost));
+    if (nnz) {
+        LGF_HIP(hipMemcpy(col.data(), p.r_col.p, 4 * nnz, hipMemcpyDeviceToHost));
+        LGF_HIP(hipMemcpy(val.data(), p.r_val.p, 8 * nnz, hipMemcpyDeviceToHost));
+    }
+    auto put = [&](int64_t cell, int64_t row, double w) {
+        const size_t q = nnz + fill[cell]++;
+        col[q] = (int32_t)row;
+        val[q] = w;
+    };
+    for (int64_t row = 0; row < nrows; ++row)
+        for (int32_t e = iptr[row]; e < iptr[row + 1]; ++e) {
+            put(icol[e] - (row % 3) * nc, row, ival[e]);
+            if (low[e] >= 0) put(low[e], row, -ival[e]);
+        }
+    std::vector<int32_t> srow, sptr(1, 0);
+    for (int64_t f = 0; f < 3 * nc; ++f)
+        if (rptr[f + 1] > rptr[f]) {
+            srow.push_back((int32_t)f);
+            sptr.push_back(rptr[f + 1]);
+        }
+    p.nfr = (int)srow.size();
+    for (int64_t c = 0; c < nc; ++c)
+        if (dptr[c + 1] > dptr[c]) {
+            srow.push_back((int32_t)(3 * nc + c));
+            sptr.push_back((int32_t)nnz + dptr[c + 1]);
+        }
+    p.ncr = (int)srow.size() - p.nfr;
+    srow.resize(std::max<size_t>(srow.size(), 1));
+    int rc;
+    if ((rc = p.i_low.reserve(4 * low.size())) || (rc = p.s_row.reserve(4 * srow.size())) ||
+        (rc = p.s_ptr.reserve(4 * sptr.size())) || (rc = p.s_col.reserve(4 * col.size())) ||
+        (rc = p.s_val.reserve(8 * val.size())))
+        return rc;
+    LGF_HIP(hipMemcpy(p.i_low.p, low.data(), 4 * low.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(p.s_row.p, srow.data(), 4 * srow.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(p.s_ptr.p, sptr.data(), 4 * sptr.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(p.s_col.p, col.data(), 4 * col.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(p.s_val.p, val.data(), 8 * val.size(), hipMemcpyHostToDevice));
+    p.grad = true;
+    return LGFIB_OK;
+}
+
 size_t ib_cache_trim(lgfib_ctx *ctx, size_t cap, int64_t *left) {
     if (!ctx->ib_cache) {
         if (left) *left = 0;
@@ -351,74 +440,118 @@ __global__ __launch_bounds__(256) void k_csr_gather(const int *__restrict__ ptr,
     if (live && lane == 0) y[row] = (Out)(acc * scale);
 }
 
-// I with the CG's p.Ap fused in: y = I faces, and *out = sum_row p[row] y[row]
-// (rows summed per block in a fixed order, then across blocks as above)
-template <typename In, int L>
-__global__ __launch_bounds__(256) void k_csr_gather_dot(const int *__restrict__ ptr, const int *__restrict__ col,
-                                                        const double *__restrict__ val, const In *__restrict__ x,
-                                                        double *__restrict__ y, int nrows,
-                                                        const double *__restrict__ p, double *part,
-                                                        unsigned *counter, double *out) {
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int row = (int)(t / L), lane = (int)(t % L);
+// Sum of n partial sums, the same value in every lane of every wavefront: each
+// lane's share first, so that its loads can be issued ahead of other work
+__device__ __forceinline__ double part_lane(const double *__restrict__ part, int n) {
+    const int i0 = threadIdx.x % 64;
+    double v = part[min(i0, n - 1)];
+    v = i0 < n ? v : 0.0;
+    for (int i = i0 + 64; i < n; i += 64) v += part[i];
+    return v;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+    return v;
+}
+
+// The CG's search direction of the iteration about to start, p = r + beta
+// p_old with beta = rs / rs_old (zero at the start of a sweep, when p_old is
+// not used); rs and rs_old come as nred partial sums each.
+struct CgDir {
+    const double *r, *p_old, *rs, *rs_old;
+    double *p;
+    int nred, n;
+};
+
+// faces = R x and c = G^T R x in one launch, eight lanes a row, on the rows
+// that some marker reaches (the others hold zeros from the start).  Short
+// gathers bound by latency: at 2200 markers R took 4.2 us and G^T of its faces
+// another 3.8; with the cells' rows folded on the host both run side by side in
+// 5.5 us, 7.4 with DIR.  Over all faces and cells instead of the reached rows (of
+// 290,000) it took 10.5 us.  DIR: x is the CG's new search direction, formed
+// as R r + beta R p_old so that beta's sums are off the gathers' path, and
+// stored for the update.
+template <bool DIR, typename In, typename Out>
+__global__ __launch_bounds__(256) void k_spread(const int *__restrict__ ptr, const int *__restrict__ col,
+                                                const double *__restrict__ val, const int *__restrict__ out,
+                                                const In *__restrict__ x, CgDir dir, Out *__restrict__ faces,
+                                                Out *__restrict__ c, int nrows, int nf) {
+    constexpr int L = 8;
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    const int row = t / L, lane = t % L;
     const bool live = row < nrows;
-    double acc = 0.0;
+    double acc = 0.0, old = 0.0, rs = 0.0, ro = 0.0, r0 = 0.0, p0 = 0.0;
+    if constexpr (DIR) {   // these loads run ahead of the gathers
+        rs = part_lane(dir.rs, dir.nred);
+        ro = part_lane(dir.rs_old, dir.nred);
+        r0 = dir.r[min(t, dir.n - 1)];
+        p0 = dir.p_old[min(t, dir.n - 1)];
+    }
     if (live) {
         const int e1 = ptr[row + 1];
-        for (int e = ptr[row] + lane; e < e1; e += L) acc += val[e] * (double)x[col[e]];
+        for (int e = ptr[row] + lane; e < e1; e += L) {
+            const int j = col[e];
+            const double w = val[e];
+            if constexpr (DIR) {
+                acc += w * dir.r[j];
+                old += w * dir.p_old[j];
+            } else {
+                acc += w * (double)x[j];
+            }
+        }
+    }
+    if constexpr (DIR) {
+        rs = wave_sum(rs);
+        ro = wave_sum(ro);
+        const double beta = ro > 0.0 ? rs / ro : 0.0;
+        if (t < dir.n) dir.p[t] = beta == 0.0 ? r0 : r0 + beta * p0;
+        for (int i = t + gridDim.x * 256; i < dir.n; i += gridDim.x * 256)
+            dir.p[i] = beta == 0.0 ? dir.r[i] : dir.r[i] + beta * dir.p_old[i];
+        if (beta != 0.0) acc += beta * old;
     }
 #pragma unroll
     for (int m = L / 2; m > 0; m >>= 1) acc += __shfl_xor(acc, m, L);
-    double contrib = 0.0;
     if (live && lane == 0) {
-        y[row] = acc;
-        contrib = acc * p[row];
+        const int o = out[row];
+        if (o < nf) faces[o] = (Out)acc;
+        else c[o - nf] = (Out)acc;
     }
-    grid_sum_to(contrib, part, counter, out);
 }
 
-// c(n) = sc sum_k u^(k)(n) - u^(k)(n + e_k)   (G^T u; faces outside are zero)
-template <typename Real>
-__global__ void k_grad_adjoint(BlockMapDev bm, const Real *__restrict__ u, Real *__restrict__ c, int nblk, Real sc) {
-    const int B = bm.B, B3 = B * B * B;
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)nblk * B3) return;
-    const int b = (int)(t / B3), cell = (int)(t % B3);
-    const int lx = cell % B, ly = (cell / B) % B, lz = cell / (B * B);
-    const int bx = bm.blocks[3 * b], by = bm.blocks[3 * b + 1], bz = bm.blocks[3 * b + 2];
-    Real s = 0;
-    for (int k = 0; k < 3; ++k) {
-        s += u[((size_t)k * nblk + b) * B3 + cell];
-        int nx = lx + (k == 0), ny = ly + (k == 1), nz = lz + (k == 2);
-        int sb = b, cbx = bx, cby = by, cbz = bz;
-        if (nx == B) { nx = 0; cbx += 1; }
-        if (ny == B) { ny = 0; cby += 1; }
-        if (nz == B) { nz = 0; cbz += 1; }
-        if (cbx != bx || cby != by || cbz != bz) sb = bm.slot(cbx, cby, cbz);
-        if (sb >= 0) s -= u[((size_t)k * nblk + sb) * B3 + (nz * B + ny) * B + nx];
+// y = I (a + G d), sixteen lanes a row: the gradient is formed where I reads
+// it, so that a + G d is never stored (a launch of 3.2 us at 2200 markers).
+// dot_p: part[block] receives the block's share of dot_p . y, in row order.
+template <typename In, typename Out>
+__global__ __launch_bounds__(256) void k_gather(const int *__restrict__ ptr, const int *__restrict__ col,
+                                                const int *__restrict__ low, const double *__restrict__ val,
+                                                const In *__restrict__ a, const In *__restrict__ d,
+                                                Out *__restrict__ y, int nrows, int nc,
+                                                const double *__restrict__ dot_p, double *__restrict__ part) {
+    __shared__ double sh[16];
+    const long t = (long)blockIdx.x * 256 + threadIdx.x;
+    const int row = (int)(t / 16), lane = (int)(t % 16);
+    const bool live = row < nrows;
+    double acc = 0.0;
+    if (live) {
+        const int e1 = ptr[row + 1], shift = (row % 3) * nc;
+        for (int e = ptr[row] + lane; e < e1; e += 16) {
+            const int f = col[e], m = low[e];
+            const In dm = d[max(m, 0)];
+            acc += val[e] * (double)(a[f] + (d[f - shift] - (m >= 0 ? dm : (In)0)));
+        }
     }
-    c[t] = sc * s;
-}
-
-// e^(k)(n) += sc (d(n) - d(n - e_k))          (G d, accumulated into faces)
-template <typename Real>
-__global__ void k_grad_acc(BlockMapDev bm, const Real *__restrict__ d, Real *__restrict__ e, int nblk, Real sc) {
-    const int B = bm.B, B3 = B * B * B;
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)nblk * B3) return;
-    const int b = (int)(t / B3), cell = (int)(t % B3);
-    const int lx = cell % B, ly = (cell / B) % B, lz = cell / (B * B);
-    const int bx = bm.blocks[3 * b], by = bm.blocks[3 * b + 1], bz = bm.blocks[3 * b + 2];
-    const Real dc = d[t];
-    for (int k = 0; k < 3; ++k) {
-        int nx = lx - (k == 0), ny = ly - (k == 1), nz = lz - (k == 2);
-        int sb = b, cbx = bx, cby = by, cbz = bz;
-        if (nx < 0) { nx = B - 1; cbx -= 1; }
-        if (ny < 0) { ny = B - 1; cby -= 1; }
-        if (nz < 0) { nz = B - 1; cbz -= 1; }
-        if (cbx != bx || cby != by || cbz != bz) sb = bm.slot(cbx, cby, cbz);
-        const Real dm = sb >= 0 ? d[(size_t)sb * B3 + (nz * B + ny) * B + nx] : (Real)0;
-        e[((size_t)k * nblk + b) * B3 + cell] += sc * (dc - dm);
+#pragma unroll
+    for (int m = 8; m > 0; m >>= 1) acc += __shfl_xor(acc, m, 16);
+    if (live && lane == 0) y[row] = (Out)acc;
+    if (!dot_p) return;
+    if (lane == 0) sh[threadIdx.x / 16] = live ? acc * dot_p[row] : 0.0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v += sh[q];
+        part[blockIdx.x] = v;
     }
 }
 
@@ -462,29 +595,37 @@ static int launch_interpolate(lgfib_ctx *ctx, const IbPlan &p, const In *faces, 
     return LGFIB_OK;
 }
 
-template <typename Real>
-static int launch_grad_adjoint(lgfib_ctx *ctx, const IbPlan &p, const Real *u, Real *c, hipStream_t st,
-                               Real sc = (Real)1) {
-    const size_t n = (size_t)p.nblk * p.B * p.B * p.B;
-    if (!n) return LGFIB_OK;
-    ProfScope ps(ctx, "k_grad_adjoint", st);
-    hipLaunchKernelGGL(k_grad_adjoint<Real>, dim3(nblocks(n, 256)), dim3(256), 0, st, devmap(p), u, c, p.nblk, sc);
+// faces = R x, c = G^T R x (plan with ib_plan_grad; faces and c hold zeros where
+// no marker reaches); dir: the CG's direction
+template <typename In, typename Out>
+static int launch_spread(lgfib_ctx *ctx, const IbPlan &p, const In *x, const CgDir *dir, Out *faces, Out *c,
+                         hipStream_t st) {
+    ProfScope ps(ctx, "k_spread", st);
+    const int nf = 3 * p.nblk * p.B * p.B * p.B, nrows = p.nfr + p.ncr;
+    const dim3 grid(std::max(1u, nblocks(8 * (size_t)nrows, 256)));
+    if (dir)
+        hipLaunchKernelGGL((k_spread<true, In, Out>), grid, dim3(256), 0, st, p.s_ptr.as<int>(), p.s_col.as<int>(),
+                           p.s_val.as<double>(), p.s_row.as<int>(), x, *dir, faces, c, nrows, nf);
+    else
+        hipLaunchKernelGGL((k_spread<false, In, Out>), grid, dim3(256), 0, st, p.s_ptr.as<int>(), p.s_col.as<int>(),
+                           p.s_val.as<double>(), p.s_row.as<int>(), x, CgDir{}, faces, c, nrows, nf);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
 }
 
-template <typename Real>
-static int launch_grad_acc(lgfib_ctx *ctx, const IbPlan &p, const Real *d, Real *e, hipStream_t st,
-                           Real sc = (Real)1) {
-    const size_t n = (size_t)p.nblk * p.B * p.B * p.B;
-    if (!n) return LGFIB_OK;
-    ProfScope ps(ctx, "k_grad_acc", st);
-    hipLaunchKernelGGL(k_grad_acc<Real>, dim3(nblocks(n, 256)), dim3(256), 0, st, devmap(p), d, e, p.nblk, sc);
+static unsigned gather_blocks(int NL) { return nblocks(16 * 3 * (size_t)NL, 256); }
+
+// y = I (a + G d); with dot_p the blocks' shares of dot_p . y go to part
+template <typename In, typename Out>
+static int launch_gather(lgfib_ctx *ctx, const IbPlan &p, const In *a, const In *d, Out *y, const double *dot_p,
+                         double *part, hipStream_t st) {
+    ProfScope ps(ctx, "k_gather", st);
+    hipLaunchKernelGGL((k_gather<In, Out>), dim3(gather_blocks(p.NL)), dim3(256), 0, st, p.i_ptr.as<int>(),
+                       p.i_col.as<int>(), p.i_low.as<int>(), p.i_val.as<double>(), a, d, y, 3 * p.NL,
+                       p.nblk * p.B * p.B * p.B, dot_p, part);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
 }
-
-// ------------------------------------------------------------ body blocks
 
 static int body_blocks(int kernel, const double *X, int NL, int B, std::vector<int32_t> &out) {
     struct H {
@@ -592,8 +733,9 @@ extern "C" int ib_interpolate(lgfib_ctx *ctx, int kernel, const double *X, int N
 
 namespace lgfib {
 constexpr int kRedBlocks = 256;   // blocks of a grid-wide reduction
-// partial-sum slots: a fused reduction may run one per block of its launch
-inline size_t red_parts(int NL) { return std::max<size_t>(kRedBlocks, (16 * 3 * (size_t)NL + 255) / 256 + 1); }
+// partial-sum slots: r.r of even and odd CG iterations, then one per block of
+// k_gather (or of k_dot)
+inline size_t red_parts(int NL) { return 2 * kRedBlocks + std::max<size_t>(kRedBlocks, (16 * 3 * (size_t)NL + 255) / 256); }
 }
 
 struct ib_system {
@@ -604,11 +746,12 @@ struct ib_system {
     std::vector<int32_t> blocks;
     lgf_table_t tbl = -1;
     std::shared_ptr<IbPlan> plan;   // held: pinned in the context's cache
-    // work fields per precision: faces g, faces a, cells c, cells d
+    // work fields per precision: faces g, faces a, cells c, cells d; g and c are
+    // written by k_spread alone
     DevBuf g[2], af[2], c[2], d[2];
     // CG vectors (FP64)
-    DevBuf r, p, ap, x, tmp, red, scal, cnt;
-    double *host_scal = nullptr;       // pinned; the CG's r.r lands in [8], [9]
+    DevBuf r, p, p2, ap, x, tmp, red, scal, cnt;   // p, p2: the search direction of even / odd iterations
+    double *host_scal = nullptr;       // pinned; [64 ..]: the CG's r.r as 2 x kRedBlocks partial sums
     double *host_scal_dev = nullptr;   // its device address
     hipEvent_t ev[2] = {nullptr, nullptr};
     // captured CG iterations per matvec precision (index 0 FP32, 1 FP64) and
@@ -630,36 +773,23 @@ namespace lgfib {
 // y = C x = I [E(a) + G K^{-1} G^T] R x with the field work in Real; x and y
 // may be held in another type (the FP32 matvec of the CG reads and writes its
 // FP64 vectors directly).
+// dir: x is the CG's new direction, and its dot product with y goes to part.
 template <typename Real, typename VIn, typename VOut>
-static int schur_apply_t(ib_system *s, const VIn *x, VOut *y, hipStream_t st, const double *dot_p = nullptr,
-                         double *dot_out = nullptr) {
+static int schur_apply_t(ib_system *s, const VIn *x, VOut *y, hipStream_t st, const CgDir *dir = nullptr) {
     lgfib_ctx *ctx = s->ctx;
     const int pi = sizeof(Real) == 8 ? 1 : 0;
     const int prec = pi ? LGF_F64 : LGF_F32;
     Real *g = s->g[pi].as<Real>(), *af = s->af[pi].as<Real>(), *c = s->c[pi].as<Real>(), *d = s->d[pi].as<Real>();
     int rc;
-    if ((rc = launch_regularize<VIn, Real>(ctx, *s->plan, 1.0, x, g, st))) return rc;
+    if ((rc = launch_spread<VIn, Real>(ctx, *s->plan, x, dir, g, c, st))) return rc;
     if ((rc = lgf_if_apply(ctx, s->a, s->B, s->blocks.data(), s->nblk, s->blocks.data(), s->nblk, 3, prec, g, af,
                            (lgfib_stream_t)st)))
         return rc;
-    if ((rc = launch_grad_adjoint<Real>(ctx, *s->plan, g, c, st))) return rc;
     if ((rc = lgf_poisson_apply(ctx, s->tbl, s->B, s->blocks.data(), s->nblk, s->blocks.data(), s->nblk, 1, prec, 1.0,
                                 c, d, 0, (lgfib_stream_t)st)))
         return rc;
-    if ((rc = launch_grad_acc<Real>(ctx, *s->plan, d, af, st))) return rc;
-    if constexpr (std::is_same<VOut, double>::value) {
-        if (dot_p) {   // y = I af with p.y fused (CG iteration)
-            const IbPlan &P = *s->plan;
-            const int nrows = 3 * P.NL;
-            ProfScope ps(ctx, "k_interpolate", st);
-            hipLaunchKernelGGL((k_csr_gather_dot<Real, 16>), dim3(nblocks(16 * (size_t)nrows, 256)), dim3(256), 0, st,
-                               P.i_ptr.as<int>(), P.i_col.as<int>(), P.i_val.as<double>(), af, y, nrows, dot_p,
-                               s->red.as<double>(), s->cnt.as<unsigned>(), dot_out);
-            LGF_HIP(hipGetLastError());
-            return LGFIB_OK;
-        }
-    }
-    return launch_interpolate<Real, VOut>(ctx, *s->plan, af, y, st);
+    return launch_gather<Real, VOut>(ctx, *s->plan, af, d, y, dir ? dir->p : nullptr,
+                                     s->red.as<double>() + 2 * kRedBlocks, st);
 }
 
 }  // namespace lgfib
@@ -684,6 +814,7 @@ extern "C" int ib_system_create(lgfib_ctx *ctx, int kernel, const double *X, int
     s->X.assign(X, X + 3 * (size_t)NL);
     s->blocks.assign(blocks, blocks + 3 * (size_t)nblk);
     if ((rc = build_ib_plan(ctx, kernel, X, NL, B, blocks, nblk, s->plan))) return rc;
+    if ((rc = ib_plan_grad(*s->plan))) return rc;
     int ext[3];
     for (int q = 0; q < 3; ++q) ext[q] = s->plan->nb[q] * B - 1;
     if ((rc = lgf_table_build(ctx, LGF_KIND_K, a, ext, nullptr, &s->tbl))) return rc;
@@ -696,12 +827,17 @@ extern "C" int ib_system_create(lgfib_ctx *ctx, int kernel, const double *X, int
         if ((rc = s->d[pi].reserve(nblk * B3 * es))) return rc;
     }
     const size_t nv = 3 * (size_t)NL * 8;
-    if ((rc = s->r.reserve(nv)) || (rc = s->p.reserve(nv)) || (rc = s->ap.reserve(nv)) || (rc = s->x.reserve(nv)) ||
+    if ((rc = s->r.reserve(nv)) || (rc = s->p.reserve(nv)) || (rc = s->p2.reserve(nv)) || (rc = s->ap.reserve(nv)) || (rc = s->x.reserve(nv)) ||
         (rc = s->tmp.reserve(nv)) || (rc = s->red.reserve(red_parts(NL) * 8)) || (rc = s->scal.reserve(64 * 8)) ||
         (rc = s->cnt.reserve(64)))
         return rc;
     LGF_HIP(hipMemset(s->cnt.p, 0, 64));
-    LGF_HIP(hipHostMalloc((void **)&s->host_scal, 64 * sizeof(double), hipHostMallocDefault));
+    for (int pi = 0; pi < 2; ++pi) {   // k_spread writes only the rows that markers reach
+        LGF_HIP(hipMemset(s->g[pi].p, 0, s->g[pi].bytes));
+        LGF_HIP(hipMemset(s->c[pi].p, 0, s->c[pi].bytes));
+    }
+    LGF_HIP(hipStreamSynchronize(nullptr));
+    LGF_HIP(hipHostMalloc((void **)&s->host_scal, (64 + 2 * kRedBlocks) * sizeof(double), hipHostMallocDefault));
     LGF_HIP(hipHostGetDevicePointer((void **)&s->host_scal_dev, s->host_scal, 0));
     for (auto &e : s->ev) LGF_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     *out = s.release();
@@ -747,32 +883,52 @@ __global__ __launch_bounds__(256) void k_dot(const double *__restrict__ a, const
     grid_sum_to(s, part, counter, out);
 }
 
-// scal layout: [1] pAp, [2] scratch dot, [3] bb, [4] final residual,
-// [6 + (j & 1)] r.r of CG iteration j (the slots alternate, so no copy is
-// needed between iterations).
 // x += alpha p ; r -= alpha Ap, alpha = rs / pAp (0 once the search direction
 // vanishes: the host tests convergence one iteration late, so a converged
-// solve may run one more, harmless, iteration); then out = r.r
+// solve may run one more, harmless, iteration); then each workgroup's share of
+// r.r to part and to pinned host memory.  pAp and rs arrive as partial sums
+// that every wavefront adds itself, in the same order: no atomics and no
+// fences.  At 6600 unknowns a whole update in one workgroup (both reductions
+// and the direction) took 9.2 us, this kernel with a last-workgroup sum 6.4,
+// and as it is 4.5.
 __global__ __launch_bounds__(256) void k_cg_xr(double *__restrict__ x, double *__restrict__ r,
                                                const double *__restrict__ p, const double *__restrict__ ap,
-                                               double *scal, int rs_slot, int out_slot, size_t n, double *part,
-                                               unsigned *counter, double *host_out) {
-    const double alpha = scal[1] > 0.0 ? scal[rs_slot] / scal[1] : 0.0;
+                                               const double *__restrict__ pap_part, int npart,
+                                               const double *__restrict__ rs_part, int nred, size_t n,
+                                               double *__restrict__ part, double *__restrict__ host_part) {
+    __shared__ double sh[4];
+    const size_t i0 = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const bool in = i0 < n;   // the first elements' loads are in flight beside the partial sums'
+    const double x0 = in ? x[i0] : 0.0, p0 = in ? p[i0] : 0.0, r0 = in ? r[i0] : 0.0, a0 = in ? ap[i0] : 0.0;
+    double pap = part_lane(pap_part, npart), rs = part_lane(rs_part, nred);
+    pap = wave_sum(pap);
+    rs = wave_sum(rs);
+    const double alpha = pap > 0.0 ? rs / pap : 0.0;
     double s = 0.0;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+    if (in) {
+        x[i0] = x0 + alpha * p0;
+        const double ri = r0 - alpha * a0;
+        r[i0] = ri;
+        s = ri * ri;
+    }
+    for (size_t i = i0 + (size_t)gridDim.x * 256; i < n; i += (size_t)gridDim.x * 256) {
         x[i] += alpha * p[i];
         const double ri = r[i] - alpha * ap[i];
         r[i] = ri;
         s += ri * ri;
     }
-    grid_sum_to(s, part, counter, scal + out_slot, host_out);
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
+    if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double v = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+        part[blockIdx.x] = v;
+        host_part[blockIdx.x] = v;
+    }
 }
 
-// The whole CG update for vectors small enough for one workgroup (the
-// marker systems): pAp = p.Ap, alpha = rs / pAp, x += alpha p,
-// r -= alpha Ap, rs_new = r.r, beta = rs_new / rs, p = r + beta p -- one
-// launch, no cross-workgroup traffic, sums in a fixed order.  rs_new also
-// goes to pinned host memory for the convergence test.
+// dot products of vectors small enough for one workgroup (the marker systems)
 constexpr int kStepThreads = 1024;
 constexpr size_t kStepMaxN = 65536;
 
@@ -792,34 +948,6 @@ __device__ inline double wg_sum(double v, double *sh) {
     return t;
 }
 
-__global__ __launch_bounds__(kStepThreads) void k_cg_step(double *__restrict__ x, double *__restrict__ r,
-                                                          double *__restrict__ p, const double *__restrict__ ap,
-                                                          double *scal, int rs_slot, int new_slot, int n,
-                                                          double *host_out) {
-    __shared__ double sh[kStepThreads];
-    const int tid = threadIdx.x;
-    double s = 0.0;
-    for (int i = tid; i < n; i += kStepThreads) s += p[i] * ap[i];
-    const double pap = wg_sum(s, sh);
-    const double rs = scal[rs_slot];
-    const double alpha = pap > 0.0 ? rs / pap : 0.0;
-    double q = 0.0;
-    for (int i = tid; i < n; i += kStepThreads) {
-        x[i] += alpha * p[i];
-        const double ri = r[i] - alpha * ap[i];
-        r[i] = ri;
-        q += ri * ri;
-    }
-    const double rsn = wg_sum(q, sh);
-    const double beta = rs > 0.0 ? rsn / rs : 0.0;
-    for (int i = tid; i < n; i += kStepThreads) p[i] = r[i] + beta * p[i];
-    if (tid == 0) {
-        scal[1] = pap;
-        scal[new_slot] = rsn;
-        if (host_out) *host_out = rsn;
-    }
-}
-
 // a.b in one workgroup (small vectors)
 __global__ __launch_bounds__(kStepThreads) void k_dot_small(const double *__restrict__ a,
                                                             const double *__restrict__ b, int n, double *out) {
@@ -830,71 +958,11 @@ __global__ __launch_bounds__(kStepThreads) void k_dot_small(const double *__rest
     if (threadIdx.x == 0) *out = t;
 }
 
-// p = r + beta p, beta = rs_new / rs
-__global__ void k_cg_p(double *__restrict__ p, const double *__restrict__ r, const double *__restrict__ scal,
-                       int rs_slot, int new_slot, size_t n) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double beta = scal[rs_slot] > 0.0 ? scal[new_slot] / scal[rs_slot] : 0.0;
-    p[i] = r[i] + beta * p[i];
-}
-
 // r = b - y
 __global__ void k_sub(double *__restrict__ r, const double *__restrict__ b, const double *__restrict__ y, size_t n) {
     const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n) r[t] = b[t] - y[t];
 }
-
-// The same update with each thread's E elements of p, Ap and r held in
-// registers: every vector is read once instead of up to twice (n <= E
-// kStepThreads).  Elements are visited in the same order, so the sums, and
-// with them the iterates, are bitwise those of k_cg_step.
-template <int E>
-__global__ __launch_bounds__(kStepThreads) void k_cg_step_reg(double *__restrict__ x, double *__restrict__ r,
-                                                              double *__restrict__ p, const double *__restrict__ ap,
-                                                              double *scal, int rs_slot, int new_slot, int n,
-                                                              double *host_out) {
-    __shared__ double sh[kStepThreads];
-    const int tid = threadIdx.x;
-    double pv[E], av[E], rv[E];
-    double s = 0.0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int i = tid + e * kStepThreads;
-        const bool in = i < n;
-        pv[e] = in ? p[i] : 0.0;
-        av[e] = in ? ap[i] : 0.0;
-        rv[e] = in ? r[i] : 0.0;
-        if (in) s += pv[e] * av[e];
-    }
-    const double pap = wg_sum(s, sh);
-    const double rs = scal[rs_slot];
-    const double alpha = pap > 0.0 ? rs / pap : 0.0;
-    double q = 0.0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int i = tid + e * kStepThreads;
-        if (i < n) {
-            x[i] += alpha * pv[e];
-            rv[e] = rv[e] - alpha * av[e];
-            r[i] = rv[e];
-            q += rv[e] * rv[e];
-        }
-    }
-    const double rsn = wg_sum(q, sh);
-    const double beta = rs > 0.0 ? rsn / rs : 0.0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int i = tid + e * kStepThreads;
-        if (i < n) p[i] = rv[e] + beta * pv[e];
-    }
-    if (tid == 0) {
-        scal[1] = pap;
-        scal[new_slot] = rsn;
-        if (host_out) *host_out = rsn;
-    }
-}
-constexpr int kStepRegE = 8, kStepRegE2 = 16;   // n up to 8192, then up to 16384
 
 __global__ void k_axpy(double *__restrict__ y, const double *__restrict__ x, double a, size_t n) {
     const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -903,15 +971,15 @@ __global__ void k_axpy(double *__restrict__ y, const double *__restrict__ x, dou
 
 static unsigned red_blocks(size_t n) { return (unsigned)std::min<size_t>(kRedBlocks, std::max<size_t>(1, (n + 255) / 256)); }
 
-static int dot(ib_system *s, const double *a, const double *b, int slot, hipStream_t st) {
+static int dot(ib_system *s, const double *a, const double *b, double *out, hipStream_t st) {
     const size_t n = 3 * (size_t)s->NL;
     if (n <= kStepMaxN) {
-        hipLaunchKernelGGL(k_dot_small, dim3(1), dim3(kStepThreads), 0, st, a, b, (int)n, s->scal.as<double>() + slot);
+        hipLaunchKernelGGL(k_dot_small, dim3(1), dim3(kStepThreads), 0, st, a, b, (int)n, out);
         LGF_HIP(hipGetLastError());
         return LGFIB_OK;
     }
-    hipLaunchKernelGGL(k_dot, dim3(red_blocks(n)), dim3(256), 0, st, a, b, n, s->red.as<double>(),
-                       s->cnt.as<unsigned>(), s->scal.as<double>() + slot);
+    hipLaunchKernelGGL(k_dot, dim3(red_blocks(n)), dim3(256), 0, st, a, b, n, s->red.as<double>() + 2 * kRedBlocks,
+                       s->cnt.as<unsigned>(), out);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
 }
@@ -924,40 +992,34 @@ static int read_scal(ib_system *s, int slot, double *v, hipStream_t st) {
 }
 
 // y = C x with an FP64 interface, field work in prec
-static int matvec(ib_system *s, int prec, const double *x, double *y, hipStream_t st, double *dot_out = nullptr) {
-    const double *dp = dot_out ? x : nullptr;   // fused x.y into *dot_out
-    if (prec == LGF_F64) return schur_apply_t<double, double, double>(s, x, y, st, dp, dot_out);
-    return schur_apply_t<float, double, double>(s, x, y, st, dp, dot_out);
+static int matvec(ib_system *s, int prec, const double *x, double *y, hipStream_t st, const CgDir *dir = nullptr) {
+    if (prec == LGF_F64) return schur_apply_t<double, double, double>(s, x, y, st, dir);
+    return schur_apply_t<float, double, double>(s, x, y, st, dir);
 }
 
-// One CG iteration (matvec, p.Ap, x/r update with r.r, the copy of r.r to
-// pinned memory, p update) for iterations of parity `par`.
+// One CG iteration (new direction, matvec, p.Ap, x/r update with r.r, the copy
+// of r.r to pinned memory) for iterations of parity `par`.
 static int cg_iteration(ib_system *s, int prec, int par, hipStream_t st) {
     const size_t n = 3 * (size_t)s->NL;
-    double *x = s->x.as<double>(), *r = s->r.as<double>(), *p = s->p.as<double>(), *ap = s->ap.as<double>();
-    double *scal = s->scal.as<double>();
-    const int rs_slot = 6 + par, new_slot = 6 + (1 - par);
+    double *x = s->x.as<double>(), *r = s->r.as<double>(), *ap = s->ap.as<double>(), *red = s->red.as<double>();
+    double *p[2] = {s->p.as<double>(), s->p2.as<double>()};
+    double *rs = red + par * kRedBlocks, *rs_next = red + (1 - par) * kRedBlocks;   // rs_next holds the previous one
+    const int nred = (int)red_blocks(n);
+    const CgDir dir{r, p[1 - par], rs, rs_next, p[par], nred, (int)n};
     int rc;
-    if (n <= kStepMaxN) {
-        if ((rc = matvec(s, prec, p, ap, st))) return rc;
-        if (n <= (size_t)kStepRegE * kStepThreads)
-            hipLaunchKernelGGL(k_cg_step_reg<kStepRegE>, dim3(1), dim3(kStepThreads), 0, st, x, r, p, ap, scal, rs_slot,
-                               new_slot, (int)n, s->host_scal_dev + 8 + par);
-        else if (n <= (size_t)kStepRegE2 * kStepThreads)
-            hipLaunchKernelGGL(k_cg_step_reg<kStepRegE2>, dim3(1), dim3(kStepThreads), 0, st, x, r, p, ap, scal,
-                               rs_slot, new_slot, (int)n, s->host_scal_dev + 8 + par);
-        else
-            hipLaunchKernelGGL(k_cg_step, dim3(1), dim3(kStepThreads), 0, st, x, r, p, ap, scal, rs_slot, new_slot,
-                               (int)n, s->host_scal_dev + 8 + par);
-        LGF_HIP(hipGetLastError());
-        return LGFIB_OK;
-    }
-    if ((rc = matvec(s, prec, p, ap, st, scal + 1))) return rc;   // ap = C p, scal[1] = p.ap
-    hipLaunchKernelGGL(k_cg_xr, dim3(red_blocks(n)), dim3(256), 0, st, x, r, p, ap, scal, rs_slot, new_slot, n,
-                       s->red.as<double>(), s->cnt.as<unsigned>(), s->host_scal_dev + 8 + par);
-    hipLaunchKernelGGL(k_cg_p, dim3(nblocks(n, 256)), dim3(256), 0, st, p, r, scal, rs_slot, new_slot, n);
+    if ((rc = matvec(s, prec, p[par], ap, st, &dir))) return rc;
+    hipLaunchKernelGGL(k_cg_xr, dim3(nred), dim3(256), 0, st, x, r, p[par], ap, red + 2 * kRedBlocks,
+                       (int)gather_blocks(s->NL), rs, nred, n, rs_next, s->host_scal_dev + 64 + par * kRedBlocks);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
+}
+
+// r.r after an iteration of parity par, once its event has passed
+static double cg_rr(const ib_system *s, int par) {
+    const double *p = s->host_scal + 64 + par * kRedBlocks;
+    double v = 0.0;
+    for (unsigned i = 0; i < red_blocks(3 * (size_t)s->NL); ++i) v += p[i];
+    return v;
 }
 
 static bool cg_graphs_wanted() {
@@ -1049,8 +1111,8 @@ static int direct_solve(ib_system *s, const double *b, double *f, ib_solve_stats
         if ((rc = matvec(s, LGF_F64, f, ap, st))) return rc;
         hipLaunchKernelGGL(k_sub, dim3(nblocks(n, 256)), dim3(256), 0, st, r, b, ap, (size_t)n);
         LGF_HIP(hipGetLastError());
-        if ((rc = dot(s, b, b, 3, st)) || (rc = read_scal(s, 3, &bb, st))) return rc;
-        if ((rc = dot(s, r, r, 4, st)) || (rc = read_scal(s, 4, &rr, st))) return rc;
+        if ((rc = dot(s, b, b, s->scal.as<double>() + 3, st)) || (rc = read_scal(s, 3, &bb, st))) return rc;
+        if ((rc = dot(s, r, r, s->scal.as<double>() + 4, st)) || (rc = read_scal(s, 4, &rr, st))) return rc;
         S->rel_residual = bb > 0.0 ? sqrt(rr / bb) : 0.0;
     }
     return LGFIB_OK;
@@ -1079,11 +1141,11 @@ extern "C" int ib_force_solve(lgfib_ctx *ctx, ib_system *sys, int prec, const do
     LGF_HIP(hipEventRecord(e0, st));
     const size_t n = 3 * (size_t)sys->NL;
     const unsigned gb = nblocks(n, 256);
-    double *x = sys->x.as<double>(), *r = sys->r.as<double>(), *p = sys->p.as<double>(), *ap = sys->ap.as<double>(),
+    double *x = sys->x.as<double>(), *r = sys->r.as<double>(),
            *tmp = sys->tmp.as<double>(), *scal = sys->scal.as<double>();
     int rc;
     double bb;
-    if ((rc = dot(sys, b, b, 3, st)) || (rc = read_scal(sys, 3, &bb, st))) return rc;
+    if ((rc = dot(sys, b, b, scal + 3, st)) || (rc = read_scal(sys, 3, &bb, st))) return rc;
     const double bnorm = sqrt(bb);
     if (bnorm == 0.0) {
         LGF_HIP(hipMemsetAsync(f, 0, n * 8, st));
@@ -1109,7 +1171,7 @@ extern "C" int ib_force_solve(lgfib_ctx *ctx, ib_system *sys, int prec, const do
         LGF_HIP(hipMemcpyAsync(x, x0, n * 8, hipMemcpyDeviceToDevice, st));
         if ((rc = matvec(sys, LGF_F64, x, tmp, st))) return rc;
         hipLaunchKernelGGL(k_sub, dim3(gb), dim3(256), 0, st, r, b, tmp, n);
-        if ((rc = dot(sys, r, r, 2, st)) || (rc = read_scal(sys, 2, &rr, st))) return rc;
+        if ((rc = dot(sys, r, r, scal + 2, st)) || (rc = read_scal(sys, 2, &rr, st))) return rc;
         S->restarts++;
         if (!(sqrt(rr) <= bnorm)) use_x0 = false;
     }
@@ -1131,8 +1193,9 @@ extern "C" int ib_force_solve(lgfib_ctx *ctx, ib_system *sys, int prec, const do
     double rsn = rr;
     while (true_r > target && it < maxit) {
         const double sweep_stop = prec == LGF_F64 ? target : std::max(target * 0.5, true_r * 1e-4);
-        LGF_HIP(hipMemcpyAsync(p, r, n * 8, hipMemcpyDeviceToDevice, st));
-        if ((rc = dot(sys, r, r, 6, st))) return rc;
+        // r.r as the only partial sum, and no previous one: beta = 0
+        LGF_HIP(hipMemsetAsync(sys->red.p, 0, 2 * kRedBlocks * sizeof(double), st));
+        if ((rc = dot(sys, r, r, sys->red.as<double>(), st))) return rc;
         bool graphs = false;
         if ((rc = cg_graphs(sys, prec, st, &graphs))) return rc;
         if (graphs) S->graphs = 1;
@@ -1149,19 +1212,19 @@ extern "C" int ib_force_solve(lgfib_ctx *ctx, ib_system *sys, int prec, const do
             ++j;
             if (j >= 2) {   // test iteration j-2 (0-based) while j-1 runs
                 LGF_HIP(hipEventSynchronize(sys->ev[j & 1]));
-                rsn = sys->host_scal[8 + (j & 1)];
+                rsn = cg_rr(sys, j & 1);
                 if (sqrt(rsn) <= sweep_stop || !std::isfinite(rsn)) stop = true;
             }
         }
         // the last queued iteration's residual
         LGF_HIP(hipEventSynchronize(sys->ev[(j - 1) & 1]));
-        rsn = sys->host_scal[8 + ((j - 1) & 1)];
+        rsn = cg_rr(sys, (j - 1) & 1);
         if (prec == LGF_F64) {
             true_r = sqrt(rsn);
         } else {
             if ((rc = matvec(sys, LGF_F64, x, tmp, st))) return rc;
             hipLaunchKernelGGL(k_sub, dim3(gb), dim3(256), 0, st, r, b, tmp, n);
-            if ((rc = dot(sys, r, r, 2, st)) || (rc = read_scal(sys, 2, &rr, st))) return rc;
+            if ((rc = dot(sys, r, r, scal + 2, st)) || (rc = read_scal(sys, 2, &rr, st))) return rc;
             S->restarts++;
             true_r = sqrt(rr);
         }
@@ -1171,7 +1234,7 @@ extern "C" int ib_force_solve(lgfib_ctx *ctx, ib_system *sys, int prec, const do
     if (prec == LGF_F64) {
         if ((rc = matvec(sys, LGF_F64, x, tmp, st))) return rc;
         hipLaunchKernelGGL(k_sub, dim3(gb), dim3(256), 0, st, tmp, b, tmp, n);
-        if ((rc = dot(sys, tmp, tmp, 4, st)) || (rc = read_scal(sys, 4, &rr, st))) return rc;
+        if ((rc = dot(sys, tmp, tmp, scal + 4, st)) || (rc = read_scal(sys, 4, &rr, st))) return rc;
         true_r = sqrt(rr);
     }
     LGF_HIP(hipMemcpyAsync(f, x, n * 8, hipMemcpyDeviceToDevice, st));
@@ -1484,8 +1547,8 @@ static int schur_dense_cols(ib_system *s, int j0, int K, double *C, long ld, hip
     for (int k = 0; k < K; ++k) {
         hipLaunchKernelGGL(k_unit, dim3(nblocks(n, 256)), dim3(256), 0, st, e + (size_t)k * n, n, j0 + k);
         LGF_HIP(hipGetLastError());
-        if ((rc = launch_regularize<double, double>(ctx, P, 1.0, e + (size_t)k * n, g + k * nf, st))) return rc;
-        if ((rc = launch_grad_adjoint<double>(ctx, P, g + k * nf, c + k * nc, st))) return rc;
+        if ((rc = launch_spread<double, double>(ctx, P, e + (size_t)k * n, nullptr, g + k * nf, c + k * nc, st)))
+            return rc;
     }
     for (int c0 = 0; c0 < 3 * K; c0 += 8) {
         const int m = std::min(8, 3 * K - c0);
@@ -1497,8 +1560,9 @@ static int schur_dense_cols(ib_system *s, int j0, int K, double *C, long ld, hip
                                 1.0, c, d, 0, (lgfib_stream_t)st)))
         return rc;
     for (int k = 0; k < K; ++k) {
-        if ((rc = launch_grad_acc<double>(ctx, P, d + k * nc, af + k * nf, st))) return rc;
-        if ((rc = launch_interpolate<double, double>(ctx, P, af + k * nf, y + (size_t)k * n, st))) return rc;
+        if ((rc = launch_gather<double, double>(ctx, P, af + k * nf, d + k * nc, y + (size_t)k * n, nullptr, nullptr,
+                                                st)))
+            return rc;
         hipLaunchKernelGGL(k_put_column, dim3(nblocks(n, 256)), dim3(256), 0, st, C, ld, j0 + k,
                            (const double *)(y + (size_t)k * n), n);
         LGF_HIP(hipGetLastError());
@@ -1515,6 +1579,9 @@ extern "C" int ib_schur_dense(lgfib_ctx *ctx, ib_system *sys, double *C, int ld,
     const size_t nc = (size_t)sys->nblk * sys->B * sys->B * sys->B;
     int rc;
     if ((rc = sys->dense_cols.reserve(((size_t)kDenseCols * (8 * nc + 2 * (size_t)n)) * sizeof(double)))) return rc;
+    // g and c of the columns (schur_dense_cols' layout): zeros where no marker reaches
+    LGF_HIP(hipMemsetAsync(sys->dense_cols.p, 0, kDenseCols * 3 * nc * sizeof(double), st));
+    LGF_HIP(hipMemsetAsync(sys->dense_cols.as<double>() + kDenseCols * 6 * nc, 0, kDenseCols * nc * sizeof(double), st));
     for (int j = 0; j < n; j += kDenseCols)
         if ((rc = schur_dense_cols(sys, j, std::min(kDenseCols, n - j), C, (long)ld, st))) return rc;
     LGF_HIP(hipStreamSynchronize(st));
@@ -1780,7 +1847,7 @@ extern "C" int ib_force_smooth(lgfib_ctx *ctx, ib_system *sys, const double *f, 
         LGF_HIP(hipGetLastError());
         if ((rc = launch_regularize<double, double>(ctx, P, 1.0, ones, sys->gamma.as<double>(), st))) return rc;
     }
-    double *g = sys->g[1].as<double>();
+    double *g = sys->af[1].as<double>();
     if ((rc = launch_regularize<double, double>(ctx, P, 1.0, f, g, st))) return rc;
     hipLaunchKernelGGL(k_div_guard, dim3(nblocks(nf, 256)), dim3(256), 0, st, g, (const double *)sys->gamma.as<double>(),
                        nf);

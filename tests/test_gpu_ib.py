@@ -299,3 +299,34 @@ def test_force_smoothing_matches_oracle(ctx, small_sphere):
     lg.ib_force_smooth(ctx, sys, fd, fd)   # in place
     assert torch.equal(fd, out)
     sys.close()
+
+
+@pytest.mark.parametrize("kernel", [ROMA3, SMOOTH3])
+@pytest.mark.parametrize("NL,B", [(1, 4), (7, 4), (7, 16), (33, 8)])
+def test_schur_matvec_block_edges(ctx, NL, B, kernel):
+    """The gather and spread operators with the gradient folded in, where their
+    rows are fewest and where the cell below a face lies in another block or
+    outside the blocks (markers on block corners; B = 4 blocks are cut by every
+    support): FP64 <= 1e-12 and FP32 <= 1e-5 of the oracle's matvec (the bars of
+    the tests above), again after the system's work fields served the force
+    smoothing, and bit for bit the same."""
+    g = np.random.Generator(np.random.PCG64(60 + NL + B))
+    X = g.uniform(14.0, 26.0, size=(NL, 3))
+    X[0] = [16.0, 16.0, 16.0]
+    blocks = lg.ib_body_blocks(kernel, X, B)
+    origin, mask = oracle.block_mask(blocks, B)
+    alpha = 0.1
+    gk = oracle.lgf_k_table(alpha, *np.array(mask.shape[::-1]))
+    x = g.standard_normal((NL, 3))
+    ref = oracle.schur_matvec(x, X, kernel, alpha, gk, mask, origin)
+    sys = lg.ib_system_create(ctx, kernel, X, B, blocks, alpha)
+    for dtype, bar in ((torch.float64, 1e-12), (torch.float32, 1e-5)):
+        xd, y = torch.from_numpy(x).cuda().to(dtype), torch.zeros((NL, 3), dtype=dtype, device="cuda")
+        lg.ib_schur_apply(ctx, sys, xd, y)
+        assert _relerr(y.cpu().numpy(), ref) < bar
+        f = torch.from_numpy(x).cuda()
+        lg.ib_force_smooth(ctx, sys, f, torch.zeros_like(f))
+        y2 = torch.zeros_like(y)
+        lg.ib_schur_apply(ctx, sys, xd, y2)
+        assert torch.equal(y, y2)
+    sys.close()

@@ -304,7 +304,7 @@ template <typename C, int P, int NP> struct ZMul {
 template <typename C, int P, int NPMAX>
 __device__ __forceinline__ void zconv_body(const BoxGeo &g, C *__restrict__ X2,
                                            const typename RealOf<C>::T *__restrict__ ghat, typename RealOf<C>::T scale,
-                                           const C *__restrict__ twg, int ntiles, int bid) {
+                                           const C *__restrict__ twg, int ntiles, int parts, int bid) {
     using R = typename RealOf<C>::T;
     constexpr int ZNP = np_zconv<P, (int)sizeof(R)>();
     constexpr int NP = ZNP < NPMAX ? ZNP : NPMAX;
@@ -319,12 +319,16 @@ __device__ __forceinline__ void zconv_body(const BoxGeo &g, C *__restrict__ X2,
     C *twt = reinterpret_cast<C *>(gh + NP * (Ph + 1));   // 8-byte aligned: NP (Ph + 1) is even
     const int Kxp = g.Kxp;
     const int nkt = Kxp / NP;
-    if (bid >= ntiles) return;
-    const int t = bid;
+    if (bid >= ntiles * parts) return;
+    const int t = bid / parts;
     const int k0 = (t % nkt) * NP, kyh = t / nkt;
     const int H1 = g.P1 / 2 + 1;
     const int nky = (kyh == 0 || 2 * kyh == g.P1) ? 1 : 2;
     const int nitems = nky * g.ncomp;
+    // this workgroup's share of the tile's columns
+    const int per = (2 * g.ncomp + parts - 1) / parts;
+    const int i0 = (bid % parts) * per, i1 = min(nitems, i0 + per);
+    if (i0 >= i1) return;
     // element e of a thread's column slice sits zstep * e past its first one
     // (consecutive threads walk pencils, then z)
     const size_t zrow = (size_t)g.P1 * Kxp;
@@ -346,7 +350,7 @@ __device__ __forceinline__ void zconv_body(const BoxGeo &g, C *__restrict__ X2,
             if (NL % kFftThreads == 0 || idx < NL) pre[e] = ld_pencil<nt_on(kNtZLd)>(&b[e * zstep]);
         }
     };
-    load(0);   // first, so that its latency overlaps the table loads below
+    load(i0);   // first, so that its latency overlaps the table loads below
     load_tw(tw, twg, P);
     for (int idx = threadIdx.x; idx < NP * (Ph + 1); idx += kFftThreads) {
         const int p = idx % NP, kz = idx / NP;
@@ -354,14 +358,14 @@ __device__ __forceinline__ void zconv_body(const BoxGeo &g, C *__restrict__ X2,
     }
     // all twiddle powers of the last stage (forward and inverse share it)
     last_stage_twiddles<C, P, RadixOf<P>::last>(twt, twg);
-    for (int item = 0; item < nitems; ++item) {
+    for (int item = i0; item < i1; ++item) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int idx = threadIdx.x + e * kFftThreads;
             if (NL % kFftThreads == 0 || idx < NL) s[idx] = pre[e];
         }
         lds_barrier();
-        if (item + 1 < nitems) load(item + 1);
+        if (item + 1 < i1) load(item + 1);
         sfft_tt<C, P, NP, 1, NP, true, false, Ph, 0>(s, tw, twt, ZMul<C, P, NP>{gh});
         sfft_tt<C, P, NP, 1, NP, true, true, 0, Ph>(s, tw, twt);
         C *b = base(item);
@@ -561,9 +565,9 @@ template <typename C, int P, int NPMAX>
 __global__ __launch_bounds__(kFftThreads) void kf_zconv(BoxGeo g, C *__restrict__ X2,
                                                         const typename RealOf<C>::T *__restrict__ ghat,
                                                         typename RealOf<C>::T scale, const C *__restrict__ twg,
-                                                        int ntiles) {
-    if ((int)blockIdx.x >= ntiles) return;
-    zconv_body<C, P, NPMAX>(g, X2, ghat, scale, twg, ntiles, xcd_remap(blockIdx.x, ntiles));
+                                                        int ntiles, int parts) {
+    if ((int)blockIdx.x >= ntiles * parts) return;
+    zconv_body<C, P, NPMAX>(g, X2, ghat, scale, twg, ntiles, parts, xcd_remap(blockIdx.x, ntiles * parts));
 }
 template <typename C, int P, int NPMAX>
 __global__ __launch_bounds__(kFftThreads) void kf_yinv(BoxGeo g, const C *__restrict__ X2, C *__restrict__ X1,
@@ -595,7 +599,7 @@ __device__ __forceinline__ void kb_item(const FastJob *__restrict__ jobs, const 
     else if constexpr (PASS == kPassYF)
         yfwd_body<C32, P, NPMAX>(J.g, (const C32 *)J.in, (C32 *)J.out, J.tw, J.n, J.T, bid);
     else if constexpr (PASS == kPassZ)
-        zconv_body<C32, P, NPMAX>(J.g, (C32 *)J.out, J.ghat, J.scale, J.tw, J.n, bid);
+        zconv_body<C32, P, NPMAX>(J.g, (C32 *)J.out, J.ghat, J.scale, J.tw, J.n, J.T, bid);
     else if constexpr (PASS == kPassYI)
         yinv_body<C32, P, NPMAX>(J.g, (const C32 *)J.in, (C32 *)J.out, J.tw, J.n, J.T, bid);
     else
@@ -805,25 +809,38 @@ static int x_np_cap(bool fwd) {
     return fwd ? capf : capi;
 }
 
+// Workgroups per tile of the FP32 z pass.  A tile holds the columns ky and P1 - ky
+// of every component, one after the other with the next one's loads in flight;
+// a box with fewer than 1024 tiles (four a compute unit) spreads them over two
+// workgroups, or one per column, until there are that many: a 64^3-cell box of
+// three components 54 -> 49 us, of one 34.1 -> 32.3, the CG force solve on 2200
+// markers (its box has 400 tiles) 2.4% faster.  At 2048 the 150-block set slows
+// (60 -> 64 us), and the FP64 pass measured slower split at every size tried.
+constexpr int kZTiles = 1024;
+static int z_parts(int ntiles, int ncomp) {
+    if (ntiles >= kZTiles) return 1;
+    return 2 * ntiles >= kZTiles ? 2 : 2 * ncomp;
+}
+
 template <int P>
 static void launch_zconv_np(int cap, dim3 grid, size_t sm, hipStream_t st, const BoxGeo &g, C32 *X2,
-                            const float *ghat, float scale, const C32 *tw, int ntiles) {
+                            const float *ghat, float scale, const C32 *tw, int ntiles, int parts) {
     if (cap == 4)
-        hipLaunchKernelGGL((kf_zconv<C32, P, 4>), grid, dim3(kFftThreads), sm, st, g, X2, ghat, scale, tw, ntiles);
+        hipLaunchKernelGGL((kf_zconv<C32, P, 4>), grid, dim3(kFftThreads), sm, st, g, X2, ghat, scale, tw, ntiles, parts);
     else if (cap == 8)
-        hipLaunchKernelGGL((kf_zconv<C32, P, 8>), grid, dim3(kFftThreads), sm, st, g, X2, ghat, scale, tw, ntiles);
+        hipLaunchKernelGGL((kf_zconv<C32, P, 8>), grid, dim3(kFftThreads), sm, st, g, X2, ghat, scale, tw, ntiles, parts);
     else
-        hipLaunchKernelGGL((kf_zconv<C32, P, 16>), grid, dim3(kFftThreads), sm, st, g, X2, ghat, scale, tw, ntiles);
+        hipLaunchKernelGGL((kf_zconv<C32, P, 16>), grid, dim3(kFftThreads), sm, st, g, X2, ghat, scale, tw, ntiles, parts);
 }
 
 int launch_fast_zconv(const BoxGeo &g, C32 *X2, const float *ghat, float scale, const C32 *tw, hipStream_t st) {
     const int NP = std::min(fast_np_zconv(g.P2), z_np_cap());
-    const int ntiles = g.Kxp / NP * (g.P1 / 2 + 1);
-    dim3 grid(ntiles);
+    const int ntiles = g.Kxp / NP * (g.P1 / 2 + 1), parts = z_parts(ntiles, g.ncomp);
+    dim3 grid(ntiles * parts);
     const size_t sm = sizeof(C32) * (size_t)(g.P2 / 2 + NP * g.P2 + g.P2) + sizeof(float) * (size_t)NP * (g.P2 / 2 + 1);
     const int cap = z_np_cap();
     switch (g.P2) {
-#define X(n) case n: launch_zconv_np<n>(cap, grid, sm, st, g, X2, ghat, scale, tw, ntiles); break;
+#define X(n) case n: launch_zconv_np<n>(cap, grid, sm, st, g, X2, ghat, scale, tw, ntiles, parts); break;
         LGF_FAST_SIZES(X)
 #undef X
     default: return fail(LGFIB_EINVAL, "no specialised z pass");
@@ -850,7 +867,8 @@ template <int P>
 static void launch_z64(dim3 grid, size_t sm, hipStream_t st, const BoxGeo &g, double2 *X2, const double *ghat,
                        double scale, const double2 *tw, int ntiles) {
     if constexpr (z64_ok<P>())
-        hipLaunchKernelGGL((kf_zconv<double2, P, 8>), grid, dim3(kFftThreads), sm, st, g, X2, ghat, scale, tw, ntiles);
+        hipLaunchKernelGGL((kf_zconv<double2, P, 8>), grid, dim3(kFftThreads), sm, st, g, X2, ghat, scale, tw, ntiles,
+                           1);
 }
 
 int launch_fast_zconv_f64(const BoxGeo &g, double2 *X2, const double *ghat, double scale, const double2 *tw,

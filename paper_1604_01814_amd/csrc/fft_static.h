@@ -11,6 +11,7 @@
 // complex products.
 #pragma once
 
+#include <type_traits>
 #include <utility>
 
 #include "fft_lds.h"
@@ -56,11 +57,56 @@ template <typename C, bool INV> struct Dft<C, 16, INV> {
 
 // Composite radices in registers, R = R1 x R2 (Cooley-Tukey, n = R2 n1 + n2,
 // k = k1 + R1 k2): R1-point DFTs over n1, twiddles W_R^(n2 k1), R2-point
-// DFTs over n2.  They let long transforms run in fewer LDS stages (384 as
-// 24 x 16: 0.50 -> 0.44 ms for the plate z pass; 640 as 40 x 16 was slower,
-// its 80-register butterflies cost occupancy).  TwiddleTable<R> holds cos / sin (2 pi m / R)
-// for m = 0 .. (R1 - 1)(R2 - 1), rounded to double.
+// DFTs over n2.  They let transforms run in fewer LDS stages (384 as 24 x 16:
+// 0.50 -> 0.44 ms for the plate z pass).  TwiddleTable<R> holds cos / sin
+// (2 pi m / R) for m = 0 .. (R1 - 1)(R2 - 1), rounded to double.
 template <int R> struct TwiddleTable;
+template <> struct TwiddleTable<6> {
+    static constexpr int N = 3;
+    static constexpr double c[3] = {
+        1, 0.5, -0.5};
+    static constexpr double s[3] = {
+        0, 0.8660254037844386, 0.8660254037844386};
+};
+template <> struct TwiddleTable<9> {
+    static constexpr int N = 5;
+    static constexpr double c[5] = {
+        1, 0.766044443118978, 0.17364817766693036, -0.5, -0.9396926207859084};
+    static constexpr double s[5] = {
+        0, 0.6427876096865394, 0.984807753012208, 0.8660254037844386, 0.3420201433256687};
+};
+template <> struct TwiddleTable<10> {
+    static constexpr int N = 5;
+    static constexpr double c[5] = {
+        1, 0.8090169943749475, 0.30901699437494745, -0.30901699437494745, -0.8090169943749475};
+    static constexpr double s[5] = {
+        0, 0.5877852522924731, 0.9510565162951535, 0.9510565162951535, 0.5877852522924731};
+};
+template <> struct TwiddleTable<12> {
+    static constexpr int N = 7;
+    static constexpr double c[7] = {
+        1, 0.8660254037844386, 0.5, 0, -0.5, -0.8660254037844386, -1};
+    static constexpr double s[7] = {
+        0, 0.5, 0.8660254037844386, 1, 0.8660254037844386, 0.5, 0};
+};
+template <> struct TwiddleTable<15> {
+    static constexpr int N = 9;
+    static constexpr double c[9] = {
+        1, 0.9135454576426009, 0.6691306063588582, 0.30901699437494745, -0.10452846326765347, -0.5,
+        -0.8090169943749475, -0.9781476007338057, -0.9781476007338057};
+    static constexpr double s[9] = {
+        0, 0.4067366430758002, 0.7431448254773942, 0.9510565162951535, 0.9945218953682733, 0.8660254037844386,
+        0.5877852522924731, 0.20791169081775934, -0.20791169081775934};
+};
+template <> struct TwiddleTable<18> {
+    static constexpr int N = 9;
+    static constexpr double c[9] = {
+        1, 0.9396926207859084, 0.766044443118978, 0.5, 0.17364817766693036, -0.17364817766693036, -0.5,
+        -0.766044443118978, -0.9396926207859084};
+    static constexpr double s[9] = {
+        0, 0.3420201433256687, 0.6427876096865394, 0.8660254037844386, 0.984807753012208, 0.984807753012208,
+        0.8660254037844386, 0.6427876096865394, 0.3420201433256687};
+};
 template <> struct TwiddleTable<20> {
     static constexpr int N = 13;
     static constexpr double c[13] = {
@@ -83,24 +129,18 @@ template <> struct TwiddleTable<24> {
         0.96592582628906831, 1, 0.96592582628906831, 0.86602540378443871, 0.70710678118654757,
         0.49999999999999994, 0.25881904510252102, 0, -0.25881904510252079, -0.49999999999999972};
 };
-template <> struct TwiddleTable<40> {
-    static constexpr int N = 29;
-    static constexpr double c[29] = {
-        1, 0.98768834059513777, 0.95105651629515353, 0.8910065241883679, 0.80901699437494745,
-        0.70710678118654757, 0.58778525229247314, 0.4539904997395468, 0.30901699437494745,
-        0.15643446504023092, 0, -0.15643446504023059, -0.30901699437494734, -0.45399049973954669,
-        -0.58778525229247303, -0.70710678118654746, -0.80901699437494734, -0.89100652418836779,
-        -0.95105651629515353, -0.98768834059513766, -1, -0.98768834059513777, -0.95105651629515375,
-        -0.8910065241883679, -0.80901699437494756, -0.70710678118654768, -0.58778525229247325,
-        -0.45399049973954692, -0.30901699437494756};
-    static constexpr double s[29] = {
-        0, 0.15643446504023087, 0.3090169943749474, 0.45399049973954675, 0.58778525229247314,
-        0.70710678118654746, 0.80901699437494745, 0.89100652418836779, 0.95105651629515353,
-        0.98768834059513777, 1, 0.98768834059513777, 0.95105651629515364, 0.8910065241883679,
-        0.80901699437494745, 0.70710678118654757, 0.58778525229247325, 0.45399049973954686,
-        0.30901699437494751, 0.15643446504023098, 0, -0.15643446504023073, -0.3090169943749469,
-        -0.45399049973954669, -0.58778525229247303, -0.70710678118654746, -0.80901699437494734,
-        -0.89100652418836779, -0.95105651629515353};
+template <> struct TwiddleTable<30> {
+    static constexpr int N = 21;
+    static constexpr double c[21] = {
+        1, 0.9781476007338057, 0.9135454576426009, 0.8090169943749475, 0.6691306063588582, 0.5,
+        0.30901699437494745, 0.10452846326765347, -0.10452846326765347, -0.30901699437494745, -0.5,
+        -0.6691306063588582, -0.8090169943749475, -0.9135454576426009, -0.9781476007338057, -1,
+        -0.9781476007338057, -0.9135454576426009, -0.8090169943749475, -0.6691306063588582, -0.5};
+    static constexpr double s[21] = {
+        0, 0.20791169081775934, 0.4067366430758002, 0.5877852522924731, 0.7431448254773942, 0.8660254037844386,
+        0.9510565162951535, 0.9945218953682733, 0.9945218953682733, 0.9510565162951535, 0.8660254037844386,
+        0.7431448254773942, 0.5877852522924731, 0.4067366430758002, 0.20791169081775934, 0,
+        -0.20791169081775934, -0.4067366430758002, -0.5877852522924731, -0.7431448254773942, -0.8660254037844386};
 };
 
 template <typename C, bool INV, int R1, int R2> struct DftComposite {
@@ -133,9 +173,15 @@ template <typename C, bool INV, int R1, int R2> struct DftComposite {
         }
     }
 };
+template <typename C, bool INV> struct Dft<C, 6, INV> : DftComposite<C, INV, 3, 2> {};
+template <typename C, bool INV> struct Dft<C, 9, INV> : DftComposite<C, INV, 3, 3> {};
+template <typename C, bool INV> struct Dft<C, 10, INV> : DftComposite<C, INV, 5, 2> {};
+template <typename C, bool INV> struct Dft<C, 12, INV> : DftComposite<C, INV, 3, 4> {};
+template <typename C, bool INV> struct Dft<C, 15, INV> : DftComposite<C, INV, 5, 3> {};
+template <typename C, bool INV> struct Dft<C, 18, INV> : DftComposite<C, INV, 9, 2> {};
+template <typename C, bool INV> struct Dft<C, 30, INV> : DftComposite<C, INV, 6, 5> {};
 template <typename C, bool INV> struct Dft<C, 20, INV> : DftComposite<C, INV, 5, 4> {};
 template <typename C, bool INV> struct Dft<C, 24, INV> : DftComposite<C, INV, 3, 8> {};
-template <typename C, bool INV> struct Dft<C, 40, INV> : DftComposite<C, INV, 5, 8> {};
 
 // twiddle power w^r from the exact powers w1, w2, w4, w8
 template <typename C, int r>
@@ -292,8 +338,23 @@ struct SStages<C, P, NP, SP, SJ, PFAST, INV, ZIN, ZOUT, Post, TT, Ns, R, Rest...
     }
 };
 
-// Radix lists of the specialised lengths (product = P, at most four stages).
-// A radix above 16 may only come first (its stage needs no twiddles).
+// Radix lists of the specialised lengths (product = P, at most three stages).
+// A radix above 16 may only come first (its stage needs no twiddles).  Every
+// stage costs a round trip through LDS with two barriers, a large butterfly
+// registers and with them workgroups in flight, so a length takes two stages
+// with the first radix as small as that allows: a radix of 16 last and 6 to 24
+// first.  Sum of the five passes of a cubic box, three components (480: one),
+// the former list in brackets:
+//   144 (3 3 16)    FP32  79 ->  67 us   FP64  109 ->  93 us
+//   160 (40 4)           110 ->  80            211 -> 120
+//   192 (24 8)           106 -> 102            177 -> 161
+//   240 (3 5 16)         200 -> 155            330 -> 278
+//   288 (24 3 4)         327 -> 288            577 -> 510
+//   480 (3 5 2 16)       685 -> 531           1059 -> 987
+//   960 (3 5 4 16)      8056 -> 7805 (one component)
+// and 96 (24 4) 61 -> 53 us in FP64.  A first radix of 30 pays in FP32 only (480 in
+// FP64: 1156 us, 5 x 6 x 16 is kept there), 36 x 16 and 40 x 16 do not; 384 as
+// 3 x 8 x 16 and 320 as 4 x 5 x 16 measured slower.
 template <int P> struct RadixOf;
 template <int... Rs> struct LastOf;
 template <int R> struct LastOf<R> { static constexpr int value = R; };
@@ -311,24 +372,31 @@ LGF_RADICES(32, 2, 16)
 LGF_RADICES(48, 3, 16)
 LGF_RADICES(64, 4, 16)
 LGF_RADICES(80, 5, 16)
-LGF_RADICES(96, 24, 4)
+LGF_RADICES(96, 6, 16)
 LGF_RADICES(128, 8, 16)
-LGF_RADICES(144, 3, 3, 16)
-LGF_RADICES(160, 40, 4)
-LGF_RADICES(192, 24, 8)
-LGF_RADICES(240, 3, 5, 16)
+LGF_RADICES(144, 9, 16)
+LGF_RADICES(160, 10, 16)
+LGF_RADICES(192, 12, 16)
+LGF_RADICES(240, 15, 16)
 LGF_RADICES(256, 16, 16)
-LGF_RADICES(288, 24, 3, 4)
+LGF_RADICES(288, 18, 16)
 LGF_RADICES(320, 20, 16)
 LGF_RADICES(384, 24, 16)
-LGF_RADICES(480, 3, 5, 2, 16)
 LGF_RADICES(512, 2, 16, 16)
 LGF_RADICES(576, 24, 3, 8)
 LGF_RADICES(640, 5, 8, 16)
 LGF_RADICES(768, 3, 16, 16)
-LGF_RADICES(960, 3, 5, 4, 16)
+LGF_RADICES(960, 5, 12, 16)
 LGF_RADICES(1024, 4, 16, 16)
 #undef LGF_RADICES
+// the lists may differ by precision (the last radix may not: the twiddle table is its)
+template <> struct RadixOf<480> {
+    template <typename C, int NP, int SP, int SJ, bool PFAST, bool INV, int ZIN, int ZOUT, class Post, bool TT>
+    using Run = std::conditional_t<sizeof(C) == 8,
+                                   SStages<C, 480, NP, SP, SJ, PFAST, INV, ZIN, ZOUT, Post, TT, 1, 30, 16>,
+                                   SStages<C, 480, NP, SP, SJ, PFAST, INV, ZIN, ZOUT, Post, TT, 1, 5, 6, 16>>;
+    static constexpr int last = 16;
+};
 
 template <typename C, int P, int NP, int SP, int SJ, bool PFAST, bool INV, int ZIN = 0, int ZOUT = 0,
           class Post = NoPost>

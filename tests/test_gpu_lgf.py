@@ -389,3 +389,25 @@ def test_poisson_fp64_x_passes_match_the_general_path(ctx, B, nb):
             out.append(u.cpu().numpy() - (u0.cpu().numpy() if acc else 0.0))
     for u in out[1:]:
         assert _relerr(u, out[0]) <= 1e-13
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("B,n", [(8, 6), (8, 9), (8, 10), (8, 12), (8, 15), (8, 18), (16, 15), (16, 30)])
+def test_poisson_two_stage_lengths_on_each_axis(ctx, B, n, dtype):
+    """Transforms of 96 to 480 and 960 points (2 n B) along x, y and z in turn:
+    the two end blocks of a row as sources and targets, against the oracle's
+    direct sum at the file's bars."""
+    g = np.random.Generator(np.random.PCG64(1604 + 10 * n + B))
+    f = g.standard_normal((1, 2, B, B, B))
+    for ax in range(3):
+        b = np.zeros((2, 3), dtype=np.int32)
+        b[1, ax] = n - 1
+        t = lg.lgf_table_build(ctx, lg.LGF_KIND_L, 0.0, _span_ext(b, b, B))
+        fd = _dev(f, dtype)
+        ud = torch.zeros_like(fd)
+        lg.lgf_poisson_apply(ctx, t, B, b, b, fd, ud)
+        cells = workloads.block_cells(b, B)
+        pick = g.choice(len(cells), 200, replace=False)
+        ext = [int(v) + 1 for v in _span_ext(b, b, B)]
+        ref = oracle.conv_direct(oracle.lgf_table(*ext), cells, f.reshape(-1), cells[pick])
+        assert _relerr(ud.cpu().numpy().reshape(-1)[pick], ref) < TOL[dtype]

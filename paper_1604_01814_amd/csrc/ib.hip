@@ -77,6 +77,14 @@ static inline void support_range(int kernel, double X, double c, long long *lo, 
     *cnt = (int)(2 * hw) + 1;
 }
 
+// R and G^T R as one sparse operator on marker vectors: the rows are the nfr
+// faces and then the cells that some marker reaches; row[q] is row q's face, or
+// the number of faces plus its cell.
+struct SpreadOp {
+    int nfr = 0, nrows = 0;
+    DevBuf row, ptr, col, val;
+};
+
 struct IbPlan {
     int kernel = 0, NL = 0, B = 0, nblk = 0;
     int lo[3] = {0, 0, 0}, nb[3] = {0, 0, 0};   // block-map box
@@ -89,12 +97,10 @@ struct IbPlan {
     int64_t nnz = 0;
     // with the gradient folded in (ib_plan_grad, built for force systems):
     // i_low[e]: the cell below entry e's face along its component, -1 outside
-    // the blocks;  R and G^T R as one operator whose rows are the nfr faces and
-    // then the ncr cells that some marker reaches: s_row[q] is row q's face, or
-    // the number of faces plus its cell
+    // the blocks
     bool grad = false;
-    int nfr = 0, ncr = 0;
-    DevBuf i_low, s_row, s_ptr, s_col, s_val;
+    DevBuf i_low;
+    SpreadOp spread;
 };
 
 struct IbKey {
@@ -271,57 +277,68 @@ static int build_ib_plan(lgfib_ctx *ctx, int kernel, const double *X, int NL, in
     return LGFIB_OK;
 }
 
-// The operators of the force Schur complement with the staggered gradient
-// folded in.  (G d)^(k)(n) = d(n) - d(n - e_k) reads, for entry e of I, the
-// face's cell and the cell below it; c = G^T u has face (n, k) add to c(n) and
-// subtract from c(n - e_k), so G^T R has two entries for each one of R.
-static int ib_plan_grad(IbPlan &p) {
-    if (p.grad) return LGFIB_OK;
+// a set of cell blocks on the host: block map over the box lo, nb
+struct CellSet {
+    const int *lo, *nb;
+    const std::vector<int32_t> &map;
+    int slot(int x, int y, int z) const {
+        x -= lo[0], y -= lo[1], z -= lo[2];
+        if (x < 0 || y < 0 || z < 0 || x >= nb[0] || y >= nb[1] || z >= nb[2]) return -1;
+        return map[((size_t)z * nb[1] + y) * nb[0] + x];
+    }
+};
+
+// The spread operator of plan p with its cells numbered on the set cs (which
+// holds p's blocks).  c = G^T u has face (n, k) add to c(n) and subtract from
+// c(n - e_k), so G^T R has two entries for each one of R, one where the cell
+// below lies outside cs.  low (nullable) receives that cell per entry of I.
+static int build_spread(const IbPlan &p, const CellSet &cs, int64_t ncell, SpreadOp &op, std::vector<int32_t> *low_out) {
     const int B = p.B, B3 = B * B * B;
     const int64_t nc = (int64_t)p.nblk * B3, nrows = 3ll * p.NL;
-    const size_t nnz = (size_t)p.nnz, nmap = (size_t)p.nb[0] * p.nb[1] * p.nb[2];
-    std::vector<int32_t> iptr(nrows + 1), icol(std::max<size_t>(nnz, 1)), low(std::max<size_t>(nnz, 1), -1), map(nmap),
-        blk(3 * (size_t)p.nblk), dptr(nc + 1, 0);
+    const size_t nnz = (size_t)p.nnz;
+    if (ncell + 3 * nc > INT32_MAX - 1 || 3 * (int64_t)nnz > INT32_MAX - 1)
+        return fail(LGFIB_ERANGE, "IB operator too large");
+    std::vector<int32_t> iptr(nrows + 1), icol(std::max<size_t>(nnz, 1)), own(std::max<size_t>(nnz, 1)),
+        low(std::max<size_t>(nnz, 1), -1), blk(3 * (size_t)p.nblk), rptr(3 * nc + 1), dptr(ncell + 1, 0);
     std::vector<double> ival(std::max<size_t>(nnz, 1));
     LGF_HIP(hipMemcpy(iptr.data(), p.i_ptr.p, 4 * iptr.size(), hipMemcpyDeviceToHost));
     LGF_HIP(hipMemcpy(icol.data(), p.i_col.p, 4 * icol.size(), hipMemcpyDeviceToHost));
     LGF_HIP(hipMemcpy(ival.data(), p.i_val.p, 8 * ival.size(), hipMemcpyDeviceToHost));
-    LGF_HIP(hipMemcpy(map.data(), p.map.p, 4 * nmap, hipMemcpyDeviceToHost));
+    LGF_HIP(hipMemcpy(rptr.data(), p.r_ptr.p, 4 * rptr.size(), hipMemcpyDeviceToHost));
     if (p.nblk) LGF_HIP(hipMemcpy(blk.data(), p.blocks.p, 4 * blk.size(), hipMemcpyDeviceToHost));
     const int step[3] = {1, B, B * B};
     for (int64_t row = 0; row < nrows; ++row) {
         const int k = (int)(row % 3);
         for (int32_t e = iptr[row]; e < iptr[row + 1]; ++e) {
             const int64_t cell = icol[e] - k * nc;
-            const int b = (int)(cell / B3), loc = (int)(cell % B3);
+            const int loc = (int)(cell % B3);
+            const int32_t *q = &blk[3 * (cell / B3)];
+            own[e] = cs.slot(q[0], q[1], q[2]) * B3 + loc;
             if (loc / step[k] % B > 0) {
-                low[e] = (int32_t)(cell - step[k]);
+                low[e] = own[e] - step[k];
             } else {
-                int q[3];
-                for (int a = 0; a < 3; ++a) q[a] = blk[3 * b + a] - p.lo[a] - (a == k);
-                const int sb = q[k] < 0 ? -1 : map[((size_t)q[2] * p.nb[1] + q[1]) * p.nb[0] + q[0]];
-                if (sb >= 0) low[e] = (int32_t)((int64_t)sb * B3 + loc + (B - 1) * step[k]);
+                const int sb = cs.slot(q[0] - (k == 0), q[1] - (k == 1), q[2] - (k == 2));
+                if (sb >= 0) low[e] = sb * B3 + loc + (B - 1) * step[k];
             }
-            dptr[cell + 1]++;
+            dptr[own[e] + 1]++;
             if (low[e] >= 0) dptr[low[e] + 1]++;
         }
     }
-    for (int64_t c = 0; c < nc; ++c) dptr[c + 1] += dptr[c];
-    std::vector<int32_t> rptr(3 * nc + 1), col(std::max<size_t>(nnz + dptr[nc], 1)), fill(dptr.begin(), dptr.end() - 1);
+    for (int64_t c = 0; c < ncell; ++c) dptr[c + 1] += dptr[c];
+    std::vector<int32_t> col(std::max<size_t>(nnz + dptr[ncell], 1)), fill(dptr.begin(), dptr.end() - 1);
     std::vector<double> val(col.size());
-    LGF_HIP(hipMemcpy(rptr.data(), p.r_ptr.p, 4 * rptr.size(), hipMemcpyDeviceToHost));
     if (nnz) {
         LGF_HIP(hipMemcpy(col.data(), p.r_col.p, 4 * nnz, hipMemcpyDeviceToHost));
         LGF_HIP(hipMemcpy(val.data(), p.r_val.p, 8 * nnz, hipMemcpyDeviceToHost));
     }
-    auto put = [&](int64_t cell, int64_t row, double w) {
+    auto put = [&](int32_t cell, int64_t row, double w) {
         const size_t q = nnz + fill[cell]++;
         col[q] = (int32_t)row;
         val[q] = w;
     };
     for (int64_t row = 0; row < nrows; ++row)
         for (int32_t e = iptr[row]; e < iptr[row + 1]; ++e) {
-            put(icol[e] - (row % 3) * nc, row, ival[e]);
+            put(own[e], row, ival[e]);
             if (low[e] >= 0) put(low[e], row, -ival[e]);
         }
     std::vector<int32_t> srow, sptr(1, 0);
@@ -330,24 +347,38 @@ static int ib_plan_grad(IbPlan &p) {
             srow.push_back((int32_t)f);
             sptr.push_back(rptr[f + 1]);
         }
-    p.nfr = (int)srow.size();
-    for (int64_t c = 0; c < nc; ++c)
+    op.nfr = (int)srow.size();
+    for (int64_t c = 0; c < ncell; ++c)
         if (dptr[c + 1] > dptr[c]) {
             srow.push_back((int32_t)(3 * nc + c));
             sptr.push_back((int32_t)nnz + dptr[c + 1]);
         }
-    p.ncr = (int)srow.size() - p.nfr;
+    op.nrows = (int)srow.size();
     srow.resize(std::max<size_t>(srow.size(), 1));
     int rc;
-    if ((rc = p.i_low.reserve(4 * low.size())) || (rc = p.s_row.reserve(4 * srow.size())) ||
-        (rc = p.s_ptr.reserve(4 * sptr.size())) || (rc = p.s_col.reserve(4 * col.size())) ||
-        (rc = p.s_val.reserve(8 * val.size())))
+    if ((rc = op.row.reserve(4 * srow.size())) || (rc = op.ptr.reserve(4 * sptr.size())) ||
+        (rc = op.col.reserve(4 * col.size())) || (rc = op.val.reserve(8 * val.size())))
+        return rc;
+    LGF_HIP(hipMemcpy(op.row.p, srow.data(), 4 * srow.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(op.ptr.p, sptr.data(), 4 * sptr.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(op.col.p, col.data(), 4 * col.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(op.val.p, val.data(), 8 * val.size(), hipMemcpyHostToDevice));
+    if (low_out) *low_out = std::move(low);
+    return LGFIB_OK;
+}
+
+// The operators of the force Schur complement with the staggered gradient
+// folded in: the spread operator on the plan's own blocks, and for (G d)^(k)(n)
+// = d(n) - d(n - e_k) the cell below each entry of I.
+static int ib_plan_grad(IbPlan &p) {
+    if (p.grad) return LGFIB_OK;
+    std::vector<int32_t> map((size_t)p.nb[0] * p.nb[1] * p.nb[2]), low;
+    LGF_HIP(hipMemcpy(map.data(), p.map.p, 4 * map.size(), hipMemcpyDeviceToHost));
+    int rc;
+    if ((rc = build_spread(p, CellSet{p.lo, p.nb, map}, (int64_t)p.nblk * p.B * p.B * p.B, p.spread, &low)) ||
+        (rc = p.i_low.reserve(4 * low.size())))
         return rc;
     LGF_HIP(hipMemcpy(p.i_low.p, low.data(), 4 * low.size(), hipMemcpyHostToDevice));
-    LGF_HIP(hipMemcpy(p.s_row.p, srow.data(), 4 * srow.size(), hipMemcpyHostToDevice));
-    LGF_HIP(hipMemcpy(p.s_ptr.p, sptr.data(), 4 * sptr.size(), hipMemcpyHostToDevice));
-    LGF_HIP(hipMemcpy(p.s_col.p, col.data(), 4 * col.size(), hipMemcpyHostToDevice));
-    LGF_HIP(hipMemcpy(p.s_val.p, val.data(), 8 * val.size(), hipMemcpyHostToDevice));
     p.grad = true;
     return LGFIB_OK;
 }
@@ -378,7 +409,6 @@ struct BlockMapDev {
     }
 };
 
-__device__ inline int fdiv(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 
 // Block sums of a grid-wide reduction go to part[block]; the last block to
 // finish (a device-scope counter) adds them in block order, so the result
@@ -416,7 +446,8 @@ __device__ inline void grid_sum_to(double s, double *part, unsigned *counter, do
     }
 }
 
-// y[row] = scale * sum_e val[e] x[col[e]] over the row's entries in FP64.
+// y[row] = scale * sum_e val[e] x[col[e]] over the row's entries in FP64, less
+// sub[row] where given.
 // R: rows are faces, columns 3 i + k, scale dx^-3
 // (g^(k)(n) = dx^-3 sum_i x_i^(k) prod_j phi(x_F^(k)(n)_j - X_ij)).
 // I: rows 3 i + k, columns face indices, scale 1.
@@ -426,7 +457,8 @@ __device__ inline void grid_sum_to(double s, double *part, unsigned *counter, do
 template <typename In, typename Out, int L>
 __global__ __launch_bounds__(256) void k_csr_gather(const int *__restrict__ ptr, const int *__restrict__ col,
                                                     const double *__restrict__ val, const In *__restrict__ x,
-                                                    Out *__restrict__ y, int nrows, double scale) {
+                                                    const Out *__restrict__ sub, Out *__restrict__ y, int nrows,
+                                                    double scale) {
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const int row = (int)(t / L), lane = (int)(t % L);
     const bool live = row < nrows;
@@ -437,7 +469,7 @@ __global__ __launch_bounds__(256) void k_csr_gather(const int *__restrict__ ptr,
     }
 #pragma unroll
     for (int m = L / 2; m > 0; m >>= 1) acc += __shfl_xor(acc, m, L);
-    if (live && lane == 0) y[row] = (Out)(acc * scale);
+    if (live && lane == 0) y[row] = sub ? (Out)(acc * scale) - sub[row] : (Out)(acc * scale);
 }
 
 // Sum of n partial sums, the same value in every lane of every wavefront: each
@@ -578,37 +610,38 @@ static int launch_regularize(lgfib_ctx *ctx, const IbPlan &p, double dx, const I
     const int nrows = 3 * p.nblk * p.B * p.B * p.B;
     hipLaunchKernelGGL((k_csr_gather<In, Out, 4>), dim3(nblocks(4 * (size_t)nrows, 256)), dim3(256), 0, st,
                        p.r_ptr.as<int>(),
-                       p.r_col.as<int>(), p.r_val.as<double>(), x, faces, nrows, 1.0 / (dx * dx * dx));
+                       p.r_col.as<int>(), p.r_val.as<double>(), x, (const Out *)nullptr, faces, nrows,
+                       1.0 / (dx * dx * dx));
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
 }
 
 template <typename In, typename Out>
-static int launch_interpolate(lgfib_ctx *ctx, const IbPlan &p, const In *faces, Out *v, hipStream_t st) {
+static int launch_interpolate(lgfib_ctx *ctx, const IbPlan &p, const In *faces, Out *v, hipStream_t st,
+                              const Out *sub = nullptr) {
     if (p.NL == 0) return LGFIB_OK;
     ProfScope ps(ctx, "k_interpolate", st);
     const int nrows = 3 * p.NL;
     hipLaunchKernelGGL((k_csr_gather<In, Out, 16>), dim3(nblocks(16 * (size_t)nrows, 256)), dim3(256), 0, st,
                        p.i_ptr.as<int>(),
-                       p.i_col.as<int>(), p.i_val.as<double>(), faces, v, nrows, 1.0);
+                       p.i_col.as<int>(), p.i_val.as<double>(), faces, sub, v, nrows, 1.0);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
 }
 
-// faces = R x, c = G^T R x (plan with ib_plan_grad; faces and c hold zeros where
-// no marker reaches); dir: the CG's direction
+// faces = R x, c = G^T R x (faces and c hold zeros where no marker reaches; nf
+// the number of faces); dir: the CG's direction
 template <typename In, typename Out>
-static int launch_spread(lgfib_ctx *ctx, const IbPlan &p, const In *x, const CgDir *dir, Out *faces, Out *c,
+static int launch_spread(lgfib_ctx *ctx, const SpreadOp &op, const In *x, const CgDir *dir, Out *faces, Out *c, int nf,
                          hipStream_t st) {
     ProfScope ps(ctx, "k_spread", st);
-    const int nf = 3 * p.nblk * p.B * p.B * p.B, nrows = p.nfr + p.ncr;
-    const dim3 grid(std::max(1u, nblocks(8 * (size_t)nrows, 256)));
+    const dim3 grid(std::max(1u, nblocks(8 * (size_t)op.nrows, 256)));
     if (dir)
-        hipLaunchKernelGGL((k_spread<true, In, Out>), grid, dim3(256), 0, st, p.s_ptr.as<int>(), p.s_col.as<int>(),
-                           p.s_val.as<double>(), p.s_row.as<int>(), x, *dir, faces, c, nrows, nf);
+        hipLaunchKernelGGL((k_spread<true, In, Out>), grid, dim3(256), 0, st, op.ptr.as<int>(), op.col.as<int>(),
+                           op.val.as<double>(), op.row.as<int>(), x, *dir, faces, c, op.nrows, nf);
     else
-        hipLaunchKernelGGL((k_spread<false, In, Out>), grid, dim3(256), 0, st, p.s_ptr.as<int>(), p.s_col.as<int>(),
-                           p.s_val.as<double>(), p.s_row.as<int>(), x, CgDir{}, faces, c, nrows, nf);
+        hipLaunchKernelGGL((k_spread<false, In, Out>), grid, dim3(256), 0, st, op.ptr.as<int>(), op.col.as<int>(),
+                           op.val.as<double>(), op.row.as<int>(), x, CgDir{}, faces, c, op.nrows, nf);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
 }
@@ -781,7 +814,7 @@ static int schur_apply_t(ib_system *s, const VIn *x, VOut *y, hipStream_t st, co
     const int prec = pi ? LGF_F64 : LGF_F32;
     Real *g = s->g[pi].as<Real>(), *af = s->af[pi].as<Real>(), *c = s->c[pi].as<Real>(), *d = s->d[pi].as<Real>();
     int rc;
-    if ((rc = launch_spread<VIn, Real>(ctx, *s->plan, x, dir, g, c, st))) return rc;
+    if ((rc = launch_spread<VIn, Real>(ctx, s->plan->spread, x, dir, g, c, 3 * s->nblk * s->B * s->B * s->B, st))) return rc;
     if ((rc = lgf_if_apply(ctx, s->a, s->B, s->blocks.data(), s->nblk, s->blocks.data(), s->nblk, 3, prec, g, af,
                            (lgfib_stream_t)st)))
         return rc;
@@ -958,6 +991,23 @@ __global__ __launch_bounds__(kStepThreads) void k_dot_small(const double *__rest
     if (threadIdx.x == 0) *out = t;
 }
 
+// out = (b.b, |b - y|^2) in one workgroup; out is pinned host memory
+__global__ __launch_bounds__(kStepThreads) void k_resid_norms(const double *__restrict__ b,
+                                                              const double *__restrict__ y, int n, double *out) {
+    __shared__ double sh[kStepThreads];
+    double s = 0.0, q = 0.0;
+    for (int i = threadIdx.x; i < n; i += kStepThreads) {
+        const double d = b[i] - y[i];
+        s += b[i] * b[i];
+        q += d * d;
+    }
+    const double bb = wg_sum(s, sh), rr = wg_sum(q, sh);
+    if (threadIdx.x == 0) {
+        out[0] = bb;
+        out[1] = rr;
+    }
+}
+
 // r = b - y
 __global__ void k_sub(double *__restrict__ r, const double *__restrict__ b, const double *__restrict__ y, size_t n) {
     const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1098,7 +1148,13 @@ static int direct_solve(ib_system *s, const double *b, double *f, ib_solve_stats
     LGF_HIP(hipEventRecord(e0, st));
     if ((rc = chol_solve_f64(s->ctx, n, s->wfac.as<double>(), n, b, f, st))) return rc;
     LGF_HIP(hipEventRecord(e1, st));
-    LGF_HIP(hipEventSynchronize(e1));
+    if (S) {
+        double *ap = s->ap.as<double>();
+        if ((rc = matvec(s, LGF_F64, f, ap, st))) return rc;
+        hipLaunchKernelGGL(k_resid_norms, dim3(1), dim3(kStepThreads), 0, st, b, ap, n, s->host_scal_dev);
+        LGF_HIP(hipGetLastError());
+    }
+    LGF_HIP(hipStreamSynchronize(st));
     float ms = 0.f;
     LGF_HIP(hipEventElapsedTime(&ms, e0, e1));
     (void)hipEventDestroy(e0);
@@ -1106,13 +1162,7 @@ static int direct_solve(ib_system *s, const double *b, double *f, ib_solve_stats
     if (S) {
         *S = ib_solve_stats_t{};
         S->ms = ms;
-        double *ap = s->ap.as<double>(), *r = s->r.as<double>();
-        double bb, rr;
-        if ((rc = matvec(s, LGF_F64, f, ap, st))) return rc;
-        hipLaunchKernelGGL(k_sub, dim3(nblocks(n, 256)), dim3(256), 0, st, r, b, ap, (size_t)n);
-        LGF_HIP(hipGetLastError());
-        if ((rc = dot(s, b, b, s->scal.as<double>() + 3, st)) || (rc = read_scal(s, 3, &bb, st))) return rc;
-        if ((rc = dot(s, r, r, s->scal.as<double>() + 4, st)) || (rc = read_scal(s, 4, &rr, st))) return rc;
+        const double bb = s->host_scal[0], rr = s->host_scal[1];
         S->rel_residual = bb > 0.0 ? sqrt(rr / bb) : 0.0;
     }
     return LGFIB_OK;
@@ -1283,67 +1333,104 @@ struct ib_flow {
     int clo[3] = {0, 0, 0}, cnb[3] = {0, 0, 0};
     DevBuf cmap, cblk;              // block map of the cell blocks
     lgf_table_t tbl = -1;           // G_L over the cell span
-    DevBuf c, dstar, dd, w, h, rhs;
+    DevBuf c, dstar, w, h, rhs;
+    // R f on the faces and G^T R f on the cells, written by the spread operator
+    // alone (zeros where no marker reaches)
+    SpreadOp spread;
+    DevBuf rf, cf;
 };
 
 namespace lgfib {
-__global__ void k_flow_rhs(double *__restrict__ b, const double *__restrict__ v, const double *__restrict__ ub,
-                           size_t n) {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) b[t] = v[t] - ub[t];
-}
-__global__ void k_add(double *__restrict__ y, const double *__restrict__ x, double a, size_t n) {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) y[t] += a * x[t];
-}
-
-// face (block slot in F, local cell) of cell n's k-face, or -1 if absent
-__device__ inline long face_index(const BlockMapDev &F, int nF, int k, int nx, int ny, int nz) {
-    const int B = F.B;
-    const int bx = fdiv(nx, B), by = fdiv(ny, B), bz = fdiv(nz, B);
-    const int sl = F.slot(bx, by, bz);
-    if (sl < 0) return -1;
-    return ((long)k * nF + sl) * B * B * B + ((nz - bz * B) * B + (ny - by * B)) * B + (nx - bx * B);
+// The drivers' stencils.  FP64 streams of 3 B^3 faces a block, bound by HBM once
+// the index arithmetic is out of the way: one block per B^3 threads, shifts for
+// the power-of-two block edge, and a block lookup only where the neighbour lies
+// in another block.  With 64-bit divisions and a lookup for every face the two
+// took 24.6 and 14.9 us on 1728 blocks of 8^3 at 99% and 81% VALU activity; now
+// 10.7 and 14.1, and 24.6 for the second gradient with its five streams.
+struct CellAt {
+    int b, cell, l[3];
+};
+__device__ __forceinline__ CellAt cell_at(unsigned t, int lb) {
+    const int m = (1 << lb) - 1;
+    CellAt a;
+    a.b = (int)(t >> (3 * lb));
+    a.cell = (int)(t & ((1u << (3 * lb)) - 1));
+    a.l[0] = a.cell & m;
+    a.l[1] = (a.cell >> lb) & m;
+    a.l[2] = a.cell >> (2 * lb);
+    return a;
 }
 
 // c(n) = sc sum_k u^(k)(n) - u^(k)(n + e_k) on the cell blocks A; faces u on
 // the flow blocks F (zero elsewhere)
-__global__ void k_div_cross(BlockMapDev F, BlockMapDev A, const double *__restrict__ u, double *__restrict__ c,
-                            int nF, int nA, double sc) {
-    const int B = A.B, B3 = B * B * B;
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)nA * B3) return;
-    const int b = (int)(t / B3), cell = (int)(t % B3);
-    const int nx = A.blocks[3 * b] * B + cell % B, ny = A.blocks[3 * b + 1] * B + (cell / B) % B,
-              nz = A.blocks[3 * b + 2] * B + cell / (B * B);
+__global__ __launch_bounds__(256) void k_div_cross(BlockMapDev F, BlockMapDev A, int lb, const double *__restrict__ u,
+                                                   double *__restrict__ c, int nF, unsigned ncell, double sc) {
+    const unsigned t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= ncell) return;
+    const CellAt a = cell_at(t, lb);
+    const int top = (1 << lb) - 1;
+    const int bx = A.blocks[3 * a.b], by = A.blocks[3 * a.b + 1], bz = A.blocks[3 * a.b + 2];
+    const int own = F.slot(bx, by, bz);
     double s = 0.0;
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const long i0 = face_index(F, nF, k, nx, ny, nz);
-        const long i1 = face_index(F, nF, k, nx + (k == 0), ny + (k == 1), nz + (k == 2));
-        if (i0 >= 0) s += u[i0];
-        if (i1 >= 0) s -= u[i1];
+        const double *uk = u + ((size_t)k * nF << (3 * lb));
+        const bool up = a.l[k] == top;
+        const int nb = up ? F.slot(bx + (k == 0), by + (k == 1), bz + (k == 2)) : own;
+        const int ncl = a.cell + ((up ? -top : 1) << (k * lb));
+        if (own >= 0) s += uk[((size_t)own << (3 * lb)) + a.cell];
+        if (nb >= 0) s -= uk[((size_t)nb << (3 * lb)) + ncl];
     }
     c[t] = sc * s;
 }
 
-// e^(k)(n) += sc (d(n) - d(n - e_k)) for faces on F; d on the cell blocks A
-__global__ void k_grad_cross(BlockMapDev F, BlockMapDev A, const double *__restrict__ d, double *__restrict__ e,
-                             int nF, double sc) {
-    const int B = F.B, B3 = B * B * B;
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)nF * B3) return;
-    const int b = (int)(t / B3), cell = (int)(t % B3);
-    const int lx = cell % B, ly = (cell / B) % B, lz = cell / (B * B);
-    const int bx = F.blocks[3 * b], by = F.blocks[3 * b + 1], bz = F.blocks[3 * b + 2];
-    const int sa = A.slot(bx, by, bz);   // every flow block is a cell block
-    const double dc = d[(size_t)sa * B3 + cell];
+// On the faces of F, with d on the cell blocks A (which hold F and its lower
+// neighbours): w = u - G d, and in its second form w = u - q, q = G d + rf, of
+// which qlam (nullable) receives q - g (g nullable).
+template <bool SECOND>
+__global__ __launch_bounds__(256) void k_grad_cross(BlockMapDev F, BlockMapDev A, int lb, const double *__restrict__ u,
+                                                    const double *__restrict__ d, const double *__restrict__ rf,
+                                                    const double *__restrict__ g, double *__restrict__ w,
+                                                    double *__restrict__ qlam, int nF, unsigned nface) {
+    const unsigned t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= nface) return;
+    const CellAt a = cell_at(t, lb);
+    const int top = (1 << lb) - 1;
+    const int bx = F.blocks[3 * a.b], by = F.blocks[3 * a.b + 1], bz = F.blocks[3 * a.b + 2];
+    const int own = A.slot(bx, by, bz);
+    const double dc = d[((size_t)own << (3 * lb)) + a.cell];
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const int nx = bx * B + lx - (k == 0), ny = by * B + ly - (k == 1), nz = bz * B + lz - (k == 2);
-        const int cbx = fdiv(nx, B), cby = fdiv(ny, B), cbz = fdiv(nz, B);
-        const int sb = A.slot(cbx, cby, cbz);
-        const double dm = sb >= 0 ? d[(size_t)sb * B3 + ((nz - cbz * B) * B + (ny - cby * B)) * B + (nx - cbx * B)] : 0.0;
-        e[((size_t)k * nF + b) * B3 + cell] += sc * (dc - dm);
+        const bool low = a.l[k] == 0;
+        const int nb = low ? A.slot(bx - (k == 0), by - (k == 1), bz - (k == 2)) : own;
+        const int ncl = a.cell + ((low ? top : -1) * (1 << (k * lb)));
+        const double dm = nb >= 0 ? d[((size_t)nb << (3 * lb)) + ncl] : 0.0;
+        const size_t i = ((size_t)k * nF << (3 * lb)) + t;
+        if constexpr (SECOND) {
+            const double q = (dc - dm) + rf[i];
+            w[i] = u[i] - q;
+            if (qlam) qlam[i] = g ? q - g[i] : q;
+        } else {
+            w[i] = u[i] - (dc - dm);
+        }
     }
+}
+
+// r = h + sum_j c[j] q[j] + g (terms in this order; null q and g are left out)
+struct HerkTerms {
+    const double *q[7];
+    double c[7];
+};
+__global__ __launch_bounds__(256) void k_combine(double *__restrict__ r, const double *__restrict__ h, HerkTerms m,
+                                                 const double *__restrict__ g, size_t n) {
+    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= n) return;
+    double v = h[t];
+#pragma unroll
+    for (int j = 0; j < 7; ++j)
+        if (m.q[j]) v += m.c[j] * m.q[j][t];
+    if (g) v += g[t];
+    r[t] = v;
 }
 }  // namespace lgfib
 
@@ -1416,16 +1503,22 @@ extern "C" int ib_flow_create(lgfib_ctx *ctx, ib_system *sys, const int32_t *flo
         if ((rc = f->cmap.reserve(map.size() * 4)) || (rc = f->cblk.reserve(f->cblocks.size() * 4))) return rc;
         LGF_HIP(hipMemcpy(f->cmap.p, map.data(), map.size() * 4, hipMemcpyHostToDevice));
         LGF_HIP(hipMemcpy(f->cblk.p, f->cblocks.data(), f->cblocks.size() * 4, hipMemcpyHostToDevice));
+        if ((rc = build_spread(*f->plan, CellSet{f->clo, f->cnb, map}, (int64_t)f->ncell * f->B * f->B * f->B, f->spread,
+                               nullptr)))
+            return rc;
     }
     int ext[3];
     for (int q = 0; q < 3; ++q) ext[q] = f->cnb[q] * sys->B - 1;
     if ((rc = lgf_table_build(ctx, LGF_KIND_L, 0.0, ext, nullptr, &f->tbl))) return rc;
     const size_t B3 = (size_t)sys->B * sys->B * sys->B;
     const size_t nfc = (size_t)nflow * B3, ncc = (size_t)f->ncell * B3;
-    if ((rc = f->c.reserve(ncc * 8)) || (rc = f->dstar.reserve(ncc * 8)) || (rc = f->dd.reserve(ncc * 8)) ||
-        (rc = f->w.reserve(3 * nfc * 8)) || (rc = f->h.reserve(3 * nfc * 8)) ||
+    if ((rc = f->c.reserve(ncc * 8)) || (rc = f->dstar.reserve(ncc * 8)) || (rc = f->cf.reserve(ncc * 8)) ||
+        (rc = f->w.reserve(3 * nfc * 8)) || (rc = f->h.reserve(3 * nfc * 8)) || (rc = f->rf.reserve(3 * nfc * 8)) ||
         (rc = f->rhs.reserve(3 * (size_t)sys->NL * 8)))
         return rc;
+    LGF_HIP(hipMemset(f->cf.p, 0, ncc * 8));
+    LGF_HIP(hipMemset(f->rf.p, 0, 3 * nfc * 8));
+    LGF_HIP(hipStreamSynchronize(nullptr));
     *out = f.release();
     return LGFIB_OK;
 }
@@ -1438,10 +1531,6 @@ extern "C" void ib_flow_destroy(ib_flow *flow) {
 }
 
 namespace lgfib {
-__global__ void k_sum2(double *__restrict__ y, const double *__restrict__ a, const double *__restrict__ b, size_t n) {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) y[t] = a[t] + b[t];
-}
 __global__ void k_scale(double *__restrict__ y, const double *__restrict__ x, double a, size_t n) {
     const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n) y[t] = a * x[t];
@@ -1449,17 +1538,17 @@ __global__ void k_scale(double *__restrict__ y, const double *__restrict__ x, do
 }  // namespace lgfib
 
 // One stage system H^{-1} u' + Q lam = u, Q^T u' = (0, u_B) by the nested
-// projection; u is the right-hand side on entry and u' on return; qlam
-// (nullable, faces) receives Q lam = G d + R f.
-static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, double *u, const double *ub, double *f, const double *x0,
-                      double rtol, int maxit, int prec, ib_solve_stats_t *stats, double *b_out, double *qlam,
-                      hipStream_t st) {
+// projection; u is the right-hand side, u_out (may be u) receives u'; qlam
+// (nullable, faces) receives Q lam - g = G d + R f - g (g nullable).
+static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, const double *u, double *u_out, const double *ub, double *f,
+                      const double *x0, double rtol, int maxit, int prec, ib_solve_stats_t *stats, double *b_out,
+                      const double *g, double *qlam, hipStream_t st) {
     ib_system *sys = fl->sys;
     const IbPlan &P = *fl->plan;
-    const int B = fl->B;
+    const int B = fl->B, lb = B == 4 ? 2 : B == 8 ? 3 : 4;   // force systems have B in {4, 8, 16}
     const size_t B3 = (size_t)B * B * B;
     const size_t nfc = (size_t)fl->nflow * B3, nf = 3 * nfc, ncc = (size_t)fl->ncell * B3, nl = 3 * (size_t)sys->NL;
-    double *c = fl->c.as<double>(), *dstar = fl->dstar.as<double>(), *dd = fl->dd.as<double>();
+    double *c = fl->c.as<double>(), *d = fl->dstar.as<double>(), *rf = fl->rf.as<double>();
     double *w = fl->w.as<double>(), *h = fl->h.as<double>(), *rhs = fl->rhs.as<double>();
     const int32_t *bl = fl->blocks.data(), *cb = fl->cblocks.data();
     const int nb = fl->nflow, nc = fl->ncell;
@@ -1476,47 +1565,29 @@ static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, double *u, const double *ub, 
     Am.blocks = fl->cblk.as<int>();
     int rc;
     // (ip) d* = L^{-1}(-G^T u)
-    hipLaunchKernelGGL(k_div_cross, dim3(nblocks(ncc, 256)), dim3(256), 0, st, Fm, Am, (const double *)u, c, nb, nc,
+    hipLaunchKernelGGL(k_div_cross, dim3(nblocks(ncc, 256)), dim3(256), 0, st, Fm, Am, lb, u, c, nb, (unsigned)ncc,
                        -1.0);
     LGF_HIP(hipGetLastError());
-    if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, c, dstar, 0, (lgfib_stream_t)st))) return rc;
+    if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, c, d, 0, (lgfib_stream_t)st))) return rc;
     // (f) b = I E(a)[u - G d*] - u_B ;  C f = b
-    LGF_HIP(hipMemcpyAsync(w, u, nf * 8, hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(k_grad_cross, dim3(nblocks(nfc, 256)), dim3(256), 0, st, Fm, Am, (const double *)dstar, w, nb,
-                       -1.0);
+    hipLaunchKernelGGL(k_grad_cross<false>, dim3(nblocks(nfc, 256)), dim3(256), 0, st, Fm, Am, lb, u, (const double *)d,
+                       (const double *)nullptr, (const double *)nullptr, w, (double *)nullptr, nb, (unsigned)nfc);
     LGF_HIP(hipGetLastError());
     if ((rc = lgf_if_apply(ctx, sys->a, B, bl, nb, bl, nb, 3, LGF_F64, w, h, (lgfib_stream_t)st))) return rc;
-    if ((rc = launch_interpolate<double, double>(ctx, P, h, rhs, st))) return rc;
-    hipLaunchKernelGGL(k_flow_rhs, dim3(nblocks(nl, 256)), dim3(256), 0, st, rhs, rhs, ub, nl);
-    LGF_HIP(hipGetLastError());
+    if ((rc = launch_interpolate<double, double>(ctx, P, h, rhs, st, ub))) return rc;
     if (b_out) LGF_HIP(hipMemcpyAsync(b_out, rhs, nl * 8, hipMemcpyDeviceToDevice, st));
     rc = ib_force_solve(ctx, sys, prec, rhs, f, x0, rtol, maxit, stats, (lgfib_stream_t)st);
     if (rc && rc != LGFIB_ENOCONV) return rc;
     const int solve_rc = rc;
     // (pc) d = d* + L^{-1} G^T R f
-    if ((rc = launch_regularize<double, double>(ctx, P, 1.0, f, w, st))) return rc;   // w = R f
-    hipLaunchKernelGGL(k_div_cross, dim3(nblocks(ncc, 256)), dim3(256), 0, st, Fm, Am, (const double *)w, c, nb, nc,
-                       1.0);
+    if ((rc = launch_spread<double, double>(ctx, fl->spread, f, nullptr, rf, fl->cf.as<double>(), (int)nf, st))) return rc;
+    if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, fl->cf.p, d, 1, (lgfib_stream_t)st)))
+        return rc;
+    // (vc) u' = E(a)[u - G d - R f]
+    hipLaunchKernelGGL(k_grad_cross<true>, dim3(nblocks(nfc, 256)), dim3(256), 0, st, Fm, Am, lb, u, (const double *)d,
+                       (const double *)rf, g, w, qlam, nb, (unsigned)nfc);
     LGF_HIP(hipGetLastError());
-    if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, c, dd, 0, (lgfib_stream_t)st))) return rc;
-    hipLaunchKernelGGL(k_add, dim3(nblocks(ncc, 256)), dim3(256), 0, st, dstar, dd, 1.0, ncc);   // d* := d
-    LGF_HIP(hipGetLastError());
-    // (vc) u = E(a)[u - G d - R f]
-    hipLaunchKernelGGL(k_add, dim3(nblocks(nf, 256)), dim3(256), 0, st, w, u, -1.0, nf);   // w = R f - u
-    LGF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_grad_cross, dim3(nblocks(nfc, 256)), dim3(256), 0, st, Fm, Am, (const double *)dstar, w, nb,
-                       1.0);                                                              // w += G d
-    LGF_HIP(hipGetLastError());
-    if (qlam) {   // Q lam = G d + R f = w + u
-        hipLaunchKernelGGL(k_sum2, dim3(nblocks(nf, 256)), dim3(256), 0, st, qlam, (const double *)w, (const double *)u,
-                           nf);
-        LGF_HIP(hipGetLastError());
-    }
-    if ((rc = lgf_if_apply(ctx, sys->a, B, bl, nb, bl, nb, 3, LGF_F64, w, h, (lgfib_stream_t)st))) return rc;
-    hipLaunchKernelGGL(k_add, dim3(nblocks(nf, 256)), dim3(256), 0, st, u, u, -1.0, nf);     // u = 0
-    hipLaunchKernelGGL(k_add, dim3(nblocks(nf, 256)), dim3(256), 0, st, u, h, -1.0, nf);     // u = -E(w)
-    LGF_HIP(hipGetLastError());
-    LGF_HIP(hipStreamSynchronize(st));
+    if ((rc = lgf_if_apply(ctx, sys->a, B, bl, nb, bl, nb, 3, LGF_F64, w, u_out, (lgfib_stream_t)st))) return rc;
     return solve_rc;
 }
 
@@ -1526,7 +1597,11 @@ extern "C" int ib_flow_step(lgfib_ctx *ctx, ib_flow *fl, double *u, const double
     if (!ctx || !fl || fl->ctx != ctx) return fail(LGFIB_EINVAL, "ib_flow_step: bad context or flow");
     if (!u || !ub || !f) return fail(LGFIB_EINVAL, "ib_flow_step: null vector");
     LGF_HIP(hipSetDevice(ctx->device));
-    return flow_stage(ctx, fl, u, ub, f, x0, rtol, maxit, prec, stats, b_out, nullptr, (hipStream_t)stream);
+    const int rc = flow_stage(ctx, fl, u, u, ub, f, x0, rtol, maxit, prec, stats, b_out, nullptr, nullptr,
+                              (hipStream_t)stream);
+    if (rc && rc != LGFIB_ENOCONV) return rc;
+    LGF_HIP(hipStreamSynchronize((hipStream_t)stream));
+    return rc;
 }
 
 // Columns j0 .. j0+K-1 of C in one pass (FP64): the operator of
@@ -1547,7 +1622,8 @@ static int schur_dense_cols(ib_system *s, int j0, int K, double *C, long ld, hip
     for (int k = 0; k < K; ++k) {
         hipLaunchKernelGGL(k_unit, dim3(nblocks(n, 256)), dim3(256), 0, st, e + (size_t)k * n, n, j0 + k);
         LGF_HIP(hipGetLastError());
-        if ((rc = launch_spread<double, double>(ctx, P, e + (size_t)k * n, nullptr, g + k * nf, c + k * nc, st)))
+        if ((rc = launch_spread<double, double>(ctx, P.spread, e + (size_t)k * n, nullptr, g + k * nf, c + k * nc,
+                                                (int)nf, st)))
             return rc;
     }
     for (int c0 = 0; c0 < 3 * K; c0 += 8) {
@@ -1625,7 +1701,7 @@ struct ib_herk {
     double conv_dt = 0.0;                  // dt / dx of the nonlinear term (0: Stokes)
     double U[3] = {0.0, 0.0, 0.0};         // frame velocity in u_a = u + U
     DevBuf fields;   // (s + 4) face fields: h, tmp, r, Q lam - g of each stage, g
-    DevBuf forces;   // (s + 1) marker vectors: stage force, previous step's stage forces
+    DevBuf forces;   // s marker vectors: the stages' forces of the last step
 };
 
 extern "C" void ib_herk_destroy(ib_herk *hk) {
@@ -1727,7 +1803,7 @@ extern "C" int ib_herk_create(lgfib_ctx *ctx, int kernel, const double *X, int N
         hk->stage_k.push_back(k);
     }
     const size_t nf = 3 * (size_t)nflow * B * B * B, nl = 3 * (size_t)NL;
-    if ((rc = hk->fields.reserve((size_t)(s + 4) * nf * 8)) || (rc = hk->forces.reserve((size_t)(s + 1) * nl * 8)))
+    if ((rc = hk->fields.reserve((size_t)(s + 4) * nf * 8)) || (rc = hk->forces.reserve((size_t)s * nl * 8)))
         return rc;
     *out = hk.release();
     return LGFIB_OK;
@@ -1750,15 +1826,15 @@ extern "C" int ib_herk_step(lgfib_ctx *ctx, ib_herk *hk, double *u, const double
     double *g = base + (3 + s) * nf;
     const bool conv = hk->conv_dt > 0.0;
     const double *ustage = u;   // u^{i-1}: the step's input, then each stage's solution (left in r)
-    double *fst = hk->forces.as<double>();
+    const double *hcur = u;     // h^i: the step's input until it has been propagated into h
     if (stats) *stats = ib_solve_stats_t{};
     int rc, solve_rc = LGFIB_OK;
-    LGF_HIP(hipMemcpyAsync(h, u, nf * 8, hipMemcpyDeviceToDevice, st));
     for (int i = 0; i < s; ++i) {
         const double ap = i > 0 ? hk->stage_a[i - 1] : 0.0;
         if (ap > 0.0) {   // h <- H^{i-1} h, Q lam^j <- H^{i-1} Q lam^j
-            if ((rc = lgf_if_apply(ctx, ap, B, bl, nb, bl, nb, 3, LGF_F64, h, tmp, stream))) return rc;
+            if ((rc = lgf_if_apply(ctx, ap, B, bl, nb, bl, nb, 3, LGF_F64, hcur, tmp, stream))) return rc;
             std::swap(h, tmp);
+            hcur = h;
             for (int j = 0; j < i; ++j) {
                 if ((rc = lgf_if_apply(ctx, ap, B, bl, nb, bl, nb, 3, LGF_F64, q[j], tmp, stream))) return rc;
                 std::swap(q[j], tmp);
@@ -1768,30 +1844,24 @@ extern "C" int ib_herk_step(lgfib_ctx *ctx, ib_herk *hk, double *u, const double
         if (conv && (rc = lamb_apply(ctx, B, bl, nb, hk->U, -hk->at[i * s + i] * hk->conv_dt, LGF_F64, ustage, g, st)))
             return rc;
         // r = h - sum_j (at_ij / at_jj) (Q lam^j - g^j) + g^i
-        LGF_HIP(hipMemcpyAsync(r, h, nf * 8, hipMemcpyDeviceToDevice, st));
+        HerkTerms terms{};
         for (int j = 0; j < i; ++j) {
-            const double cij = -hk->at[i * s + j] / hk->at[j * s + j];
-            if (cij == 0.0) continue;
-            hipLaunchKernelGGL(k_add, dim3(nblocks(nf, 256)), dim3(256), 0, st, r, (const double *)q[j], cij, nf);
-            LGF_HIP(hipGetLastError());
+            terms.c[j] = -hk->at[i * s + j] / hk->at[j * s + j];
+            terms.q[j] = terms.c[j] == 0.0 ? nullptr : q[j];
         }
-        if (conv) {
-            hipLaunchKernelGGL(k_add, dim3(nblocks(nf, 256)), dim3(256), 0, st, r, (const double *)g, 1.0, nf);
-            LGF_HIP(hipGetLastError());
-        }
-        double *fprev = fst + (1 + i) * nl;
+        hipLaunchKernelGGL(k_combine, dim3(nblocks(nf, 256)), dim3(256), 0, st, r, hcur, terms,
+                           (const double *)(conv ? g : nullptr), nf);
+        LGF_HIP(hipGetLastError());
+        // the stage's force stays where the next step's solve starts from; its
+        // propagated field is Q lam^i - g^i; the last stage's u is the step's
+        double *fi = hk->forces.as<double>() + i * nl;
         ib_solve_stats_t si{};
-        rc = flow_stage(ctx, hk->flows[hk->stage_k[i]], r, ub + i * nl, fst,
-                        (!hk->direct && hk->have_prev) ? fprev : nullptr, rtol, maxit,
-                        hk->direct ? IB_SOLVE_DIRECT : prec, &si, nullptr, q[i], st);
+        rc = flow_stage(ctx, hk->flows[hk->stage_k[i]], r, i == s - 1 ? u : r, ub + i * nl, fi,
+                        (!hk->direct && hk->have_prev) ? fi : nullptr, rtol, maxit,
+                        hk->direct ? IB_SOLVE_DIRECT : prec, &si, nullptr, conv ? g : nullptr, q[i], st);
         if (rc && rc != LGFIB_ENOCONV) return rc;
         if (rc) solve_rc = rc;
-        if (conv) {   // the propagated field of this stage is Q lam^i - g^i
-            hipLaunchKernelGGL(k_add, dim3(nblocks(nf, 256)), dim3(256), 0, st, q[i], (const double *)g, -1.0, nf);
-            LGF_HIP(hipGetLastError());
-        }
         ustage = r;
-        LGF_HIP(hipMemcpyAsync(fprev, fst, nl * 8, hipMemcpyDeviceToDevice, st));
         if (stats) {
             stats->iterations += si.iterations;
             stats->restarts += si.restarts;
@@ -1801,9 +1871,8 @@ extern "C" int ib_herk_step(lgfib_ctx *ctx, ib_herk *hk, double *u, const double
             stats->rel_residual = std::max(stats->rel_residual, si.rel_residual);
         }
     }
-    LGF_HIP(hipMemcpyAsync(u, r, nf * 8, hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(k_scale, dim3(nblocks(nl, 256)), dim3(256), 0, st, f, (const double *)fst,
-                       1.0 / hk->at[(s - 1) * s + s - 1], nl);
+    hipLaunchKernelGGL(k_scale, dim3(nblocks(nl, 256)), dim3(256), 0, st, f,
+                       (const double *)(hk->forces.as<double>() + (s - 1) * nl), 1.0 / hk->at[(s - 1) * s + s - 1], nl);
     LGF_HIP(hipGetLastError());
     LGF_HIP(hipStreamSynchronize(st));
     hk->have_prev = true;

@@ -127,3 +127,36 @@ def test_herk_steps_match_oracle(ctx, case, scheme, direct):
         if direct:
             assert st["iterations"] == 0
     hk.close()
+
+
+@pytest.mark.parametrize("B,NL", [(4, 6), (16, 2)])
+def test_driver_stencils_on_ragged_flow_sets(ctx, B, NL):
+    """The divergence and gradient stencils, the spread on the flow set and the
+    stage's combinations where neighbours are missing: a flow set with holes in
+    shuffled order, blocks of 4^3 and 16^3, one Scheme-A step of a random field
+    against the oracle (1e-9, the bar of the scheme tests above)."""
+    g = np.random.Generator(np.random.PCG64(70 + B))
+    X = g.uniform(10.0, 13.0, size=(NL, 3)) if B == 4 else g.uniform(6.0, 9.0, size=(NL, 3))
+    body = oracle.body_blocks(X, ROMA3, B)
+    lo, hi = body.min(axis=0) - (1 if B == 4 else 0), body.max(axis=0) + 1
+    cand = [(x, y, z) for z in range(lo[2], hi[2] + 1) for y in range(lo[1], hi[1] + 1) for x in range(lo[0], hi[0] + 1)]
+    keep = set(map(tuple, body.tolist()))
+    flow = [b for b in cand if b in keep or g.uniform() < 0.6]
+    flow = np.array([flow[i] for i in g.permutation(len(flow))], dtype=np.int32)
+    at, ct = lg.ib_herk_tableau("A")
+    a = 0.05
+    org, mask = oracle.block_mask(flow, B)
+    gl = oracle.lgf_table(*np.array([n + 1 for n in mask.shape[::-1]]))
+    C = _stage_C(X, body, B, a, ct)
+    u0 = g.standard_normal((3,) + mask.shape) * mask[None]
+    ub = g.standard_normal((len(ct), NL, 3))
+    uref, fref = oracle.stokes_ifherk_step(u0, X, ub, ROMA3, a, at, ct, gl, C, mask, org)
+    hk = lg.ib_herk_create(ctx, lg.IB_ROMA3, X, B, body, flow, a, at, ct, direct=True)
+    u = torch.from_numpy(_box_to_blocks(u0, flow, B, org)).cuda()
+    f = torch.zeros((NL, 3), dtype=torch.float64, device="cuda")
+    for _ in range(2):   # the second step starts from the first one's buffers
+        ud = u.clone()
+        lg.ib_herk_step(ctx, hk, ud, torch.from_numpy(ub).cuda(), f)
+        assert _rel(ud.cpu().numpy(), _box_to_blocks(uref, flow, B, org)) < 1e-9
+        assert _rel(f.cpu().numpy(), fref) < 1e-9
+    hk.close()

@@ -160,138 +160,148 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
 }
 
 // Leaf: Cholesky factor L and its inverse W = L^{-1} of an n x n block
-// (n <= kLeaf) by one workgroup of 256 threads (rows n..kLeaf-1 padded with
-// the identity, whose factor is the identity).  Thread t works on row
-// i = t / 4 and the columns j = t mod 4 (mod 4).
-// Factor, right-looking, four columns per outer step: in registers,
-// r[m] = a[i][4 (c + m) + t mod 4] for the current column group c (the
-// array shifts down by one after each group, so that its indices stay
-// constants).  Step k reads column k (final, not yet scaled) from LDS, where
-// it is published with zeros in rows <= k and its pivot d_k = a[k][k] in a
-// slot of its own; every thread then subtracts a[i][k] a[j][k] / d_k from all
-// of its entries, which leaves rows <= k and columns <= k as they are, and
-// scales its column-k entry, L[k][k] = sqrt(d_k), L[i][k] = a[i][k] / L[k][k].
-// The holders of column k + 1 update it first and publish it into the other
-// of two buffers, so a step needs one barrier.  Entries above the diagonal
-// are garbage (finite) and never stored.
-// Inverse, from L W = I row by row: row k of W (the residual, not yet
-// divided by L[k][k]) is published; its holders divide their copy by L[k][k]
-// and the rows q > k subtract L[q][k] / L[k][k] times it.  The entries of W
-// above the diagonal stay exactly zero, so every step can run over all of
-// them.  A pivot that is not positive sets *bad; the factor then holds NaN.
-// On return, ls holds W (row stride kLeaf + 1; the padding rows and columns
-// n..kLeaf-1 hold the identity).
+// (n <= kLeaf) by one workgroup of four wavefronts (rows n..kLeaf-1 padded with
+// the identity, whose factor is the identity).  The leaves form a serial chain
+// of n steps, so a leaf is bound by the latency of a step, and the fewer of
+// them cross a workgroup barrier the better: the block is taken in panels of
+// 16 columns.  Of panel p,
+//   one wavefront factors and inverts the 16 x 16 diagonal block in registers
+//     (lane i holds row i; a column is spread by lane reads, no barrier),
+//   L_ip = A_ip W_pp^T for the blocks below it, one wavefront each, and
+//   A_ij -= L_ip L_jp^T for the blocks to its right, on the matrix cores;
+// then, for i - j = 1, 2, 3, W_ij = -W_ii sum_k L_ik W_kj, whose inner sum comes
+// out of the matrix cores in the operand layout of the outer product.  15
+// barriers a leaf.  The form with one column of all 64 rows per barrier took
+// 43 us (128 barriers), this one 23; a 128-row node 107 -> 65 us.
+// A pivot that is not positive sets *bad; the factor then holds NaN.
+// On return, ls holds the factor and wv its inverse (row stride kLP, zeros
+// above the diagonal, the identity in the padding).
 constexpr int kLeafThreads = 256;
-constexpr int kLeafPer = kLeaf * kLeaf / kLeafThreads;   // entries of a row part
-constexpr int kLP = kLeaf + 1;                           // row stride of the LDS tiles
-struct LeafLds {
-    double ls[kLeaf * kLP];     // the factor, then W (staging of the outputs)
-    double vec[2][2 * kLeaf];   // column k of the factor / row k of W (upper half: slack)
-    double piv_in[2];           // d_k
-    double rdiag[kLeaf];        // 1 / L[k][k]
-};
-__device__ __forceinline__ void leaf_run(double *__restrict__ A, long lda, double *__restrict__ W, long ldw, int n,
-                                         int *__restrict__ bad, LeafLds &sm) {
-    constexpr int L = kLeaf, LP = kLP, PER = kLeafPer;
-    static_assert(PER * 4 == L && L * 4 == kLeafThreads, "four threads per row");
-    double *ls = sm.ls;
-    double(*vec)[2 * L] = sm.vec;
-    double *piv_in = sm.piv_in;
-    double *rdiag = sm.rdiag;
-    const int t = threadIdx.x, ri = t >> 2, part = t & 3;
-    double r[PER];
+constexpr int kLP = kLeaf + 1;   // row stride of the LDS tiles
+constexpr int kPan = 16;         // panel width: one MFMA block
+
+__device__ __forceinline__ double lane_read(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Factor and inverse of the diagonal block at d (in ls), inverse to w (in wv),
+// by one wavefront; its four groups of sixteen lanes do the same.
+__device__ __forceinline__ void chol16(double *__restrict__ d, double *__restrict__ w, int *__restrict__ bad) {
+    const int i = threadIdx.x % kPan;
+    double r[kPan], ip[kPan], x[kPan];
 #pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const int j = 4 * m + part;
-        r[m] = ri < n ? (j <= ri ? A[(long)ri * lda + j] : 0.0) : (j == ri ? 1.0 : 0.0);
+    for (int k = 0; k < kPan; ++k) r[k] = d[i * kLP + k];
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < kPan; ++k) {
+        const double piv = lane_read(r[k], k);
+        ok = ok && piv > 0.0;
+        ip[k] = rsqrt_f64(piv);
+        r[k] *= ip[k];   // L[i][k]; rows above k hold garbage that nothing reads
+#pragma unroll
+        for (int j = k + 1; j < kPan; ++j) r[j] = fma(-r[k], lane_read(r[k], j), r[j]);
     }
-    for (int e = t; e < 2 * L; e += kLeafThreads) vec[0][e] = vec[1][e] = 0.0;
+    // column i of the inverse: L x = e_i
+#pragma unroll
+    for (int k = 0; k < kPan; ++k) x[k] = k == i ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < kPan; ++k) {
+        x[k] *= ip[k];
+#pragma unroll
+        for (int j = k + 1; j < kPan; ++j) x[j] = fma(-lane_read(r[k], j), x[k], x[j]);
+    }
+    if (threadIdx.x < kPan) {
+#pragma unroll
+        for (int k = 0; k < kPan; ++k) {
+            d[i * kLP + k] = k <= i ? r[k] : 0.0;
+            w[k * kLP + i] = x[k];
+        }
+        if (i == 0 && !ok) *bad = 1;
+    }
+}
+
+// acc += X Y^T for 16 x 16 blocks in LDS
+__device__ __forceinline__ f64x4 mm16_nt(const double *__restrict__ X, const double *__restrict__ Y, f64x4 acc) {
+    const int r = threadIdx.x % 16, kq = (threadIdx.x % 64) / 16;
+#pragma unroll
+    for (int ks = 0; ks < kPan; ks += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[r * kLP + ks + kq], Y[r * kLP + ks + kq], acc, 0, 0, 0);
+    return acc;
+}
+// acc += X Y
+__device__ __forceinline__ f64x4 mm16_nn(const double *__restrict__ X, const double *__restrict__ Y, f64x4 acc) {
+    const int r = threadIdx.x % 16, kq = (threadIdx.x % 64) / 16;
+#pragma unroll
+    for (int ks = 0; ks < kPan; ks += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[r * kLP + ks + kq], Y[(ks + kq) * kLP + r], acc, 0, 0, 0);
+    return acc;
+}
+
+__device__ __forceinline__ void leaf_run(double *__restrict__ A, long lda, double *__restrict__ W, long ldw, int n,
+                                         int *__restrict__ bad, double *__restrict__ ls, double *__restrict__ wv) {
+    constexpr int L = kLeaf, LP = kLP, NP = kLeaf / kPan;
+    const int t = threadIdx.x, wave = t / 64, c = t % 16, rq = (t % 64) / 16;
+    auto at = [](double *p, int i, int j) { return p + i * kPan * kLP + j * kPan; };
+#pragma unroll
+    for (int q = 0; q < L * L / kLeafThreads; ++q) {
+        const int e = t + q * kLeafThreads, i = e / L, j = e % L;
+        ls[i * LP + j] = i < n ? (j <= i ? A[(long)i * lda + j] : 0.0) : (j == i ? 1.0 : 0.0);
+        wv[i * LP + j] = 0.0;
+    }
     __syncthreads();
-    if (part == 0) {
-        vec[0][ri] = ri > 0 ? r[0] : 0.0;
-        if (ri == 0) piv_in[0] = r[0];
+#pragma unroll 1
+    for (int p = 0; p < NP; ++p) {
+        if (wave == 0) chol16(at(ls, p, p), at(wv, p, p), bad);
+        __syncthreads();
+        if (p + 1 == NP) break;
+        if (p + 1 + wave < NP) {   // this wavefront alone reads and writes its block
+            double *x = at(ls, p + 1 + wave, p);
+            const f64x4 v = mm16_nt(x, at(wv, p, p), f64x4{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[(rq + 4 * q) * LP + c] = v[q];
+        }
+        __syncthreads();
+        const int m = NP - 1 - p;   // blocks (i, j), p < j <= i
+        for (int e = wave; e < m * (m + 1) / 2; e += 4) {
+            const int i = e >= 3 ? 2 : e >= 1 ? 1 : 0, j = e - i * (i + 1) / 2;
+            double *x = at(ls, p + 1 + i, p + 1 + j);
+            const f64x4 v = mm16_nt(at(ls, p + 1 + i, p), at(ls, p + 1 + j, p), f64x4{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[(rq + 4 * q) * LP + c] -= v[q];
+        }
+        __syncthreads();
     }
 #pragma unroll 1
-    for (int c = 0; c < PER; ++c) {
+    for (int dd = 1; dd < NP; ++dd) {
+        if (wave + dd < NP) {
+            const int j = wave, i = wave + dd;
+            f64x4 sum{0.0, 0.0, 0.0, 0.0}, v{0.0, 0.0, 0.0, 0.0};
+            for (int k = j; k < i; ++k) sum = mm16_nn(at(ls, i, k), at(wv, k, j), sum);
+            // sum[q] is row rq + 4 q, column c: the operand of k step q
+            const double *x = at(wv, i, i);
 #pragma unroll
-        for (int pk = 0; pk < 4; ++pk) {
-            const int k = 4 * c + pk;
-            const double *col = vec[pk & 1];
-            const double *colj = col + 4 * c + part;   // colj[4 m] = a[4 (c + m) + part][k]
-            __syncthreads();
-            const double d = piv_in[pk & 1], cri = col[ri];
-            double cj[PER];
+            for (int q = 0; q < 4; ++q)
+                v = __builtin_amdgcn_mfma_f64_16x16x4f64(x[c * LP + 4 * q + rq], sum[q], v, 0, 0, 0);
+            double *y = at(wv, i, j);
 #pragma unroll
-            for (int m = 0; m < PER; ++m) cj[m] = colj[4 * m];
-            const double ip = rsqrt_f64(d), piv = d * ip, invd = ip * ip;
-            const double lik = cri * invd;
-            const int m1 = (pk + 1) / 4, p1 = (pk + 1) % 4;   // column k + 1
-            r[m1] = fma(-lik, cj[m1], r[m1]);
-            if (part == p1 && k + 1 < L) {
-                vec[(pk + 1) & 1][ri] = ri > k + 1 ? r[m1] : 0.0;
-                if (ri == k + 1) piv_in[(pk + 1) & 1] = r[m1];
-            }
-#pragma unroll
-            for (int m = 0; m < PER; ++m)
-                if (m != m1) r[m] = fma(-lik, cj[m], r[m]);
-            r[0] = part == pk ? (ri == k ? piv : r[0] * ip) : r[0];
-            if (t == 0) {
-                rdiag[k] = ip;
-                if (!(d > 0.0)) *bad = 1;
-            }
+            for (int q = 0; q < 4; ++q) y[(rq + 4 * q) * LP + c] = -v[q];
         }
-        const int j = 4 * c + part;
-        ls[ri * LP + j] = j <= ri ? r[0] : 0.0;
-#pragma unroll
-        for (int m = 0; m + 1 < PER; ++m) r[m] = r[m + 1];
-        r[PER - 1] = 0.0;
-    }
-    __syncthreads();
-    for (int e = t; e < L * L; e += kLeafThreads) {   // rows of L, coalesced
-        const int i = e / L, j = e % L;
-        if (i < n && j <= i) A[(long)i * lda + j] = ls[i * LP + j];
-    }
-    double w[PER];
-#pragma unroll
-    for (int m = 0; m < PER; ++m) w[m] = 4 * m + part == ri ? 1.0 : 0.0;
-    if (ri == 0) {
-#pragma unroll
-        for (int m = 0; m < PER; ++m) vec[0][4 * m + part] = w[m];
-    }
-    double lq = ls[ri * LP] * rdiag[0];   // L[i][k] / L[k][k] for k = 0
-#pragma unroll 2
-    for (int k = 0; k < L; ++k) {
-        const double *row = vec[k & 1];
-        const double ik = rdiag[k];
-        const double lq_next = k + 1 < L ? ls[ri * LP + k + 1] * rdiag[k + 1] : 0.0;
         __syncthreads();
-        if (ri == k) {
-#pragma unroll
-            for (int m = 0; m < PER; ++m) w[m] *= ik;
-        } else if (ri > k) {
-#pragma unroll
-            for (int m = 0; m < PER; ++m) w[m] -= lq * row[4 * m + part];
-            if (ri == k + 1) {
-#pragma unroll
-                for (int m = 0; m < PER; ++m) vec[(k + 1) & 1][4 * m + part] = w[m];
-            }
-        }
-        lq = lq_next;
     }
-    __syncthreads();   // every read of the factor in ls is done
 #pragma unroll
-    for (int m = 0; m < PER; ++m) ls[ri * LP + 4 * m + part] = w[m];
-    __syncthreads();
-    for (int e = t; e < L * L; e += kLeafThreads) {   // W, zeros above the diagonal
-        const int i = e / L, j = e % L;
-        if (i < n && j < n) W[(long)i * ldw + j] = j <= i ? ls[i * LP + j] : 0.0;
+    for (int q = 0; q < L * L / kLeafThreads; ++q) {   // rows of L, and of W with zeros above the diagonal
+        const int e = t + q * kLeafThreads, i = e / L, j = e % L;
+        if (i < n && j <= i) A[(long)i * lda + j] = ls[i * LP + j];
+        if (i < n && j < n) W[(long)i * ldw + j] = j <= i ? wv[i * LP + j] : 0.0;
     }
 }
 
 __global__ __launch_bounds__(kLeafThreads) void k_chol_leaf(double *__restrict__ A, long lda, double *__restrict__ W,
                                                             long ldw, int n, int *__restrict__ bad) {
-    __shared__ LeafLds sm;
-    leaf_run(A, lda, W, ldw, n, bad, sm);
+    __shared__ double ls[kLeaf * kLP], wv[kLeaf * kLP];
+    leaf_run(A, lda, W, ldw, n, bad, ls, wv);
 }
 
 // C = X Y^T for 64 x 64 tiles in LDS (row stride kLP): C[i][j] = sum_k
@@ -337,16 +347,15 @@ __device__ __forceinline__ void mm64(const double *__restrict__ X, const double 
 __global__ __launch_bounds__(kLeafThreads) void k_chol_node(double *__restrict__ A, long lda, double *__restrict__ W,
                                                             long ldw, int n, int *__restrict__ bad) {
     constexpr int L = kLeaf, LP = kLP;
-    __shared__ LeafLds sm;
     __shared__ double Wb[L * LP];   // W11
     __shared__ double Xb[L * LP];   // A21, then L21
-    __shared__ double Tb[L * LP];   // S^T = (L21 W11)^T
+    __shared__ double Tb[L * LP];   // the leaves' factors, then S^T = (L21 W11)^T
+    __shared__ double Vb[L * LP];   // W22
     const int t = threadIdx.x, n2 = n - L;
     double *A21 = A + (long)L * lda, *A22 = A21 + L, *W21 = W + (long)L * ldw, *W22 = W21 + L;
-    leaf_run(A, lda, W, ldw, L, bad, sm);
+    leaf_run(A, lda, W, ldw, L, bad, Tb, Wb);
     for (int e = t; e < L * L; e += kLeafThreads) {
         const int i = e / L, j = e % L;
-        Wb[i * LP + j] = sm.ls[i * LP + j];
         Xb[i * LP + j] = i < n2 ? A21[(long)i * lda + j] : 0.0;
     }
     __syncthreads();
@@ -370,12 +379,13 @@ __global__ __launch_bounds__(kLeafThreads) void k_chol_node(double *__restrict__
         if (i < n2 && j <= i) A22[(long)i * lda + j] -= v;
     });
     __syncthreads();
-    leaf_run(A22, lda, W22, ldw, n2, bad, sm);
+    leaf_run(A22, lda, W22, ldw, n2, bad, Tb, Vb);
+    __syncthreads();   // Tb has been read
     // S^T = W11^T L21^T
     mm64<true>(Wb, Xb, [&](int i, int j, double v) { Tb[i * LP + j] = v; });
     __syncthreads();
     // W21 = -W22 S
-    mm64<false>(sm.ls, Tb, [&](int i, int j, double v) {
+    mm64<false>(Vb, Tb, [&](int i, int j, double v) {
         if (i < n2) W21[(long)i * ldw + j] = -v;
     });
 }

@@ -19,8 +19,8 @@
 //         interpolated at c's nodes (a plain store that precedes M2L);
 //   leaf  per target block: L2P (Phi interpolated at the cells) plus the exact
 //         sum over the neighbouring source blocks.  For B = 8 that sum runs on
-//         the matrix cores, one 512 x 512 matrix per neighbour displacement
-//         (k_ml_pairs_mfma below); for B = 4 in the leaf kernel, the kernel's
+//         the matrix cores, in the even and odd parts of the blocks along each
+//         axis (k_ml_near below); for B = 4 in the leaf kernel, the kernel's
 //         2B x 2B x 2B corner held in LDS, one thread owning one x-row of B
 //         target cells (B^2 FMAs per 3B/2 loads).
 //
@@ -47,6 +47,10 @@ namespace {
 constexpr int kTopSpan = 4;   // top level: at most this many clusters per axis
 constexpr int kNearTile = 128;   // pairs (and output columns) per MFMA tile
 constexpr int kNearKT = 32;      // contraction terms staged in LDS per step
+// Zero axes from which a neighbour product (edge 512 / 2^axes) is cut into
+// tiles of 64 columns: edge 128 in one tile of 128 leaves too few workgroups
+// (sphere shell of 2.1e5 points: 1.29 ms, against 1.22 with tiles of 64)
+constexpr int kNearNarrow = 2;
 
 struct CKey {
     int32_t x, y, z;
@@ -287,26 +291,214 @@ __global__ __launch_bounds__(256) void k_ml_leaf(const double *__restrict__ f, c
 //
 // For a neighbour displacement D (source block - target block) the sum is a
 // dense 512 x 512 matrix K_D[i][j] = G(x_i - y_j), i a target cell, j a source
-// cell, applied to every pair with that displacement: the pairs of one D form
-// a GEMM C[pair][i] = sum_j f[src(pair)][j] K_D[i][j] with gathered rows,
-// whose tiles are added atomically into u (one target receives up to 27
-// displacements, after the leaf kernel has stored its far-field part).
+// cell, applied to every pair with that displacement.  G is even along each
+// axis, so along an axis where D is zero K_D commutes with the reflection of
+// the block: split into the even and odd part along every axis,
+//   T f = (f(h) + f(7 - h), f(h) - f(7 - h)), h < 4,   T^{-1} = T^T / 2,
+// K'_D = T K_D T^{-1} has no entries between the two parities of such an axis.
+// With z zero axes the 512 x 512 product falls into 2^z products of edge
+// 512 / 2^z: an eighth of the work for the block itself, a quarter for the six
+// face neighbours, half for the twelve edge neighbours.  T is additions only.
+// The folded order is [parity px + 2 py + 4 pz][hx + 4 hy + 16 hz], so that the
+// rows of one product are whole 64-value chunks.
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// axes along which displacement code 9 (DZ + 1) + 3 (DY + 1) + DX + 1 is zero
+__host__ __device__ inline int near_zero_axes(int code) {
+    return (code % 3 == 1 ? 1 : 0) | ((code / 3) % 3 == 1 ? 2 : 0) | (code / 9 == 1 ? 4 : 0);
+}
+// parity chunks of product `sub` of a displacement with zero axes zmask, four
+// bits each: the parities whose bits in zmask spell sub
+__host__ __device__ inline unsigned near_chunks(int zmask, int sub) {
+    unsigned out = 0;
+    int n = 0;
+    for (int pi = 0; pi < 8; ++pi) {
+        int key = 0, b = 0;
+        for (int a = 0; a < 3; ++a)
+            if (zmask >> a & 1) key |= (pi >> a & 1) << b++;
+        if (key == sub) out |= (unsigned)pi << (4 * n++);
+    }
+    return out;
+}
+
+// K'_D, product by product: product sub of code at code * 512^2 + sub * N^2, row
+// length N = 512 / 2^z.  One workgroup per (row of the folded target, code).
 template <typename R>
 __global__ __launch_bounds__(256) void k_ml_near_mats(const double *__restrict__ tab, int e1, int e2, int e3,
                                                        R *__restrict__ Kn) {
-    const int code = blockIdx.y, i = blockIdx.x;
+    const int code = blockIdx.y, zm = near_zero_axes(code), z = __popc(zm), N = 512 >> z;
+    const int sub = blockIdx.x / N, i = blockIdx.x % N;
+    const unsigned ch = near_chunks(zm, sub);
     const int DX = code % 3 - 1, DY = (code / 3) % 3 - 1, DZ = code / 9 - 1;
-    const int tx = i & 7, ty = (i >> 3) & 7, tz = i >> 6;
-    for (int j = threadIdx.x; j < 512; j += blockDim.x) {
-        const int sx = j & 7, sy = (j >> 3) & 7, sz = j >> 6;
-        const int dx = abs(tx - sx - 8 * DX), dy = abs(ty - sy - 8 * DY), dz = abs(tz - sz - 8 * DZ);
-        Kn[((size_t)code * 512 + i) * 512 + j] =
-            (R)((dx <= e1 && dy <= e2 && dz <= e3) ? tab[((size_t)dz * (e2 + 1) + dy) * (e1 + 1) + dx] : 0.0);
+    const int pt = ch >> (4 * (i / 64)) & 7, tx = i & 3, ty = (i >> 2) & 3, tz = (i >> 4) & 3;
+    for (int j = threadIdx.x; j < N; j += blockDim.x) {
+        const int ps = ch >> (4 * (j / 64)) & 7, sx = j & 3, sy = (j >> 2) & 3, sz = (j >> 4) & 3;
+        double v = 0.0;
+        for (int a = 0; a < 8; ++a)
+            for (int b = 0; b < 8; ++b) {
+                const int dx = abs((a & 1 ? 7 - tx : tx) - (b & 1 ? 7 - sx : sx) - 8 * DX);
+                const int dy = abs((a & 2 ? 7 - ty : ty) - (b & 2 ? 7 - sy : sy) - 8 * DY);
+                const int dz = abs((a & 4 ? 7 - tz : tz) - (b & 4 ? 7 - sz : sz) - 8 * DZ);
+                const double g =
+                    dx <= e1 && dy <= e2 && dz <= e3 ? tab[((size_t)dz * (e2 + 1) + dy) * (e1 + 1) + dx] : 0.0;
+                v += (__popc(a & pt) + __popc(b & ps)) & 1 ? -g : g;
+            }
+        Kn[((size_t)code * 512 + (size_t)sub * N * N / 512) * 512 + (size_t)i * N + j] = (R)(0.125 * v);
     }
+}
+
+// One butterfly of T along an axis of stride s (in cells) for a block in LDS
+__device__ __forceinline__ void near_fold_axis(double *b, int s, bool inverse) {
+    // 256 pairs (h, 7 - h) of the axis, one per thread: h < 4 and 64 lines
+    const int t = threadIdx.x, h = t & 3, line = t >> 2;
+    const int base = s == 1 ? line * 8 : s == 8 ? (line >> 3) * 64 + (line & 7) : line;
+    // forward: even parts to places 0..3, odd parts to 4..7; inverse: back
+    const double x = b[base + h * s], y = b[base + (inverse ? 4 + h : 7 - h) * s];
+    __syncthreads();
+    b[base + h * s] = x + y;
+    b[base + (inverse ? 7 - h : 4 + h) * s] = x - y;
+    __syncthreads();
+}
+// place of the folded block's cell c (axis places 0..7) in the folded order
+__device__ __forceinline__ int near_place(int c) {
+    const int x = c & 7, y = (c >> 3) & 7, z = c >> 6;
+    return (((x >> 2) | (y >> 2) << 1 | (z >> 2) << 2) << 6) | (x & 3) | (y & 3) << 2 | (z & 3) << 4;
+}
+// Fp = T f for every source block, and zeros in every target block of Yp
+__global__ __launch_bounds__(256) void k_ml_fold(const double *__restrict__ f, double *__restrict__ Fp,
+                                                  double *__restrict__ Yp, int nsrc, int ntgt) {
+    __shared__ double b[512];
+    const int t = threadIdx.x, s = blockIdx.x;
+    if (s < ntgt)
+        for (int c = t; c < 512; c += 256) Yp[(size_t)s * 512 + c] = 0.0;
+    if (s >= nsrc) return;
+    for (int c = t; c < 512; c += 256) b[c] = f[(size_t)s * 512 + c];
+    __syncthreads();
+    near_fold_axis(b, 1, false);
+    near_fold_axis(b, 8, false);
+    near_fold_axis(b, 64, false);
+    for (int c = t; c < 512; c += 256) Fp[(size_t)s * 512 + near_place(c)] = b[c];
+}
+// u += scale T^{-1} Yp
+__global__ __launch_bounds__(256) void k_ml_unfold(const double *__restrict__ Yp, double *__restrict__ u, double scale) {
+    __shared__ double b[512];
+    const int t = threadIdx.x;
+    const size_t o = (size_t)blockIdx.x * 512;
+    for (int c = t; c < 512; c += 256) b[c] = Yp[o + near_place(c)];
+    __syncthreads();
+    near_fold_axis(b, 1, true);
+    near_fold_axis(b, 8, true);
+    near_fold_axis(b, 64, true);
+    for (int c = t; c < 512; c += 256) u[o + c] += scale * (0.125 * b[c]);
+}
+
+// One product of the folded neighbour sum for up to 128 pairs of a displacement:
+// C[pair][n] = sum_k Fp[src(pair)][k] K'[n][k], added atomically into Yp (a
+// target receives up to 27 displacements).  tasks: int4 (matrix offset / 4096,
+// first pair, pair count | column tile << 8 | z << 16, parity chunks).  Tiles of
+// 128 pairs x TN columns, four wavefronts, each a 64 x 64 (TN = 128) or 32 x 64
+// (TN = 64) part as v_mfma_f64_16x16x4f64 products, or v_mfma_f32_16x16x4f32 on
+// request (FP32 matrix and rounded sources, FP32 accumulation).  Bound by the
+// matrix cores: 31.7 GFLOP in 0.86 ms for the 6344 blocks of a sphere shell of
+// diameter 256, where the unfolded matrices took 65 GFLOP and 1.33 ms.
+template <int TN, typename R>
+__global__ __launch_bounds__(256) void k_ml_near(const int4 *__restrict__ tasks, const int2 *__restrict__ pairs,
+                                                  const double *__restrict__ X, const R *__restrict__ Kn,
+                                                  double *__restrict__ Y) {
+    constexpr bool F64 = std::is_same<R, double>::value;
+    using acc_t = typename std::conditional<F64, f64x4, f32x4>::type;
+    constexpr int T = kNearTile, KT = kNearKT;
+    constexpr int FMR = TN == 64 ? 2 : 4, FMC = 4, PA = T * KT / 256, PB = TN * KT / 256;
+    __shared__ R As[T][KT + 1];    // [pair][k]
+    __shared__ R Bs[TN][KT + 1];   // [n][k]
+    __shared__ int srow[T], trow[T];
+    // consecutive tasks (mostly one displacement) on one XCD, so its L2 keeps
+    // the matrix they share
+    const int4 tk = tasks[xcd_remap(blockIdx.x, gridDim.x)];
+    const int npair = tk.z & 255, n0 = (tk.z >> 8 & 255) * TN, N = 512 >> (tk.z >> 16);
+    const unsigned ch = (unsigned)tk.w;
+    const R *A = Kn + (size_t)tk.x * 4096;
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
+    const int wm = TN == 64 ? wave * 32 : (wave / 2) * 64, wn = TN == 64 ? 0 : (wave % 2) * 64;
+    for (int m = tid; m < T; m += 256) {
+        const int2 pr = m < npair ? pairs[tk.y + m] : make_int2(-1, 0);
+        trow[m] = pr.x;
+        srow[m] = pr.y;   // rows past the pairs read block 0 and are not stored
+    }
+    __syncthreads();
+    acc_t acc[FMR][FMC];
+#pragma unroll
+    for (int i = 0; i < FMR; ++i)
+#pragma unroll
+        for (int j = 0; j < FMC; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+    double ra[PA];
+    R rb[PB];
+    const int kk = tid % KT;
+    auto fetch = [&](int k0) {   // a slice lies in one parity chunk
+        const int off = (int)(ch >> (4 * (k0 / 64)) & 7) * 64 + k0 % 64 + kk;
+#pragma unroll
+        for (int q = 0; q < PA; ++q) ra[q] = X[(size_t)srow[tid / KT + q * (256 / KT)] * 512 + off];
+#pragma unroll
+        for (int q = 0; q < PB; ++q) rb[q] = A[(size_t)(n0 + tid / KT + q * (256 / KT)) * N + k0 + kk];
+    };
+    auto stage = [&]() {
+#pragma unroll
+        for (int q = 0; q < PA; ++q) As[tid / KT + q * (256 / KT)][kk] = (R)ra[q];
+#pragma unroll
+        for (int q = 0; q < PB; ++q) Bs[tid / KT + q * (256 / KT)][kk] = rb[q];
+    };
+    fetch(0);
+    stage();
+    __syncthreads();
+    // v_mfma_f64_16x16x4f64: lane l holds A[row l%16][k l/16] and B[k l/16][col
+    // l%16]; the result D[row l/16 + 4q][col l%16] lands in acc[q]
+    const int r = lane % 16, kq = lane / 16;
+    for (int k0 = 0; k0 < N; k0 += KT) {
+        const bool more = k0 + KT < N;
+        if (more) fetch(k0 + KT);
+#pragma unroll
+        for (int ks = 0; ks < KT; ks += 4) {
+            R a[FMR], b[FMC];
+#pragma unroll
+            for (int i = 0; i < FMR; ++i) a[i] = As[wm + 16 * i + r][ks + kq];
+#pragma unroll
+            for (int j = 0; j < FMC; ++j) b[j] = Bs[wn + 16 * j + r][ks + kq];
+#pragma unroll
+            for (int i = 0; i < FMR; ++i)
+#pragma unroll
+                for (int j = 0; j < FMC; ++j) {
+                    if constexpr (F64)
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+                    else
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+                }
+        }
+        __syncthreads();
+        if (more) {
+            stage();
+            __syncthreads();
+        }
+    }
+    const int c = lane % 16, rq = lane / 16;
+    // the tile's columns lie in whole chunks: 16 of them never straddle one
+    int col[FMC];
+#pragma unroll
+    for (int j = 0; j < FMC; ++j) {
+        const int n = n0 + wn + 16 * j;
+        col[j] = (int)(ch >> (4 * (n / 64)) & 7) * 64 + n % 64 + c;
+    }
+#pragma unroll
+    for (int i = 0; i < FMR; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            // result row of acc[q]: l/16 + 4q for the FP64 form, 4(l/16) + q for FP32
+            const int t = trow[wm + 16 * i + (F64 ? rq + 4 * q : 4 * rq + q)];
+            if (t < 0) continue;
+#pragma unroll
+            for (int j = 0; j < FMC; ++j) unsafeAtomicAdd(&Y[(size_t)t * 512 + col[j]], (double)acc[i][j][q]);
+        }
 }
 
 // C[pair][n] = sum_k X[src(pair)][k] A_d[n][k] for the pairs of one task,
@@ -316,8 +508,7 @@ __global__ __launch_bounds__(256) void k_ml_near_mats(const double *__restrict__
 // 128.  Four waves, each a 64 x 64 (TN = 128) or 32 x 64 (TN = 64) block of
 // the tile as v_mfma_f64_16x16x4f64 products; columns past NCOL and
 // contraction terms past KK are zero-filled.
-// Serves the neighbour sum of 8^3 blocks (KK = NCOL = 512, A_d the cell
-// kernel of a displacement) and M2L (KK = NCOL = p^3, A_d the node kernel).
+// Serves M2L (KK = NCOL = p^3, A_d the node kernel).
 // R is the product's precision: double (v_mfma_f64_16x16x4f64), or float
 // (v_mfma_f32_16x16x4f32, FP32 matrix and rounded X, FP32 accumulation)
 // on request; Y is FP64 either way.
@@ -442,9 +633,9 @@ struct lgf_ml {
     std::vector<int> task_off, ntask;   // M2L tasks per level
     int64_t npairs = 0, nnear = 0, nd = 0;
     DevBuf W0, Wup, kids, par, tasks, pairs, K, near_off, near_ent, M, Phi, dinfo, nodes;
-    int nntask = 0;                     // B = 8: neighbour pairs on the matrix cores
+    int nntask[2] = {0, 0};             // B = 8: neighbour products on the matrix cores, 128 and 64 columns wide
     int pair_prec = LGF_F64;            // precision of the pair products (M2L, neighbour sums)
-    DevBuf nbr_tasks, nbr_pairs, Kn;
+    DevBuf nbr_tasks, nbr_pairs, Kn, Fp, Yp;
 };
 
 namespace {
@@ -503,16 +694,24 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
                                pl->near_ent.as<int2>(), Phi, pl->W0.as<double>(), dx * dx, uc, pl->ntgt);
             LGF_HIP(hipGetLastError());
         }
-        if (B == 8 && pl->nntask > 0) {
+        if (B == 8 && pl->nntask[0] + pl->nntask[1] > 0) {
+            double *Fp = pl->Fp.as<double>(), *Yp = pl->Yp.as<double>();
             ProfScope ps(ctx, "k_ml_near_mfma", st);
-            if (pl->pair_prec == LGF_F64)
-                hipLaunchKernelGGL((k_ml_pairs_mfma<512, 512, double>), dim3(pl->nntask, 512 / kNearTile), dim3(256),
-                                   0, st, pl->nbr_tasks.as<int4>(), pl->nbr_pairs.as<int2>(), fc, pl->Kn.as<double>(),
-                                   uc, dx * dx);
-            else
-                hipLaunchKernelGGL((k_ml_pairs_mfma<512, 512, float>), dim3(pl->nntask, 512 / kNearTile), dim3(256),
-                                   0, st, pl->nbr_tasks.as<int4>(), pl->nbr_pairs.as<int2>(), fc, pl->Kn.as<float>(),
-                                   uc, dx * dx);
+            hipLaunchKernelGGL(k_ml_fold, dim3(std::max(pl->nsrc, pl->ntgt)), dim3(256), 0, st, fc, Fp, Yp, pl->nsrc,
+                               pl->ntgt);
+            const int4 *tk = pl->nbr_tasks.as<int4>();
+            const int2 *pr = pl->nbr_pairs.as<int2>();
+            const dim3 g0(pl->nntask[0]), g1(pl->nntask[1]), b(256);
+            if (pl->pair_prec == LGF_F64) {
+                const double *Kn = pl->Kn.as<double>();
+                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, double>), g0, b, 0, st, tk, pr, Fp, Kn, Yp);
+                if (g1.x) hipLaunchKernelGGL((k_ml_near<64, double>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
+            } else {
+                const float *Kn = pl->Kn.as<float>();
+                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, float>), g0, b, 0, st, tk, pr, Fp, Kn, Yp);
+                if (g1.x) hipLaunchKernelGGL((k_ml_near<64, float>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
+            }
+            hipLaunchKernelGGL(k_ml_unfold, dim3(pl->ntgt), b, 0, st, Yp, uc, dx * dx);
             LGF_HIP(hipGetLastError());
         }
     }
@@ -704,14 +903,27 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
                 byc[near_ent[2 * e + 1]].push_back(ti);
                 byc[near_ent[2 * e + 1]].push_back(near_ent[2 * e]);
             }
+        // products of full and half edge in tiles of 128 columns, the others
+        // (edge 128 and 64) in tiles of 64
+        std::vector<int32_t> first(27);
         for (int code = 0; code < 27; ++code) {
-            const int np = (int)(byc[code].size() / 2);
-            for (int s0 = 0; s0 < np; s0 += kNearTile)
-                ntasks.insert(ntasks.end(),
-                              {code, (int32_t)(npairs.size() / 2) + s0, std::min(kNearTile, np - s0), 0});
+            first[code] = (int32_t)(npairs.size() / 2);
             npairs.insert(npairs.end(), byc[code].begin(), byc[code].end());
         }
-        pl->nntask = (int)(ntasks.size() / 4);
+        for (int narrow = 0; narrow < 2; ++narrow)
+            for (int code = 0; code < 27; ++code) {
+                const int zm = near_zero_axes(code), z = __builtin_popcount(zm), N = 512 >> z;
+                const int TN = z < kNearNarrow ? 128 : 64, np = (int)(byc[code].size() / 2);
+                if ((TN == 64) != (narrow == 1)) continue;
+                for (int sub = 0; sub < 1 << z; ++sub)
+                    for (int ct = 0; ct < N / TN; ++ct)
+                        for (int s0 = 0; s0 < np; s0 += kNearTile) {
+                            ntasks.insert(ntasks.end(), {code * 64 + sub * N * N / 4096, first[code] + s0,
+                                                         std::min(kNearTile, np - s0) | ct << 8 | z << 16,
+                                                         (int32_t)near_chunks(zm, sub)});
+                            ++pl->nntask[narrow];
+                        }
+            }
     }
     // interpolation weights
     std::vector<double> W0((size_t)p * B), Wup((size_t)std::max(top, 1) * 2 * p * p);
@@ -732,7 +944,10 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
         (rc = upload(pl->dinfo, dinfo)) || (rc = upload(pl->nodes, nodes_flat)) ||
         (rc = upload(pl->nbr_tasks, ntasks)) || (rc = upload(pl->nbr_pairs, npairs)))
         return rc;
-    if (pl->nntask > 0) {
+    if (pl->nntask[0] + pl->nntask[1] > 0) {
+        if ((rc = pl->Fp.reserve((size_t)nsrc * 512 * sizeof(double))) ||
+            (rc = pl->Yp.reserve((size_t)ntgt * 512 * sizeof(double))))
+            return rc;
         const bool f64 = pair_prec == LGF_F64;
         if ((rc = pl->Kn.reserve((size_t)27 * 512 * 512 * (f64 ? sizeof(double) : sizeof(float))))) return rc;
         if (f64)

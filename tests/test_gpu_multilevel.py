@@ -104,6 +104,26 @@ def test_small_and_far_apart_sets(ctx, src, tgt):
     assert np.max(np.abs(got[0] - ref)) < 1e-11 * np.max(np.abs(ref))
 
 
+@pytest.mark.parametrize("drop_src,drop_tgt", [(3, 50), (50, 3), (0, 0)])
+def test_neighbour_products_over_several_pair_tiles(ctx, drop_src, drop_tgt):
+    """Full neighbourhoods with more than 128 pairs for several displacements
+    (tile remainders) and more sources than targets or fewer, on a kernel that
+    differs by axis and that the evaluator represents exactly."""
+    B, p = 8, 4
+    box = np.array(list(np.ndindex(6, 5, 6)), dtype=np.int32)[:, ::-1] - np.array([2, 1, 4], dtype=np.int32)
+    g = np.random.Generator(np.random.PCG64(90 + drop_src))
+    src = box[np.sort(g.permutation(len(box))[drop_src:])]
+    tgt = box[np.sort(g.permutation(len(box))[drop_tgt:])]
+    ext = [int(v) for v in fmm.ml_table_extent(box, B)]
+    tab = _poly_table(ext)
+    tbl = lg.lgf_table_upload(ctx, tab)
+    f = g.standard_normal((len(src), B, B, B))
+    got, _ = _gpu(ctx, tbl, B, p, src, f, tgt)
+    sel = g.permutation(len(tgt))[:6]
+    ref = fmm.direct_conv(fmm.even_table_kernel(tab), src, f, tgt[sel], B)
+    assert np.max(np.abs(got[0][sel] - ref)) < 1e-11 * np.max(np.abs(ref))
+
+
 @pytest.mark.parametrize("p", [4, 5, 6])
 def test_fp32_pair_products(ctx, p):
     """M2L and the neighbour sum as FP32 matrix products: within 2e-6 of the

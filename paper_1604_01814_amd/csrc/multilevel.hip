@@ -46,7 +46,7 @@ namespace {
 
 constexpr int kTopSpan = 4;   // top level: at most this many clusters per axis
 constexpr int kNearTile = 128;   // pairs (and output columns) per MFMA tile
-constexpr int kNearKT = 32;      // contraction terms staged in LDS per step
+constexpr int kNearKT = 16;      // contraction terms staged in LDS per step
 // Zero axes from which a neighbour product (edge 512 / 2^axes) is cut into
 // tiles of 64 columns: edge 128 in one tile of 128 leaves too few workgroups
 // (sphere shell of 2.1e5 points: 1.29 ms, against 1.22 with tiles of 64)
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void k_ml_l2l(const double *__restrict__ Phip,
             for (int kx = 0; kx < P; ++kx) r += wx[kx * P + bx] * pp[(kz * P + ky) * P + kx];
             acc += wzy * r;
         }
-    Phi[(size_t)c * P3 + b] = acc;
+    Phi[(size_t)c * P3 + b] += acc;
 }
 
 template <int P, typename R>
@@ -394,40 +394,25 @@ __global__ __launch_bounds__(256) void k_ml_unfold(const double *__restrict__ Yp
     for (int c = t; c < 512; c += 256) u[o + c] += scale * (0.125 * b[c]);
 }
 
-// One product of the folded neighbour sum for up to 128 pairs of a displacement:
-// C[pair][n] = sum_k Fp[src(pair)][k] K'[n][k], added atomically into Yp (a
-// target receives up to 27 displacements).  tasks: int4 (matrix offset / 4096,
-// first pair, pair count | column tile << 8 | z << 16, parity chunks).  Tiles of
-// 128 pairs x TN columns, four wavefronts, each a 64 x 64 (TN = 128) or 32 x 64
-// (TN = 64) part as v_mfma_f64_16x16x4f64 products, or v_mfma_f32_16x16x4f32 on
-// request (FP32 matrix and rounded sources, FP32 accumulation).  Bound by the
-// matrix cores: 31.7 GFLOP in 0.86 ms for the 6344 blocks of a sphere shell of
-// diameter 256, where the unfolded matrices took 65 GFLOP and 1.33 ms.
-template <int TN, typename R>
-__global__ __launch_bounds__(256) void k_ml_near(const int4 *__restrict__ tasks, const int2 *__restrict__ pairs,
-                                                  const double *__restrict__ X, const R *__restrict__ Kn,
-                                                  double *__restrict__ Y) {
+// ---- products of gathered rows on the matrix cores
+//
+// One tile: C[row][n] = sum_k a(row, k) b(n, k) for 128 rows (pairs) and TN
+// columns by 4 TN threads, each wavefront a 32 x 64 part as
+// v_mfma_f64_16x16x4f64 products, or v_mfma_f32_16x16x4f32 on request (FP32
+// matrix and rounded sources, FP32 accumulation).  a(m, k) and b(n, k) load the
+// operands of a thread's place in a slice, out(row, col, value) takes a result.
+// Slices of 16 terms and at most 128 registers give two workgroups of eight
+// wavefronts a CU; four wavefronts of 64 x 64 need 275 registers, one workgroup
+// a CU (neighbour products of the sphere shell: 0.63 against 0.73 ms; four
+// wavefronts with two buffers 0.64).
+template <int TN, typename R, typename Rows, typename Cols, typename FA, typename FB, typename OUT>
+__device__ __forceinline__ void pair_tile(Rows &As, Cols &Bs, int K, const FA &la, const FB &lb, const OUT &out) {
     constexpr bool F64 = std::is_same<R, double>::value;
     using acc_t = typename std::conditional<F64, f64x4, f32x4>::type;
-    constexpr int T = kNearTile, KT = kNearKT;
-    constexpr int FMR = TN == 64 ? 2 : 4, FMC = 4, PA = T * KT / 256, PB = TN * KT / 256;
-    __shared__ R As[T][KT + 1];    // [pair][k]
-    __shared__ R Bs[TN][KT + 1];   // [n][k]
-    __shared__ int srow[T], trow[T];
-    // consecutive tasks (mostly one displacement) on one XCD, so its L2 keeps
-    // the matrix they share
-    const int4 tk = tasks[xcd_remap(blockIdx.x, gridDim.x)];
-    const int npair = tk.z & 255, n0 = (tk.z >> 8 & 255) * TN, N = 512 >> (tk.z >> 16);
-    const unsigned ch = (unsigned)tk.w;
-    const R *A = Kn + (size_t)tk.x * 4096;
+    constexpr int KT = kNearKT, NT = 4 * TN, RS = NT / KT;
+    constexpr int FMR = 2, FMC = 4, PA = kNearTile / RS, PB = TN / RS;
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
-    const int wm = TN == 64 ? wave * 32 : (wave / 2) * 64, wn = TN == 64 ? 0 : (wave % 2) * 64;
-    for (int m = tid; m < T; m += 256) {
-        const int2 pr = m < npair ? pairs[tk.y + m] : make_int2(-1, 0);
-        trow[m] = pr.x;
-        srow[m] = pr.y;   // rows past the pairs read block 0 and are not stored
-    }
-    __syncthreads();
+    const int wm = (wave & 3) * 32, wn = (wave >> 2) * 64, kk = tid % KT, row = tid / KT;
     acc_t acc[FMR][FMC];
 #pragma unroll
     for (int i = 0; i < FMR; ++i)
@@ -435,19 +420,17 @@ __global__ __launch_bounds__(256) void k_ml_near(const int4 *__restrict__ tasks,
         for (int j = 0; j < FMC; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
     double ra[PA];
     R rb[PB];
-    const int kk = tid % KT;
-    auto fetch = [&](int k0) {   // a slice lies in one parity chunk
-        const int off = (int)(ch >> (4 * (k0 / 64)) & 7) * 64 + k0 % 64 + kk;
+    auto fetch = [&](int k0) {
 #pragma unroll
-        for (int q = 0; q < PA; ++q) ra[q] = X[(size_t)srow[tid / KT + q * (256 / KT)] * 512 + off];
+        for (int q = 0; q < PA; ++q) ra[q] = la(row + q * RS, k0, kk);
 #pragma unroll
-        for (int q = 0; q < PB; ++q) rb[q] = A[(size_t)(n0 + tid / KT + q * (256 / KT)) * N + k0 + kk];
+        for (int q = 0; q < PB; ++q) rb[q] = lb(row + q * RS, k0, kk);
     };
     auto stage = [&]() {
 #pragma unroll
-        for (int q = 0; q < PA; ++q) As[tid / KT + q * (256 / KT)][kk] = (R)ra[q];
+        for (int q = 0; q < PA; ++q) As[row + q * RS][kk] = (R)ra[q];
 #pragma unroll
-        for (int q = 0; q < PB; ++q) Bs[tid / KT + q * (256 / KT)][kk] = rb[q];
+        for (int q = 0; q < PB; ++q) Bs[row + q * RS][kk] = rb[q];
     };
     fetch(0);
     stage();
@@ -455,8 +438,8 @@ __global__ __launch_bounds__(256) void k_ml_near(const int4 *__restrict__ tasks,
     // v_mfma_f64_16x16x4f64: lane l holds A[row l%16][k l/16] and B[k l/16][col
     // l%16]; the result D[row l/16 + 4q][col l%16] lands in acc[q]
     const int r = lane % 16, kq = lane / 16;
-    for (int k0 = 0; k0 < N; k0 += KT) {
-        const bool more = k0 + KT < N;
+    for (int k0 = 0; k0 < K; k0 += KT) {
+        const bool more = k0 + KT < K;
         if (more) fetch(k0 + KT);
 #pragma unroll
         for (int ks = 0; ks < KT; ks += 4) {
@@ -482,139 +465,95 @@ __global__ __launch_bounds__(256) void k_ml_near(const int4 *__restrict__ tasks,
         }
     }
     const int c = lane % 16, rq = lane / 16;
-    // the tile's columns lie in whole chunks: 16 of them never straddle one
-    int col[FMC];
-#pragma unroll
-    for (int j = 0; j < FMC; ++j) {
-        const int n = n0 + wn + 16 * j;
-        col[j] = (int)(ch >> (4 * (n / 64)) & 7) * 64 + n % 64 + c;
-    }
 #pragma unroll
     for (int i = 0; i < FMR; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            // result row of acc[q]: l/16 + 4q for the FP64 form, 4(l/16) + q for FP32
-            const int t = trow[wm + 16 * i + (F64 ? rq + 4 * q : 4 * rq + q)];
-            if (t < 0) continue;
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int j = 0; j < FMC; ++j) unsafeAtomicAdd(&Y[(size_t)t * 512 + col[j]], (double)acc[i][j][q]);
-        }
+            for (int j = 0; j < FMC; ++j)   // result row of acc[q]: l/16 + 4q for the FP64 form, 4(l/16) + q for FP32
+                out(wm + 16 * i + (F64 ? rq + 4 * q : 4 * rq + q), wn + 16 * j, c, (double)acc[i][j][q]);
 }
 
-// C[pair][n] = sum_k X[src(pair)][k] A_d[n][k] for the pairs of one task,
-// added atomically into Y[tgt(pair)][n]: rows of X and Y hold KK and NCOL
-// values, A_d is NCOL x KK.  tasks: int4 (matrix d, first pair, pair count
-// <= 128, 0); grid (tasks, ceil(NCOL / TN)), TN = 64 for NCOL <= 64, else
-// 128.  Four waves, each a 64 x 64 (TN = 128) or 32 x 64 (TN = 64) block of
-// the tile as v_mfma_f64_16x16x4f64 products; columns past NCOL and
-// contraction terms past KK are zero-filled.
-// Serves M2L (KK = NCOL = p^3, A_d the node kernel).
-// R is the product's precision: double (v_mfma_f64_16x16x4f64), or float
-// (v_mfma_f32_16x16x4f32, FP32 matrix and rounded X, FP32 accumulation)
-// on request; Y is FP64 either way.
-template <int KK, int NCOL, typename R>
-__global__ __launch_bounds__(256) void k_ml_pairs_mfma(const int4 *__restrict__ tasks, const int2 *__restrict__ pairs,
-                                                        const double *__restrict__ X, const R *__restrict__ Amat,
-                                                        double *__restrict__ Y, double scale) {
-    constexpr bool F64 = std::is_same<R, double>::value;
-    using acc_t = typename std::conditional<F64, f64x4, f32x4>::type;
-    // tiles of 128 pairs x TN columns; with TN = 64 each wave takes 32 x 64
-    constexpr int T = kNearTile, TN = NCOL <= 64 ? 64 : 128, KT = kNearKT;
-    constexpr int FMR = TN == 64 ? 2 : 4, FMC = 4, PA = T * KT / 256, PB = TN * KT / 256;
-    constexpr int KP = (KK + KT - 1) / KT * KT;
-    __shared__ R As[T][KT + 1];    // [pair][k]
-    __shared__ R Bs[TN][KT + 1];   // [n][k]
-    __shared__ int srow[T], trow[T];
-    // consecutive tasks (mostly one displacement) on one XCD, so its L2 keeps
-    // the matrix slab they share
-    const int4 tk = tasks[xcd_remap(blockIdx.x, gridDim.x)];
-    const int n0 = blockIdx.y * TN;
-    const R *A = Amat + (size_t)tk.x * NCOL * KK;
-    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
-    const int wm = TN == 64 ? wave * 32 : (wave / 2) * 64, wn = TN == 64 ? 0 : (wave % 2) * 64;
-    for (int m = tid; m < T; m += 256) {
-        const int2 pr = m < tk.z ? pairs[tk.y + m] : make_int2(-1, -1);
+// rows (target, source) of a task's pairs; rows past them read source 0 and
+// are not stored
+__device__ __forceinline__ void pair_rows(const int2 *__restrict__ pairs, int np, int *trow, int *srow) {
+    for (int m = threadIdx.x; m < kNearTile; m += blockDim.x) {
+        const int2 pr = m < np ? pairs[m] : make_int2(-1, 0);
         trow[m] = pr.x;
         srow[m] = pr.y;
     }
     __syncthreads();
-    acc_t acc[FMR][FMC];
-#pragma unroll
-    for (int i = 0; i < FMR; ++i)
-#pragma unroll
-        for (int j = 0; j < FMC; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
-    R ra[PA], rb[PB];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int q = 0; q < PA; ++q) {
-            const int e = tid + 256 * q, k = k0 + e % KT;
-            const int sr = srow[e / KT];
-            ra[q] = (sr >= 0 && k < KK) ? (R)X[(size_t)sr * KK + k] : (R)0;
-        }
-#pragma unroll
-        for (int q = 0; q < PB; ++q) {
-            const int e = tid + 256 * q, k = k0 + e % KT, n = n0 + e / KT;
-            rb[q] = (n < NCOL && k < KK) ? A[(size_t)n * KK + k] : (R)0;
-        }
-    };
-    auto stage = [&]() {
-#pragma unroll
-        for (int q = 0; q < PA; ++q) {
-            const int e = tid + 256 * q;
-            As[e / KT][e % KT] = ra[q];
-        }
-#pragma unroll
-        for (int q = 0; q < PB; ++q) {
-            const int e = tid + 256 * q;
-            Bs[e / KT][e % KT] = rb[q];
-        }
-    };
-    fetch(0);
-    stage();
-    __syncthreads();
-    // v_mfma_f64_16x16x4f64: lane l holds A[row l%16][k l/16] and B[k l/16][col
-    // l%16]; the result D[row l/16 + 4q][col l%16] lands in acc[q]
-    const int r = lane % 16, kq = lane / 16;
-    for (int k0 = 0; k0 < KP; k0 += KT) {
-        const bool more = k0 + KT < KP;
-        if (more) fetch(k0 + KT);
-#pragma unroll
-        for (int ks = 0; ks < KT; ks += 4) {
-            R a[FMR], b[FMC];
-#pragma unroll
-            for (int i = 0; i < FMR; ++i) a[i] = As[wm + 16 * i + r][ks + kq];
-#pragma unroll
-            for (int j = 0; j < FMC; ++j) b[j] = Bs[wn + 16 * j + r][ks + kq];
-#pragma unroll
-            for (int i = 0; i < FMR; ++i)
-#pragma unroll
-                for (int j = 0; j < FMC; ++j) {
-                    if constexpr (F64)
-                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-                    else
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-                }
-        }
-        __syncthreads();
-        if (more) {
-            stage();
-            __syncthreads();
-        }
-    }
-    const int c = lane % 16, rq = lane / 16;
-#pragma unroll
-    for (int i = 0; i < FMR; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            // result row of acc[q]: l/16 + 4q for the FP64 form, 4(l/16) + q for FP32
-            const int t = trow[wm + 16 * i + (F64 ? rq + 4 * q : 4 * rq + q)];
-            if (t < 0) continue;
-#pragma unroll
-            for (int j = 0; j < FMC; ++j) {
-                const int n = n0 + wn + 16 * j + c;
-                if (n < NCOL) unsafeAtomicAdd(&Y[(size_t)t * NCOL + n], scale * (double)acc[i][j][q]);
-            }
-        }
+}
+
+// One product of the folded neighbour sum for up to 128 pairs of a displacement:
+// C[pair][n] = sum_k Fp[src(pair)][k] K'[n][k], added atomically into Yp (a
+// target receives up to 27 displacements).  tasks: int4 (matrix offset / 4096,
+// first pair, pair count | column tile << 8 | z << 16, parity chunks).  Bound by
+// the matrix cores: 31.7 GFLOP in 0.70 ms for the 6344 blocks of a sphere shell
+// of diameter 256, where the unfolded matrices took 65 GFLOP and 1.33 ms (FP64
+// atomics or plain stores: no difference).
+template <int TN, typename R>
+__global__ __launch_bounds__(4 * TN, TN == 128 ? 4 : 2) void k_ml_near(const int4 *__restrict__ tasks,
+                                                                       const int2 *__restrict__ pairs,
+                                                                       const double *__restrict__ X,
+                                                                       const R *__restrict__ Kn,
+                                                                       double *__restrict__ Y) {
+    __shared__ R As[kNearTile][kNearKT + 1];   // [pair][k]
+    __shared__ R Bs[TN][kNearKT + 1];          // [n][k]
+    __shared__ int srow[kNearTile], trow[kNearTile];
+    const int4 tk = tasks[blockIdx.x];
+    const int n0 = (tk.z >> 8 & 255) * TN, N = 512 >> (tk.z >> 16);
+    const unsigned ch = (unsigned)tk.w;
+    const R *A = Kn + (size_t)tk.x * 4096 + (size_t)n0 * N;
+    pair_rows(pairs + tk.y, tk.z & 255, trow, srow);
+    // a slice, and 16 columns, lie in one parity chunk
+    auto chunk = [&](int k) { return (int)(ch >> (4 * (k / 64)) & 7) * 64 + k % 64; };
+    pair_tile<TN, R>(
+        As, Bs, N, [&](int m, int k0, int kk) { return X[(size_t)srow[m] * 512 + (chunk(k0) + kk)]; },
+        [&](int n, int k0, int kk) { return A[n * N + k0 + kk]; },
+        [&](int m, int n, int c, double v) {
+            const int t = trow[m];
+            if (t >= 0) unsafeAtomicAdd(&Y[(size_t)t * 512 + chunk(n0 + n) + c], v);
+        });
+}
+
+// M2L: C[pair][n] = sum_k M[src(pair)][k] A_d[n][k] with the node matrix A_d
+// (NB x NB, NB = p^3) of a displacement, added atomically into Phi.  tasks:
+// int4 (displacement, first pair, pair count, column tile); one launch for the
+// pairs of every level.  Gathers, atomics and products
+// about alike: the 4.0e5 pairs of the sphere shell of diameter 256 at p = 4 in
+// 0.20 ms, against 0.24 level by level (0.16 with plain stores)
+template <int NB, typename R>
+__global__ __launch_bounds__(NB <= 64 ? 256 : 512, NB <= 64 ? 2 : 4) void k_ml_m2l(const int4 *__restrict__ tasks,
+                                                                                 const int2 *__restrict__ pairs,
+                                                                                 const double *__restrict__ M,
+                                                                                 const R *__restrict__ Amat,
+                                                                                 double *__restrict__ Phi) {
+    constexpr int TN = NB <= 64 ? 64 : 128;
+    __shared__ R As[kNearTile][kNearKT + 1];   // [pair][k]
+    __shared__ R Bs[TN][kNearKT + 1];          // [n][k]
+    __shared__ int srow[kNearTile], trow[kNearTile];
+    const int4 tk = tasks[blockIdx.x];
+    const int n0 = tk.w * TN;
+    const R *A = Amat + (size_t)tk.x * NB * NB;
+    pair_rows(pairs + tk.y, tk.z, trow, srow);
+    constexpr bool whole = NB % TN == 0;   // else the last slice and column tile are filled with zeros
+    pair_tile<TN, R>(
+        As, Bs, NB,
+        [&](int m, int k0, int kk) {
+            const int k = k0 + kk;
+            const double v = M[(size_t)srow[m] * NB + (whole ? k : min(k, NB - 1))];
+            return whole || k < NB ? v : 0.0;
+        },
+        [&](int n, int k0, int kk) {
+            const int k = k0 + kk, nn = n0 + n;
+            const R v = A[(whole ? nn : min(nn, NB - 1)) * NB + (whole ? k : min(k, NB - 1))];
+            return whole || (nn < NB && k < NB) ? v : (R)0;
+        },
+        [&](int m, int n, int c, double v) {
+            const int t = trow[m];
+            if (t >= 0 && (whole || n0 + n + c < NB)) unsafeAtomicAdd(&Phi[(size_t)t * NB + n0 + n + c], v);
+        });
 }
 
 }  // namespace
@@ -630,12 +569,12 @@ struct lgf_ml {
     std::vector<int> ns, nt;            // clusters per level
     std::vector<size_t> m_off, t_off;   // first cluster of each level in M / Phi
     std::vector<size_t> kid_off;        // first parent row of each level's M2M map
-    std::vector<int> task_off, ntask;   // M2L tasks per level
+    int nm2l = 0;                       // M2L tasks
     int64_t npairs = 0, nnear = 0, nd = 0;
     DevBuf W0, Wup, kids, par, tasks, pairs, K, near_off, near_ent, M, Phi, dinfo, nodes;
     int nntask[2] = {0, 0};             // B = 8: neighbour products on the matrix cores, 128 and 64 columns wide
     int pair_prec = LGF_F64;            // precision of the pair products (M2L, neighbour sums)
-    DevBuf nbr_tasks, nbr_pairs, Kn, Fp, Yp;
+    DevBuf nbr_tasks, nbr_pairs, Kn, folded;   // folded: sources, then targets
 };
 
 namespace {
@@ -662,30 +601,26 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
                                M + pl->m_off[l + 1] * P3);
             LGF_HIP(hipGetLastError());
         }
-        for (int l = pl->top; l >= 0; --l) {
-            double *Phl = Phi + pl->t_off[l] * P3;
-            if (l == pl->top) {
-                const size_t n = (size_t)pl->nt[l] * P3;
-                hipLaunchKernelGGL(k_ml_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, Phl, n);
-            } else {
-                ProfScope ps(ctx, "k_ml_l2l", st);
-                hipLaunchKernelGGL((k_ml_l2l<P>), dim3(pl->nt[l]), dim3(P3 <= 128 ? 128 : 256), 0, st, Phi + pl->t_off[l + 1] * P3,
-                                   pl->par.as<int>() + 2 * pl->t_off[l], Wup + (size_t)l * 2 * P * P, Phl);
-            }
+        const size_t nphi = (pl->t_off[pl->top] + pl->nt[pl->top]) * P3;
+        hipLaunchKernelGGL(k_ml_zero, dim3((unsigned)((nphi + 255) / 256)), dim3(256), 0, st, Phi, nphi);
+        LGF_HIP(hipGetLastError());
+        if (pl->nm2l > 0) {
+            ProfScope ps(ctx, "k_ml_m2l", st);
+            const dim3 g(pl->nm2l), b(P3 <= 64 ? 256 : 512);
+            if (pl->pair_prec == LGF_F64)
+                hipLaunchKernelGGL((k_ml_m2l<P3, double>), g, b, 0, st, pl->tasks.as<int4>(), pl->pairs.as<int2>(), M,
+                                   pl->K.as<double>(), Phi);
+            else
+                hipLaunchKernelGGL((k_ml_m2l<P3, float>), g, b, 0, st, pl->tasks.as<int4>(), pl->pairs.as<int2>(), M,
+                                   pl->K.as<float>(), Phi);
             LGF_HIP(hipGetLastError());
-            if (pl->ntask[l] > 0) {
-                ProfScope ps(ctx, "k_ml_m2l", st);
-                constexpr int ytiles = P3 <= 64 ? 1 : (P3 + 127) / 128;   // the kernel's column tiles
-                if (pl->pair_prec == LGF_F64)
-                    hipLaunchKernelGGL((k_ml_pairs_mfma<P3, P3, double>), dim3(pl->ntask[l], ytiles), dim3(256), 0,
-                                       st, pl->tasks.as<int4>() + pl->task_off[l], pl->pairs.as<int2>(),
-                                       M + pl->m_off[l] * P3, pl->K.as<double>(), Phl, 1.0);
-                else
-                    hipLaunchKernelGGL((k_ml_pairs_mfma<P3, P3, float>), dim3(pl->ntask[l], ytiles), dim3(256), 0,
-                                       st, pl->tasks.as<int4>() + pl->task_off[l], pl->pairs.as<int2>(),
-                                       M + pl->m_off[l] * P3, pl->K.as<float>(), Phl, 1.0);
-                LGF_HIP(hipGetLastError());
-            }
+        }
+        for (int l = pl->top - 1; l >= 0; --l) {
+            ProfScope ps(ctx, "k_ml_l2l", st);
+            hipLaunchKernelGGL((k_ml_l2l<P>), dim3(pl->nt[l]), dim3(P3 <= 128 ? 128 : 256), 0, st, Phi + pl->t_off[l + 1] * P3,
+                               pl->par.as<int>() + 2 * pl->t_off[l], Wup + (size_t)l * 2 * P * P,
+                               Phi + pl->t_off[l] * P3);
+            LGF_HIP(hipGetLastError());
         }
         {
             ProfScope ps(ctx, "k_ml_leaf", st);
@@ -695,7 +630,7 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
             LGF_HIP(hipGetLastError());
         }
         if (B == 8 && pl->nntask[0] + pl->nntask[1] > 0) {
-            double *Fp = pl->Fp.as<double>(), *Yp = pl->Yp.as<double>();
+            double *Fp = pl->folded.as<double>(), *Yp = Fp + (size_t)pl->nsrc * 512;
             ProfScope ps(ctx, "k_ml_near_mfma", st);
             hipLaunchKernelGGL(k_ml_fold, dim3(std::max(pl->nsrc, pl->ntgt)), dim3(256), 0, st, fc, Fp, Yp, pl->nsrc,
                                pl->ntgt);
@@ -704,11 +639,11 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
             const dim3 g0(pl->nntask[0]), g1(pl->nntask[1]), b(256);
             if (pl->pair_prec == LGF_F64) {
                 const double *Kn = pl->Kn.as<double>();
-                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, double>), g0, b, 0, st, tk, pr, Fp, Kn, Yp);
+                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, double>), g0, dim3(512), 0, st, tk, pr, Fp, Kn, Yp);
                 if (g1.x) hipLaunchKernelGGL((k_ml_near<64, double>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
             } else {
                 const float *Kn = pl->Kn.as<float>();
-                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, float>), g0, b, 0, st, tk, pr, Fp, Kn, Yp);
+                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, float>), g0, dim3(512), 0, st, tk, pr, Fp, Kn, Yp);
                 if (g1.x) hipLaunchKernelGGL((k_ml_near<64, float>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
             }
             hipLaunchKernelGGL(k_ml_unfold, dim3(pl->ntgt), b, 0, st, Yp, uc, dx * dx);
@@ -716,6 +651,25 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
         }
     }
     return LGFIB_OK;
+}
+
+// Launch order of tasks (four ints each, groups of falling cost): workgroup b
+// runs on XCD b % 8, and each XCD takes an eighth of every group, consecutive
+// tasks of it (mostly one displacement, so its L2 keeps the matrix they share).
+// Eighths of the whole list instead leave the XCDs with unequal work: the
+// neighbour products of a sphere shell kept the CUs busy 79 % of the time.
+std::vector<int32_t> spread_tasks(const std::vector<std::vector<int32_t>> &groups) {
+    std::vector<int32_t> q[8], out;
+    size_t longest = 0;
+    for (const auto &g : groups) {
+        const size_t n = g.size() / 4;
+        for (size_t x = 0; x < 8; ++x) q[x].insert(q[x].end(), g.begin() + n * x / 8 * 4, g.begin() + n * (x + 1) / 8 * 4);
+    }
+    for (const auto &v : q) longest = std::max(longest, v.size());
+    for (size_t i = 0; i < longest; i += 4)
+        for (const auto &v : q)
+            if (i < v.size()) out.insert(out.end(), v.begin() + i, v.begin() + i + 4);
+    return out;
 }
 
 template <typename T> int upload(DevBuf &d, const std::vector<T> &v) {
@@ -831,15 +785,19 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
         if (l < top) ks += sc[l + 1].size();
     }
     // interaction lists, grouped by displacement
-    std::vector<int32_t> tasks, pairs;
+    std::vector<int32_t> pairs;
+    std::vector<std::vector<int32_t>> m2l_groups;        // tasks by level
+    const int ytiles = (p * p * p + 127) / 128;          // k_ml_m2l's column tiles
     std::vector<int32_t> dinfo;
     for (int l = 0; l <= top; ++l) {
+        // rows of all levels in one numbering, so that one launch takes them
+        const int32_t t0 = (int32_t)pl->t_off[l], s0 = (int32_t)pl->m_off[l];
         std::vector<std::vector<int32_t>> byd(343);
         auto add = [&](int ti, int si, const CKey &c, const CKey &s) {
             const int Dx = c.x - s.x, Dy = c.y - s.y, Dz = c.z - s.z;
             auto &v = byd[(Dz + 3) * 49 + (Dy + 3) * 7 + Dx + 3];
-            v.push_back(ti);
-            v.push_back(si);
+            v.push_back(t0 + ti);
+            v.push_back(s0 + si);
         };
         for (int ti = 0; ti < (int)tc[l].size(); ++ti) {
             const CKey c = tc[l][ti];
@@ -863,7 +821,7 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
                         }
                     }
         }
-        pl->task_off.push_back((int)(tasks.size() / 4));
+        std::vector<int32_t> ltasks;
         for (int di = 0; di < 343; ++di) {
             const auto &v = byd[di];
             if (v.empty()) continue;
@@ -872,12 +830,16 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
             const int d = (int)(dinfo.size() / 4);
             dinfo.insert(dinfo.end(), {Dx * L, Dy * L, Dz * L, l});
             const int np = (int)(v.size() / 2);
-            for (int s0 = 0; s0 < np; s0 += kNearTile)
-                tasks.insert(tasks.end(), {d, (int32_t)(pairs.size() / 2) + s0, std::min(kNearTile, np - s0), 0});
+            for (int ct = 0; ct < ytiles; ++ct)
+                for (int q = 0; q < np; q += kNearTile)
+                    ltasks.insert(ltasks.end(),
+                                  {d, (int32_t)(pairs.size() / 2) + q, std::min(kNearTile, np - q), ct});
             pairs.insert(pairs.end(), v.begin(), v.end());
         }
-        pl->ntask.push_back((int)(tasks.size() / 4) - pl->task_off.back());
+        m2l_groups.push_back(std::move(ltasks));
     }
+    const std::vector<int32_t> tasks = spread_tasks(m2l_groups);
+    pl->nm2l = (int)(tasks.size() / 4);
     pl->npairs = (int64_t)(pairs.size() / 2);
     pl->nd = (int64_t)(dinfo.size() / 4);
     // neighbour lists of the target blocks
@@ -895,7 +857,7 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
         near_off.push_back((int32_t)(near_ent.size() / 2));
     }
     pl->nnear = (int64_t)(near_ent.size() / 2);
-    std::vector<int32_t> ntasks, npairs;
+    std::vector<int32_t> ntasks[2], npairs;
     if (B == 8) {
         std::vector<std::vector<int32_t>> byc(27);
         for (int ti = 0; ti < ntgt; ++ti)
@@ -910,20 +872,24 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
             first[code] = (int32_t)(npairs.size() / 2);
             npairs.insert(npairs.end(), byc[code].begin(), byc[code].end());
         }
-        for (int narrow = 0; narrow < 2; ++narrow)
-            for (int code = 0; code < 27; ++code) {
-                const int zm = near_zero_axes(code), z = __builtin_popcount(zm), N = 512 >> z;
-                const int TN = z < kNearNarrow ? 128 : 64, np = (int)(byc[code].size() / 2);
-                if ((TN == 64) != (narrow == 1)) continue;
-                for (int sub = 0; sub < 1 << z; ++sub)
-                    for (int ct = 0; ct < N / TN; ++ct)
-                        for (int s0 = 0; s0 < np; s0 += kNearTile) {
-                            ntasks.insert(ntasks.end(), {code * 64 + sub * N * N / 4096, first[code] + s0,
-                                                         std::min(kNearTile, np - s0) | ct << 8 | z << 16,
-                                                         (int32_t)near_chunks(zm, sub)});
-                            ++pl->nntask[narrow];
-                        }
-            }
+        std::vector<std::vector<int32_t>> groups[2] = {std::vector<std::vector<int32_t>>(4),
+                                                       std::vector<std::vector<int32_t>>(4)};   // by z
+        for (int code = 0; code < 27; ++code) {
+            const int zm = near_zero_axes(code), z = __builtin_popcount(zm), N = 512 >> z;
+            const int TN = z < kNearNarrow ? 128 : 64, np = (int)(byc[code].size() / 2);
+            auto &g = groups[TN == 64][z];
+            for (int sub = 0; sub < 1 << z; ++sub)
+                for (int ct = 0; ct < N / TN; ++ct)
+                    for (int s0 = 0; s0 < np; s0 += kNearTile)
+                        g.insert(g.end(), {code * 64 + sub * N * N / 4096, first[code] + s0,
+                                           std::min(kNearTile, np - s0) | ct << 8 | z << 16,
+                                           (int32_t)near_chunks(zm, sub)});
+        }
+        for (int w = 0; w < 2; ++w) {
+            ntasks[w] = spread_tasks(groups[w]);
+            pl->nntask[w] = (int)(ntasks[w].size() / 4);
+        }
+        ntasks[0].insert(ntasks[0].end(), ntasks[1].begin(), ntasks[1].end());
     }
     // interpolation weights
     std::vector<double> W0((size_t)p * B), Wup((size_t)std::max(top, 1) * 2 * p * p);
@@ -942,12 +908,10 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
         (rc = upload(pl->par, par)) || (rc = upload(pl->tasks, tasks)) || (rc = upload(pl->pairs, pairs)) ||
         (rc = upload(pl->near_off, near_off)) || (rc = upload(pl->near_ent, near_ent)) ||
         (rc = upload(pl->dinfo, dinfo)) || (rc = upload(pl->nodes, nodes_flat)) ||
-        (rc = upload(pl->nbr_tasks, ntasks)) || (rc = upload(pl->nbr_pairs, npairs)))
+        (rc = upload(pl->nbr_tasks, ntasks[0])) || (rc = upload(pl->nbr_pairs, npairs)))
         return rc;
     if (pl->nntask[0] + pl->nntask[1] > 0) {
-        if ((rc = pl->Fp.reserve((size_t)nsrc * 512 * sizeof(double))) ||
-            (rc = pl->Yp.reserve((size_t)ntgt * 512 * sizeof(double))))
-            return rc;
+        if ((rc = pl->folded.reserve(((size_t)nsrc + ntgt) * 512 * sizeof(double)))) return rc;
         const bool f64 = pair_prec == LGF_F64;
         if ((rc = pl->Kn.reserve((size_t)27 * 512 * 512 * (f64 ? sizeof(double) : sizeof(float))))) return rc;
         if (f64)

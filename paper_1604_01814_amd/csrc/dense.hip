@@ -435,12 +435,43 @@ __global__ __launch_bounds__(kLeafThreads) void k_chol_node(double *__restrict__
     });
 }
 
-__global__ void k_copy2d(const double *__restrict__ src, long lds, double *__restrict__ dst, long ldd, int rows,
-                         int cols) {
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (long)rows * cols) return;
-    const int i = (int)(t / cols), j = (int)(t % cols);
-    dst[(long)i * ldd + j] = src[(long)i * lds + j];
+// What follows from L21 = S at one level of the recursion, in one launch: A22 -=
+// S S^T (tiles on and below the diagonal), T = S W11 (T nullable) and S copied to
+// A21.  Three launches of their own leave most of the chip idle on the small
+// levels, where a product is bound by its latency
+// (factor of 6600 unknowns: 11.5 -> 10.2 ms).
+__global__ __launch_bounds__(256) void k_chol_trail(int n1, int n2, const double *__restrict__ S, long lds,
+                                                    double *__restrict__ A21, double *__restrict__ A22, long lda,
+                                                    const double *__restrict__ W11, long ldw, double *__restrict__ T,
+                                                    long ldt) {
+    constexpr int E = 64;
+    __shared__ double As[2][E][kKT + 1];
+    __shared__ double Bs[2][E][kKT + 1];
+    const int t1 = (n1 + E - 1) / E, t2 = (n2 + E - 1) / E;
+    int id = blockIdx.x;
+    if (id < t2 * (t2 + 1) / 2) {
+        int r = (int)((sqrtf(8.0f * id + 1.0f) - 1.0f) * 0.5f);
+        while (r * (r + 1) / 2 > id) --r;
+        while ((r + 1) * (r + 2) / 2 <= id) ++r;
+        const int m0 = r * E, n0 = (id - r * (r + 1) / 2) * E;
+        if (m0 + E <= n2)   // then n0 + E <= n2; n1 is a multiple of the slice
+            gemm_f64_tile<2, true, false>(As, Bs, m0, n0, 0, n1, n2, n2, -1.0, S, lds, S, lds, 1.0, A22, lda);
+        else
+            gemm_f64_tile<2, true, true>(As, Bs, m0, n0, 0, n1, n2, n2, -1.0, S, lds, S, lds, 1.0, A22, lda);
+        return;
+    }
+    id -= t2 * (t2 + 1) / 2;
+    if (T && id < t1 * t2) {   // long contractions first: k runs from n0 to n1
+        const int m0 = id % t2 * E, n0 = id / t2 * E;
+        if (m0 + E <= n2)
+            gemm_f64_tile<2, false, false>(As, Bs, m0, n0, n0, n1, n2, n1, 1.0, S, lds, W11, ldw, 0.0, T, ldt);
+        else
+            gemm_f64_tile<2, false, true>(As, Bs, m0, n0, n0, n1, n2, n1, 1.0, S, lds, W11, ldw, 0.0, T, ldt);
+        return;
+    }
+    if (T) id -= t1 * t2;
+    const int m0 = id % t2 * E, c = id / t2 * E + threadIdx.x % E, m1 = min(m0 + E, n2);
+    for (int m = m0 + threadIdx.x / E; m < m1; m += 256 / E) A21[m * lda + c] = S[m * lds + c];
 }
 
 __global__ void k_zero2d(double *__restrict__ dst, long ldd, int rows, int cols) {
@@ -451,9 +482,14 @@ __global__ void k_zero2d(double *__restrict__ dst, long ldd, int rows, int cols)
 
 static inline unsigned nblk256(long n) { return (unsigned)((n + 255) / 256); }
 
-// factor the n x n block at A (lower) into L (in place) and W = L^{-1};
-// S: workspace of at least (n/2 + 64) * (n/2 + 64) doubles
-static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long ldw, double *S, int *bad,
+// Workspace of the recursion: S, L21 of a level until it is in place, and T, per
+// depth, L21 W11 until the level's W22 is known (null: formed in S only then)
+struct CholWs {
+    double *S, *T;
+};
+
+// factor the n x n block at A (lower) into L (in place) and W = L^{-1}
+static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long ldw, CholWs ws, int *bad,
                     hipStream_t st) {
     int rc;
     if (n <= kLeaf) {
@@ -469,26 +505,31 @@ static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long 
         return LGFIB_OK;
     }
     const int n1 = kLeaf * ((n + 2 * kLeaf - 1) / (2 * kLeaf)), n2 = n - n1;
+    const long lds = n1;
     double *A21 = A + (long)n1 * lda, *A22 = A21 + n1, *W21 = W + (long)n1 * ldw, *W22 = W21 + n1;
-    if ((rc = chol_rec(ctx, n1, A, lda, W, ldw, S, bad, st))) return rc;
+    const CholWs inner{ws.S, ws.T ? ws.T + n2 * lds : nullptr};
+    if ((rc = chol_rec(ctx, n1, A, lda, W, ldw, inner, bad, st))) return rc;
     {
         ProfScope ps(ctx, "k_gemm_f64", st);
-        // S = L21 = A21 W11^T, copied over A21
-        if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, true, 0.0, S, n1, false, kTriBtLower, st)))
+        // S = L21 = A21 W11^T
+        if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, true, 0.0, ws.S, lds, false, kTriBtLower, st)))
             return rc;
-        hipLaunchKernelGGL(k_copy2d, dim3(nblk256((long)n2 * n1)), dim3(256), 0, st, S, (long)n1, A21, lda, n2, n1);
+        const unsigned t1 = n1 / 64, t2 = (n2 + 63) / 64;
+        hipLaunchKernelGGL(k_chol_trail, dim3(t2 * (t2 + 1) / 2 + (ws.T ? 2 : 1) * t1 * t2), dim3(256), 0, st, n1, n2,
+                           ws.S, lds, A21, A22, lda, W, ldw, ws.T, lds);
         LGF_HIP(hipGetLastError());
-        // A22 -= L21 L21^T (tiles on and below the diagonal)
-        if ((rc = gemm_f64(n2, n2, n1, -1.0, A21, lda, A21, lda, true, 1.0, A22, lda, true, kTriNone, st)))
-            return rc;
     }
-    if ((rc = chol_rec(ctx, n2, A22, lda, W22, ldw, S, bad, st))) return rc;
+    if ((rc = chol_rec(ctx, n2, A22, lda, W22, ldw, inner, bad, st))) return rc;
     {
         ProfScope ps(ctx, "k_gemm_f64", st);
         // W21 = -W22 (L21 W11)
-        if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, false, 0.0, S, n1, false, kTriBLower, st)))
-            return rc;
-        if ((rc = gemm_f64(n2, n1, n2, -1.0, W22, ldw, S, n1, false, 0.0, W21, ldw, false, kTriALower, st)))
+        const double *T = ws.T;
+        if (!T) {
+            if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, false, 0.0, ws.S, lds, false, kTriBLower, st)))
+                return rc;
+            T = ws.S;
+        }
+        if ((rc = gemm_f64(n2, n1, n2, -1.0, W22, ldw, T, lds, false, 0.0, W21, ldw, false, kTriALower, st)))
             return rc;
     }
     return LGFIB_OK;
@@ -497,14 +538,28 @@ static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long 
 int chol_factor_f64(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long ldw, hipStream_t st) {
     if (n == 0) return LGFIB_OK;
     int rc;
-    const size_t h = (size_t)n / 2 + kLeaf;
-    if ((rc = ctx->dense_ws.reserve(h * h * sizeof(double))) || (rc = ctx->dense_flag.reserve(sizeof(int))))
-        return rc;
+    // S, then T of the depths: half the order of the depth above, rounded up to leaves
+    size_t ns = 0, nt = 0;
+    for (size_t m = n; m > 2 * kLeaf;) {
+        const size_t n1 = kLeaf * ((m + 2 * kLeaf - 1) / (2 * kLeaf));
+        if (!ns) ns = (m - n1) * n1;
+        nt += n1 * n1;
+        m = n1;
+    }
+    CholWs ws{nullptr, nullptr};
+    if (ns) {   // without room for T its products are formed level by level
+        if (ctx->dense_ws.reserve((ns + nt) * sizeof(double)) == LGFIB_OK)
+            ws.T = ctx->dense_ws.as<double>() + ns;
+        else if ((void)hipGetLastError(), (rc = ctx->dense_ws.reserve(ns * sizeof(double))))
+            return rc;
+        ws.S = ctx->dense_ws.as<double>();
+    }
+    if ((rc = ctx->dense_flag.reserve(sizeof(int)))) return rc;
     LGF_HIP(hipMemsetAsync(ctx->dense_flag.p, 0, sizeof(int), st));
     // the strict upper blocks of W are never written by the recursion
     hipLaunchKernelGGL(k_zero2d, dim3(nblk256((long)n * n)), dim3(256), 0, st, W, ldw, n, n);
     LGF_HIP(hipGetLastError());
-    if ((rc = chol_rec(ctx, n, A, lda, W, ldw, ctx->dense_ws.as<double>(), ctx->dense_flag.as<int>(), st))) return rc;
+    if ((rc = chol_rec(ctx, n, A, lda, W, ldw, ws, ctx->dense_flag.as<int>(), st))) return rc;
     int bad = 0;
     LGF_HIP(hipMemcpyAsync(&bad, ctx->dense_flag.p, sizeof(int), hipMemcpyDeviceToHost, st));
     LGF_HIP(hipStreamSynchronize(st));

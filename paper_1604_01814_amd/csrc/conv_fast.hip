@@ -296,6 +296,111 @@ template <typename C, int P, int NP> struct ZMul {
     }
 };
 
+// A column of a two-stage length P = Q x 16 (Q <= 20) without a trip through LDS at
+// its ends or between its transforms: the first stage takes its elements
+// z = j + 16 r from registers that were loaded in that place, the second leaves a
+// thread with kz = j + r Q, the very elements that a first inverse stage of radix
+// 16 needs, and the last stage stores its outputs z = j + 16 r.  Two writes and two
+// reads of a column's P values where stage after stage has eight passes (half of
+// them half a column), four barriers instead of ten.
+//
+// Taken where the pass alone measured faster (three components of a cubic box,
+// us, on the stages in LDS -> here):
+//   FP32   48: 7.0 -> 5.7    64: 8.2 -> 6.9    96: 14.6 -> 14.1  128: 18.6 -> 15.9
+//         160: 33.0 -> 29.8  192: 49.5 -> 47.5 240: 68.6 -> 64.0
+//   FP64   32: 8.9 -> 6.8    48: 21.1 -> 15.3  64: 21.8 -> 16.7   80: 23.2 -> 18.1
+//          96: 25.0 -> 20.3  128: 29.2 -> 24.1 144: 37.5 -> 30.8 192: 72.8 -> 64.1
+//         320: 308 -> 287
+// and not where the registers that a thread holds at both ends leave too few
+// workgroups in flight or an odd radix idles threads: FP32 80 9.9 -> 11.5, 144
+// 23.1 -> 23.9, 256 74 -> 79, 288 123 -> 126, 320 154 -> 162, 384 367 -> 474, 480 217 ->
+// 265; FP64 160 43.0 -> 45.9, 240 121 -> 128, 256 136 -> 150, 288 210 -> 241, 384
+// 826 -> 2046 (with the radices exchanged 1306).
+template <typename C, int P> constexpr bool z_column() {
+    if (sizeof(C) == 8) return P == 32 || P == 48 || P == 64 || P == 96 || P == 128 || P == 160 || P == 192 || P == 240;
+    return P == 32 || P == 48 || P == 64 || P == 80 || P == 96 || P == 128 || P == 144 || P == 192 || P == 320;
+}
+template <typename C, int P, int NP> struct ZColumn {
+    using R = typename RealOf<C>::T;
+    static constexpr int Q = P / 16, M = 16, Ph = P / 2;
+    static constexpr int N1 = M * NP, NB = (N1 + kFftThreads - 1) / kFftThreads;   // butterflies of radix Q, by thread
+    static constexpr int RH = (Q + 1) / 2;                                         // of their Q elements, z < Ph
+    static_assert(RadixOf<P>::last == M && Q * NP <= kFftThreads, "one butterfly of radix M a thread");
+    C pre[NB][RH];
+    // b: the column's first element of pencil 0, zrow apart along z
+    __device__ __forceinline__ void load(const C *b, size_t zrow) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int idx = threadIdx.x + i * kFftThreads, p = idx % NP, j = idx / NP;
+            if (N1 % kFftThreads == 0 || idx < N1)
+#pragma unroll
+                for (int r = 0; r < RH; ++r) {
+                    const int z = Q % 2 == 0 ? j + r * M : min(j + r * M, Ph - 1);
+                    pre[i][r] = ld_pencil<nt_on(kNtZLd)>(&b[z * zrow + p]);
+                }
+        }
+    }
+    // first stage of the forward transform; the barrier that follows is the caller's
+    __device__ __forceinline__ void first(C *s) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int idx = threadIdx.x + i * kFftThreads, p = idx % NP, j = idx / NP;
+            if (N1 % kFftThreads != 0 && idx >= N1) break;
+            C v[Q];
+#pragma unroll
+            for (int r = 0; r < Q; ++r) v[r] = r < RH && (Q % 2 == 0 || r + 1 < RH || j + r * M < Ph) ? pre[i][r] : C{};
+            Dft<C, Q, false>::run(v);
+#pragma unroll
+            for (int r = 0; r < Q; ++r) s[(Q * j + r) * NP + p] = v[r];
+        }
+    }
+    // the rest; s must hold every first stage and t the last stage's table
+    // w^(a b), a < Q, 1 <= b < 16, at a * 15 + b - 1
+    __device__ __forceinline__ void rest(C *s, const C *t, const R *gh, C *b, size_t zrow) const {
+        {
+            const int p = threadIdx.x % NP, j = threadIdx.x / NP;
+            C v[M];
+            if (Q * NP == kFftThreads || j < Q) {
+#pragma unroll
+                for (int r = 0; r < M; ++r) v[r] = s[(j + r * Q) * NP + p];
+#pragma unroll
+                for (int r = 1; r < M; ++r) v[r] = cmul(v[r], t[j * 15 + r - 1]);
+                Dft<C, M, false>::run(v);
+#pragma unroll
+                for (int r = 0; r < M; ++r) {
+                    const int kz = j + r * Q;
+                    const R w = gh[min(kz, P - kz) * NP + p];
+                    v[r] = C{v[r].x * w, v[r].y * w};
+                }
+                Dft<C, M, true>::run(v);
+            }
+            lds_barrier();
+            if (Q * NP == kFftThreads || j < Q)
+#pragma unroll
+                for (int r = 0; r < M; ++r) s[(M * j + r) * NP + p] = v[r];
+        }
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int idx = threadIdx.x + i * kFftThreads, p = idx % NP, j = idx / NP;
+            if (N1 % kFftThreads != 0 && idx >= N1) break;
+            C v[Q];
+#pragma unroll
+            for (int r = 0; r < Q; ++r) v[r] = s[(j + r * M) * NP + p];
+#pragma unroll
+            for (int r = 1; r < Q; ++r) {
+                const C w = t[r * 15 + j - 1];   // j = 0: some other entry, not used
+                v[r] = cmul(v[r], j ? C{w.x, -w.y} : C{1, 0});
+            }
+            Dft<C, Q, true>::run(v);
+#pragma unroll
+            for (int r = 0; r < RH; ++r)
+                if (Q % 2 == 0 || r + 1 < RH || j + r * M < Ph) st_pencil<nt_on(kNtZSt)>(&b[(j + r * M) * zrow + p], v[r]);
+        }
+        lds_barrier();
+    }
+};
+
 // Tile = (kx tile, kyh): the workgroup convolves the columns ky = kyh and
 // ky = P1 - kyh (which share the kernel-spectrum column) for every component.
 // Only z < P/2 holds sources and only z < P/2 is kept, so the forward FFT
@@ -329,9 +434,29 @@ __device__ __forceinline__ void zconv_body(const BoxGeo &g, C *__restrict__ X2,
     const int per = (2 * g.ncomp + parts - 1) / parts;
     const int i0 = (bid % parts) * per, i1 = min(nitems, i0 + per);
     if (i0 >= i1) return;
+    const size_t zrow = (size_t)g.P1 * Kxp;
+    if constexpr (z_column<C, P>() && P / 16 * NP <= kFftThreads) {
+        auto column = [&](int item) -> C * {
+            const int ky = (item / g.ncomp) == 0 ? kyh : g.P1 - kyh;
+            return X2 + (size_t)(item % g.ncomp) * g.N2 * zrow + (size_t)ky * Kxp + k0;
+        };
+        ZColumn<C, P, NP> z;
+        z.load(column(i0), zrow);
+        for (int idx = threadIdx.x; idx < NP * (Ph + 1); idx += kFftThreads) {
+            const int p = idx % NP, kz = idx / NP;
+            gh[kz * NP + p] = scale * ghat[((size_t)kz * H1 + kyh) * Kxp + k0 + p];
+        }
+        last_stage_twiddles<C, P, 16>(twt, twg);
+        for (int item = i0; item < i1; ++item) {
+            z.first(s);
+            if (item + 1 < i1) z.load(column(item + 1), zrow);
+            lds_barrier();
+            z.rest(s, twt, gh, column(item), zrow);
+        }
+        return;
+    }
     // element e of a thread's column slice sits zstep * e past its first one
     // (consecutive threads walk pencils, then z)
-    const size_t zrow = (size_t)g.P1 * Kxp;
     const size_t zstep = (size_t)(kFftThreads / NP) * zrow;
     const size_t lane = (size_t)(threadIdx.x / NP) * zrow + k0 + threadIdx.x % NP;
     static_assert(kFftThreads % NP == 0, "pencils must divide the workgroup");

@@ -411,3 +411,26 @@ def test_poisson_two_stage_lengths_on_each_axis(ctx, B, n, dtype):
         ext = [int(v) + 1 for v in _span_ext(b, b, B)]
         ref = oracle.conv_direct(oracle.lgf_table(*ext), cells, f.reshape(-1), cells[pick])
         assert _relerr(ud.cpu().numpy().reshape(-1)[pick], ref) < TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 20])
+def test_poisson_full_column_along_z(ctx, n, dtype):
+    """Transforms of 32 to 320 points along z with a source in every cell of the
+    column and two components (whose columns follow each other in a workgroup),
+    against the oracle's direct sum at the file's bars."""
+    B = 8
+    g = np.random.Generator(np.random.PCG64(2718 + n))
+    b = np.zeros((n, 3), dtype=np.int32)
+    b[:, 2] = g.permutation(n)
+    f = g.standard_normal((2, n, B, B, B))
+    t = lg.lgf_table_build(ctx, lg.LGF_KIND_L, 0.0, _span_ext(b, b, B))
+    fd = _dev(f, dtype)
+    ud = torch.zeros_like(fd)
+    lg.lgf_poisson_apply(ctx, t, B, b, b, fd, ud)
+    cells = workloads.block_cells(b, B)
+    pick = g.choice(len(cells), 120, replace=False)
+    ext = [int(v) + 1 for v in _span_ext(b, b, B)]
+    for c in range(2):
+        ref = oracle.conv_direct(oracle.lgf_table(*ext), cells, f[c].reshape(-1), cells[pick])
+        assert _relerr(ud.cpu().numpy()[c].reshape(-1)[pick], ref) < TOL[dtype], c

@@ -490,7 +490,7 @@ __device__ __forceinline__ void pair_rows(const int2 *__restrict__ pairs, int np
 // target receives up to 27 displacements).  tasks: int4 (matrix offset / 4096,
 // first pair, pair count | column tile << 8 | z << 16, parity chunks).  Bound by
 // the matrix cores: 31.7 GFLOP in 0.70 ms for the 6344 blocks of a sphere shell
-// of diameter 256, where the unfolded matrices took 65 GFLOP and 1.33 ms (FP64
+// of diameter 256, where the unfolded matrices took 58.5 GFLOP and 1.33 ms (FP64
 // atomics or plain stores: no difference).
 template <int TN, typename R>
 __global__ __launch_bounds__(4 * TN, TN == 128 ? 4 : 2) void k_ml_near(const int4 *__restrict__ tasks,
@@ -521,8 +521,8 @@ __global__ __launch_bounds__(4 * TN, TN == 128 ? 4 : 2) void k_ml_near(const int
 // (NB x NB, NB = p^3) of a displacement, added atomically into Phi.  tasks:
 // int4 (displacement, first pair, pair count, column tile); one launch for the
 // pairs of every level.  Gathers, atomics and products
-// about alike: the 4.0e5 pairs of the sphere shell of diameter 256 at p = 4 in
-// 0.20 ms, against 0.24 level by level (0.16 with plain stores)
+// about alike: the 481,568 pairs of the sphere shell of diameter 256 at p = 4
+// in 0.20 ms, against 0.24 level by level (0.16 with plain stores)
 template <int NB, typename R>
 __global__ __launch_bounds__(NB <= 64 ? 256 : 512, NB <= 64 ? 2 : 4) void k_ml_m2l(const int4 *__restrict__ tasks,
                                                                                  const int2 *__restrict__ pairs,

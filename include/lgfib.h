@@ -332,7 +332,7 @@ typedef struct {
     int iterations;        /* CG iterations (inner iterations summed) */
     int restarts;          /* outer FP64 residual evaluations */
     int fallback;          /* 1 if x0 was rejected (NaN/Inf or worse than 0) */
-    double rel_residual;   /* final ||b - C f|| / ||b|| from an FP64 matvec */
+    double rel_residual;   /* final ||b - C f|| / ||b|| from FP64 matvecs */
     double ms;             /* wall time of the solve */
     int graphs;            /* 1: CG iterations ran as captured HIP graphs */
 } ib_solve_stats_t;
@@ -341,7 +341,10 @@ typedef struct {
  * The matvec runs in prec; all dot products, the iterate and the residual
  * in FP64.  With prec == LGF_F32 the solve is refined: inner FP32-matvec CG
  * sweeps are restarted from the FP64 true residual b - C f until
- * ||b - C f|| / ||b|| <= rtol (FP64 matvec).  x0 (DEVICE [NL][3] double, may
+ * ||b - C f|| / ||b|| <= rtol (FP64 matvec).  Near the rounding error of an
+ * FP64 matvec, where a sweep no longer halves that residual, it is formed
+ * from the mean of up to 64 of them (at scales between 1 and 2 of f), with
+ * either prec.  x0 (DEVICE [NL][3] double, may
  * be NULL for a cold start) is the initial guess; a guess containing NaN/Inf
  * or whose residual exceeds ||b|| is replaced by 0 and stats->fallback = 1.
  * b, f: DEVICE double [NL][3].  Returns LGFIB_ENOCONV (with f holding the

@@ -330,3 +330,37 @@ def test_schur_matvec_block_edges(ctx, NL, B, kernel):
         lg.ib_schur_apply(ctx, sys, xd, y2)
         assert torch.equal(y, y2)
     sys.close()
+
+
+@pytest.mark.parametrize("prec", [lg.LGF_F32, lg.LGF_F64])
+def test_force_solve_at_the_rounding_of_its_matvec(ctx, prec):
+    """A tolerance of 0.6 eta, eta the rounding error of one FP64 matvec at the
+    solution.  A residual formed by one matvec stays near sqrt(2) eta (the error
+    of the residual that a sweep starts from and of the one that it is judged
+    by; somewhat less, as the two are not independent) and never meets it.
+    Formed by 64 they carry eta / 8 each, and with the sweep's stop at half the
+    tolerance the sum is 0.35 eta.  A smooth velocity, for which the force is
+    some thousand times larger; the force found is judged by 100 matvecs at
+    other scales, another eta / 10."""
+    NL, B = 1200, 8
+    X = workloads.fibonacci_sphere(NL, 12.0, (40.3, 40.3, 40.3))
+    sys = lg.ib_system_create(ctx, lg.IB_ROMA3, X, B, lg.ib_body_blocks(lg.IB_ROMA3, X, B), 0.05)
+
+    def matvec(x):
+        y = torch.empty_like(x)
+        lg.ib_schur_apply(ctx, sys, x.contiguous(), y)
+        return y
+
+    g = np.random.Generator(np.random.PCG64(15))
+    k, ph, am = g.uniform(-0.15, 0.15, (4, 3)), g.uniform(0, 2 * np.pi, (4, 1, 3)), g.standard_normal((4, 1, 3))
+    b = torch.from_numpy(sum(am[q] * np.sin((X @ k[q])[:, None] + ph[q]) for q in range(4))).cuda()
+    bn = float(b.norm())
+    f0, f = torch.zeros_like(b), torch.zeros_like(b)
+    lg.ib_force_solve(ctx, sys, b, f0, rtol=1e-10, maxit=3000)
+    ys = [matvec(s * f0) / s for s in (1.0, 1 / 3.0, 0.7, 0.55)]
+    eta = float(np.mean([float((ys[p] - ys[q]).norm()) for p in range(4) for q in range(p)])) / np.sqrt(2.0)
+    st = lg.ib_force_solve(ctx, sys, b, f, rtol=0.6 * eta / bn, maxit=3000, prec=prec)
+    assert st["converged"] and st["rel_residual"] <= 0.6 * eta / bn
+    r = b - sum(matvec(s * f) / s for s in np.linspace(0.37, 0.93, 100)) / 100
+    assert float(r.norm()) <= (0.6 + 1 / 8 + 1 / 10) * eta
+    sys.close()

@@ -366,9 +366,12 @@ __device__ __forceinline__ int near_place(int c) {
     const int x = c & 7, y = (c >> 3) & 7, z = c >> 6;
     return (((x >> 2) | (y >> 2) << 1 | (z >> 2) << 2) << 6) | (x & 3) | (y & 3) << 2 | (z & 3) << 4;
 }
-// Fp = T f for every source block, and zeros in every target block of Yp
+// Fp = T f for every source block, and zeros in every target block of Yp.
+// bad[s]: a folded value of block s is no finite R (an infinity or NaN in f, or
+// a sum of finite cells that overflows)
+template <typename R>
 __global__ __launch_bounds__(256) void k_ml_fold(const double *__restrict__ f, double *__restrict__ Fp,
-                                                  double *__restrict__ Yp, int nsrc, int ntgt) {
+                                                  double *__restrict__ Yp, int *__restrict__ bad, int nsrc, int ntgt) {
     __shared__ double b[512];
     const int t = threadIdx.x, s = blockIdx.x;
     if (s < ntgt)
@@ -379,15 +382,58 @@ __global__ __launch_bounds__(256) void k_ml_fold(const double *__restrict__ f, d
     near_fold_axis(b, 1, false);
     near_fold_axis(b, 8, false);
     near_fold_axis(b, 64, false);
-    for (int c = t; c < 512; c += 256) Fp[(size_t)s * 512 + near_place(c)] = b[c];
+    bool fin = true;
+    for (int c = t; c < 512; c += 256) {
+        Fp[(size_t)s * 512 + near_place(c)] = b[c];
+        fin = fin && isfinite((R)b[c]);
+    }
+    const int any = __syncthreads_or(!fin);
+    if (t == 0) bad[s] = any;
 }
-// u += scale T^{-1} Yp
-__global__ __launch_bounds__(256) void k_ml_unfold(const double *__restrict__ Yp, double *__restrict__ u, double scale) {
+
+// The neighbour sum of target block t as it stands, without the parities:
+// u += scale sum_s sum_j G(x_i - y_j) f_j, in R as the products
+template <typename R>
+__device__ __noinline__ void near_direct(const double *__restrict__ f, const double *__restrict__ tab, int e1, int e2,
+                                         int e3, const int2 *__restrict__ ent, int n, double *__restrict__ u,
+                                         double scale, double *b) {
+    R acc[2] = {0, 0};
+    for (int e = 0; e < n; ++e) {
+        const int2 en = ent[e];
+        const int DX = en.y % 3 - 1, DY = (en.y / 3) % 3 - 1, DZ = en.y / 9 - 1;
+        __syncthreads();
+        for (int c = threadIdx.x; c < 512; c += 256) b[c] = f[(size_t)en.x * 512 + c];
+        __syncthreads();
+        for (int j = 0; j < 512; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int i = threadIdx.x + 256 * h;
+                const int dx = abs((i & 7) - (j & 7) - 8 * DX);
+                const int dy = abs((i >> 3 & 7) - (j >> 3 & 7) - 8 * DY);
+                const int dz = abs((i >> 6) - (j >> 6) - 8 * DZ);
+                const R g = dx <= e1 && dy <= e2 && dz <= e3 ? (R)tab[((size_t)dz * (e2 + 1) + dy) * (e1 + 1) + dx] : (R)0;
+                acc[h] += g * (R)b[j];
+            }
+    }
+    for (int h = 0; h < 2; ++h) u[threadIdx.x + 256 * h] += scale * (double)acc[h];
+}
+
+// u += scale T^{-1} Yp.  Sums and differences of a block's cells spread an
+// infinity as NaN over the block; a target with such a source beside it takes
+// the plain sum instead, where it meets each cell on its own.
+template <typename R>
+__global__ __launch_bounds__(256) void k_ml_unfold(const double *__restrict__ Yp, double *__restrict__ u, double scale,
+                                                    const int *__restrict__ near_off, const int2 *__restrict__ near_ent,
+                                                    const int *__restrict__ bad, const double *__restrict__ f,
+                                                    const double *__restrict__ tab, int e1, int e2, int e3) {
     __shared__ double b[512];
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, n0 = near_off[blockIdx.x], n = near_off[blockIdx.x + 1] - n0;   // n <= 27
     const size_t o = (size_t)blockIdx.x * 512;
     for (int c = t; c < 512; c += 256) b[c] = Yp[o + near_place(c)];
-    __syncthreads();
+    if (__syncthreads_or(t < n && bad[near_ent[n0 + t].x])) {
+        near_direct<R>(f, tab, e1, e2, e3, near_ent + n0, n, u + o, scale, b);
+        return;
+    }
     near_fold_axis(b, 1, true);
     near_fold_axis(b, 8, true);
     near_fold_axis(b, 64, true);
@@ -574,7 +620,7 @@ struct lgf_ml {
     DevBuf W0, Wup, kids, par, tasks, pairs, K, near_off, near_ent, M, Phi, dinfo, nodes;
     int nntask[2] = {0, 0};             // B = 8: neighbour products on the matrix cores, 128 and 64 columns wide
     int pair_prec = LGF_F64;            // precision of the pair products (M2L, neighbour sums)
-    DevBuf nbr_tasks, nbr_pairs, Kn, folded;   // folded: sources, then targets
+    DevBuf nbr_tasks, nbr_pairs, Kn, folded, bad;   // folded: sources, then targets; bad: by source block
 };
 
 namespace {
@@ -632,21 +678,21 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
         if (B == 8 && pl->nntask[0] + pl->nntask[1] > 0) {
             double *Fp = pl->folded.as<double>(), *Yp = Fp + (size_t)pl->nsrc * 512;
             ProfScope ps(ctx, "k_ml_near_mfma", st);
-            hipLaunchKernelGGL(k_ml_fold, dim3(std::max(pl->nsrc, pl->ntgt)), dim3(256), 0, st, fc, Fp, Yp, pl->nsrc,
-                               pl->ntgt);
             const int4 *tk = pl->nbr_tasks.as<int4>();
             const int2 *pr = pl->nbr_pairs.as<int2>();
-            const dim3 g0(pl->nntask[0]), g1(pl->nntask[1]), b(256);
-            if (pl->pair_prec == LGF_F64) {
-                const double *Kn = pl->Kn.as<double>();
-                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, double>), g0, dim3(512), 0, st, tk, pr, Fp, Kn, Yp);
-                if (g1.x) hipLaunchKernelGGL((k_ml_near<64, double>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
-            } else {
-                const float *Kn = pl->Kn.as<float>();
-                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, float>), g0, dim3(512), 0, st, tk, pr, Fp, Kn, Yp);
-                if (g1.x) hipLaunchKernelGGL((k_ml_near<64, float>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
-            }
-            hipLaunchKernelGGL(k_ml_unfold, dim3(pl->ntgt), b, 0, st, Yp, uc, dx * dx);
+            auto run = [&](auto *Kn) {
+                using R = std::remove_reference_t<decltype(*Kn)>;
+                const dim3 g0(pl->nntask[0]), g1(pl->nntask[1]), b(256);
+                hipLaunchKernelGGL(k_ml_fold<R>, dim3(std::max(pl->nsrc, pl->ntgt)), b, 0, st, fc, Fp, Yp,
+                                   pl->bad.as<int>(), pl->nsrc, pl->ntgt);
+                if (g0.x) hipLaunchKernelGGL((k_ml_near<128, R>), g0, dim3(512), 0, st, tk, pr, Fp, Kn, Yp);
+                if (g1.x) hipLaunchKernelGGL((k_ml_near<64, R>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
+                hipLaunchKernelGGL(k_ml_unfold<R>, dim3(pl->ntgt), b, 0, st, Yp, uc, dx * dx, pl->near_off.as<int>(),
+                                   pl->near_ent.as<int2>(), pl->bad.as<int>(), fc, tb.g.as<double>(), tb.ext[0],
+                                   tb.ext[1], tb.ext[2]);
+            };
+            if (pl->pair_prec == LGF_F64) run(pl->Kn.as<double>());
+            else run(pl->Kn.as<float>());
             LGF_HIP(hipGetLastError());
         }
     }
@@ -911,7 +957,9 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
         (rc = upload(pl->nbr_tasks, ntasks[0])) || (rc = upload(pl->nbr_pairs, npairs)))
         return rc;
     if (pl->nntask[0] + pl->nntask[1] > 0) {
-        if ((rc = pl->folded.reserve(((size_t)nsrc + ntgt) * 512 * sizeof(double)))) return rc;
+        if ((rc = pl->folded.reserve(((size_t)nsrc + ntgt) * 512 * sizeof(double))) ||
+            (rc = pl->bad.reserve((size_t)nsrc * sizeof(int))))
+            return rc;
         const bool f64 = pair_prec == LGF_F64;
         if ((rc = pl->Kn.reserve((size_t)27 * 512 * 512 * (f64 ? sizeof(double) : sizeof(float))))) return rc;
         if (f64)

@@ -124,6 +124,41 @@ def test_neighbour_products_over_several_pair_tiles(ctx, drop_src, drop_tgt):
     assert np.max(np.abs(got[0][sel] - ref)) < 1e-11 * np.max(np.abs(ref))
 
 
+@pytest.mark.parametrize("prec", [lg.LGF_F64, lg.LGF_F32])
+def test_neighbours_of_an_infinite_cell(ctx, prec):
+    """The neighbour sum of 8^3 blocks runs on sums and differences of a block's
+    cells, the definition meets every cell on its own: with a kernel of positive
+    values an infinity reaches each cell of its neighbours as that infinity, two
+    of opposite sign as NaN, and cells whose sum alone overflows stay finite.  A
+    second component without such cells is what it is without them (bars: FP64
+    and FP32 products as above and below)."""
+    B, p = 8, 4
+    src = np.array(list(np.ndindex(7, 2, 2)), dtype=np.int32)
+    ext = [int(v) for v in fmm.ml_table_extent(src, B)]
+    tab = np.abs(oracle.lgf_table(*ext)) + 1e-3
+    tbl = lg.lgf_table_upload(ctx, tab)
+    g = np.random.Generator(np.random.PCG64(91))
+    f = g.standard_normal((len(src), B, B, B))
+    clean, _ = _gpu(ctx, tbl, B, p, src, f, src, pair_prec=prec)
+    bar = 1e-12 if prec == lg.LGF_F64 else 2e-6
+    near = src[:, 0] <= 1
+    # 0.9 of the largest value of the products' type in a cell and in its mirror image
+    top = 0.9 * (np.finfo(np.float64).max if prec == lg.LGF_F64 else float(np.finfo(np.float32).max))
+    for cells, want in (([(3, 4, 5, np.inf)], np.inf), ([(0, 0, 0, -np.inf)], -np.inf),
+                        ([(1, 1, 1, np.inf), (6, 2, 0, -np.inf)], np.nan), ([(2, 2, 2, np.nan)], np.nan)):
+        h = f.copy()
+        for z, y, x, v in cells:
+            h[0, z, y, x] = v
+        got, _ = _gpu(ctx, tbl, B, p, src, np.stack([h, f]), src, pair_prec=prec)
+        assert np.max(np.abs(got[1] - clean[0])) < bar * np.max(np.abs(clean[0]))
+        assert np.array_equal(got[0][near], np.full(got[0][near].shape, want), equal_nan=True), cells
+    h = f.copy()
+    h[0, 1, 2, 0] = h[0, 1, 2, 7] = top
+    got, _ = _gpu(ctx, tbl, B, p, src, h, src, pair_prec=prec)
+    ref = fmm.direct_conv(fmm.even_table_kernel(tab), src[:1], h[:1] / top, src[near], B)   # the others: 1e-38 of it
+    assert np.max(np.abs(got[0][near] / top - ref)) < bar * np.max(np.abs(ref))
+
+
 @pytest.mark.parametrize("p", [4, 5, 6])
 def test_fp32_pair_products(ctx, p):
     """M2L and the neighbour sum as FP32 matrix products: within 2e-6 of the

@@ -483,10 +483,18 @@ __global__ void k_zero2d(double *__restrict__ dst, long ldd, int rows, int cols)
 static inline unsigned nblk256(long n) { return (unsigned)((n + 255) / 256); }
 
 // Workspace of the recursion: S, L21 of a level until it is in place, and T, per
-// depth, L21 W11 until the level's W22 is known (null: formed in S only then)
+// depth with chol_early(n1), L21 W11 until the level's W22 is known (at the other
+// depths, and with null T, it is formed in S only then)
 struct CholWs {
     double *S, *T;
 };
+// The early product fills up a launch that is too small by itself, so it gains on
+// the small levels: 11.2 ms without any for a factor of 6600 unknowns, 10.1 with
+// those up to 24 MiB (n1 <= 1773), 10.0 with all; 12,000 34.2 and 33.9 ms with all,
+// 16,000 68.7 and 68.3.  The context keeps the workspace, and all of T would be
+// n^2 / 3 values beside the n^2 / 4 of S; so it is at most 32 MiB.
+constexpr size_t kEarlyMax = (size_t)3 << 20;   // values at one depth
+static bool chol_early(size_t n1) { return n1 * n1 <= kEarlyMax; }
 
 // factor the n x n block at A (lower) into L (in place) and W = L^{-1}
 static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long ldw, CholWs ws, int *bad,
@@ -507,7 +515,8 @@ static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long 
     const int n1 = kLeaf * ((n + 2 * kLeaf - 1) / (2 * kLeaf)), n2 = n - n1;
     const long lds = n1;
     double *A21 = A + (long)n1 * lda, *A22 = A21 + n1, *W21 = W + (long)n1 * ldw, *W22 = W21 + n1;
-    const CholWs inner{ws.S, ws.T ? ws.T + n2 * lds : nullptr};
+    double *early = chol_early(n1) ? ws.T : nullptr;
+    const CholWs inner{ws.S, early ? early + n2 * lds : ws.T};
     if ((rc = chol_rec(ctx, n1, A, lda, W, ldw, inner, bad, st))) return rc;
     {
         ProfScope ps(ctx, "k_gemm_f64", st);
@@ -515,15 +524,15 @@ static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long 
         if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, true, 0.0, ws.S, lds, false, kTriBtLower, st)))
             return rc;
         const unsigned t1 = n1 / 64, t2 = (n2 + 63) / 64;
-        hipLaunchKernelGGL(k_chol_trail, dim3(t2 * (t2 + 1) / 2 + (ws.T ? 2 : 1) * t1 * t2), dim3(256), 0, st, n1, n2,
-                           ws.S, lds, A21, A22, lda, W, ldw, ws.T, lds);
+        hipLaunchKernelGGL(k_chol_trail, dim3(t2 * (t2 + 1) / 2 + (early ? 2 : 1) * t1 * t2), dim3(256), 0, st, n1, n2,
+                           ws.S, lds, A21, A22, lda, W, ldw, early, lds);
         LGF_HIP(hipGetLastError());
     }
     if ((rc = chol_rec(ctx, n2, A22, lda, W22, ldw, inner, bad, st))) return rc;
     {
         ProfScope ps(ctx, "k_gemm_f64", st);
         // W21 = -W22 (L21 W11)
-        const double *T = ws.T;
+        const double *T = early;
         if (!T) {
             if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, false, 0.0, ws.S, lds, false, kTriBLower, st)))
                 return rc;
@@ -543,11 +552,11 @@ int chol_factor_f64(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long 
     for (size_t m = n; m > 2 * kLeaf;) {
         const size_t n1 = kLeaf * ((m + 2 * kLeaf - 1) / (2 * kLeaf));
         if (!ns) ns = (m - n1) * n1;
-        nt += n1 * n1;
+        if (chol_early(n1)) nt += n1 * n1;
         m = n1;
     }
     CholWs ws{nullptr, nullptr};
-    if (ns) {   // without room for T its products are formed level by level
+    if (ns) {   // without room for T its products are formed in S
         if (ctx->dense_ws.reserve((ns + nt) * sizeof(double)) == LGFIB_OK)
             ws.T = ctx->dense_ws.as<double>() + ns;
         else if ((void)hipGetLastError(), (rc = ctx->dense_ws.reserve(ns * sizeof(double))))

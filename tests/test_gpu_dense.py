@@ -72,6 +72,42 @@ def test_solve_matches_oracle_and_allows_aliasing(ctx):
     assert np.array_equal(bd.cpu().numpy(), x.cpu().numpy())
 
 
+@pytest.mark.parametrize("n", [3700, 3841])
+def test_factor_with_late_products_at_the_top(ctx, n):
+    """Sizes whose top level forms L21 W11 late and whose lower levels early,
+    ragged at every level.  L L^T = C to n eps of the largest entry (backward
+    error of Cholesky, with the 4 above), W L = 1 to n eps kappa."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    r = torch.randn((n, n), generator=g, device="cuda", dtype=torch.float64)
+    C = r @ r.T / n
+    C.diagonal().add_(4e-3)   # largest eigenvalue about 4
+    A, W = C.clone(), torch.full_like(C, 7.0)
+    lg.ib_chol_factor(ctx, A, W)
+    L = torch.tril(A)
+    assert float((L @ L.T - C).abs().max()) < 4 * n * EPS * float(C.abs().max())
+    E = W @ L
+    E.diagonal().sub_(1.0)
+    assert float(E.abs().max()) < 4 * n * EPS * 1e3
+    assert not torch.triu(W, 1).any()
+
+
+def test_factor_keeps_a_bounded_workspace(ctx):
+    """What a context holds after a factor: n^2 / 4 values for a panel and, for
+    early products, no more than 32 MiB at any order (64 MiB allowed here)."""
+    n = 8192
+    own = lg.Context(0)
+    C = torch.full((n, n), 0.5, dtype=torch.float64, device="cuda")
+    C.diagonal().fill_(float(n))
+    W = torch.empty_like(C)
+    S = torch.eye(100, dtype=torch.float64, device="cuda")
+    lg.ib_chol_factor(own, S, torch.empty_like(S))   # kernels loaded
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    lg.ib_chol_factor(own, C, W)
+    held = free - torch.cuda.mem_get_info()[0]
+    assert held <= n * n // 4 * 8 + (64 << 20)
+    own.close()
+
 def test_indefinite_matrix_reports_enotspd(ctx):
     n = 70
     C = workloads.spd_matrix(n, 10.0, seed=4)

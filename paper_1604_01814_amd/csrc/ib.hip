@@ -95,12 +95,25 @@ struct IbPlan {
     DevBuf i_ptr, i_col, i_val;
     DevBuf r_ptr, r_col, r_val;
     int64_t nnz = 0;
+    // on the host: the faces that some marker reaches, and the end of each one's
+    // row of R
+    std::vector<int32_t> face, fend;
     // with the gradient folded in (ib_plan_grad, built for force systems):
     // i_low[e]: the cell below entry e's face along its component, -1 outside
     // the blocks
     bool grad = false;
     DevBuf i_low;
     SpreadOp spread;
+    // the same with the cells of a flow on these blocks (ib_flow_create), which
+    // every flow of the plan uses
+    bool flow = false;
+    SpreadOp flow_spread;
+};
+
+// I of a plan on the host, as build_ib_plan leaves it
+struct IbHost {
+    std::vector<int32_t> iptr, icol;
+    std::vector<double> ival;
 };
 
 struct IbKey {
@@ -126,8 +139,10 @@ static IbCache &ib_cache(lgfib_ctx *ctx) {
     return *static_cast<IbCache *>(ctx->ib_cache.get());
 }
 
+// host (nullable) receives I if it is built here, and nothing if the plan is in
+// the cache
 static int build_ib_plan(lgfib_ctx *ctx, int kernel, const double *X, int NL, int B, const int32_t *blocks, int nblk,
-                         std::shared_ptr<IbPlan> &out) {
+                         std::shared_ptr<IbPlan> &out, IbHost *host = nullptr) {
     // cache by exact bytes of (kernel, B, X, blocks)
     std::vector<char> key;
     key.resize(sizeof(int) * 2 + sizeof(double) * 3 * (size_t)NL + sizeof(int32_t) * 3 * (size_t)nblk);
@@ -208,10 +223,16 @@ static int build_ib_plan(lgfib_ctx *ctx, int kernel, const double *X, int NL, in
             long long l[3];
             int cnt[3];
             double w[3][8];
+            long long bq[3][8];   // block and place in it of the support's cells, by axis
+            int at[3][8];
             for (int a = 0; a < 3; ++a) {
                 const double c = (a == k) ? 0.0 : 0.5;
                 support_range(kernel, X[3 * i + a], c, &l[a], &cnt[a]);
-                for (int q = 0; q < cnt[a]; ++q) w[a][q] = phi_k(kernel, (double)(l[a] + q) + c - X[3 * i + a]);
+                for (int q = 0; q < cnt[a]; ++q) {
+                    w[a][q] = phi_k(kernel, (double)(l[a] + q) + c - X[3 * i + a]);
+                    bq[a][q] = floordiv(l[a] + q, B);
+                    at[a][q] = (int)(l[a] + q - bq[a][q] * B);
+                }
             }
             for (int dz = 0; dz < cnt[2]; ++dz) {
                 if (w[2][dz] == 0.0) continue;
@@ -219,13 +240,11 @@ static int build_ib_plan(lgfib_ctx *ctx, int kernel, const double *X, int NL, in
                     if (w[1][dy] == 0.0) continue;
                     for (int dxx = 0; dxx < cnt[0]; ++dxx) {
                         if (w[0][dxx] == 0.0) continue;
-                        const long long n[3] = {l[0] + dxx, l[1] + dy, l[2] + dz};
-                        const long long bq[3] = {floordiv(n[0], B), floordiv(n[1], B), floordiv(n[2], B)};
-                        const int slot = slot_of(bq[0], bq[1], bq[2]);
+                        const int slot = slot_of(bq[0][dxx], bq[1][dy], bq[2][dz]);
                         if (slot < 0)
                             return fail(LGFIB_ESUPPORT, "support of marker " + std::to_string(i) +
                                                             " leaves the block set");
-                        const long long loc = ((n[2] - bq[2] * B) * B + (n[1] - bq[1] * B)) * B + (n[0] - bq[0] * B);
+                        const int loc = (at[2][dz] * B + at[1][dy]) * B + at[0][dxx];
                         icol.push_back((int32_t)(((long long)k * nblk + slot) * B3 + loc));
                         ival.push_back(w[2][dz] * w[1][dy] * w[0][dxx]);
                     }
@@ -239,7 +258,12 @@ static int build_ib_plan(lgfib_ctx *ctx, int kernel, const double *X, int NL, in
     std::vector<int32_t> rptr((size_t)nfaces + 1, 0), rcol(std::max<size_t>(nnz, 1));
     std::vector<double> rval(std::max<size_t>(nnz, 1));
     for (size_t e = 0; e < nnz; ++e) rptr[(size_t)icol[e] + 1]++;
-    for (int64_t f = 0; f < nfaces; ++f) rptr[f + 1] += rptr[f];
+    for (int64_t f = 0; f < nfaces; ++f) {
+        if (rptr[f + 1] > 0) plan->face.push_back((int32_t)f);
+        rptr[f + 1] += rptr[f];
+    }
+    plan->fend.reserve(plan->face.size());
+    for (int32_t f : plan->face) plan->fend.push_back(rptr[f + 1]);
     {
         std::vector<int32_t> fill(rptr.begin(), rptr.end() - 1);
         for (int64_t row = 0; row < 3ll * NL; ++row)
@@ -270,6 +294,7 @@ static int build_ib_plan(lgfib_ctx *ctx, int kernel, const double *X, int NL, in
     LGF_HIP(hipMemcpy(plan->r_ptr.p, rptr.data(), 4 * rptr.size(), hipMemcpyHostToDevice));
     LGF_HIP(hipMemcpy(plan->r_col.p, rcol.data(), 4 * rcol.size(), hipMemcpyHostToDevice));
     LGF_HIP(hipMemcpy(plan->r_val.p, rval.data(), 8 * rval.size(), hipMemcpyHostToDevice));
+    if (host) *host = IbHost{std::move(iptr), std::move(icol), std::move(ival)};
     out = plan;
     cache.keys[h] = std::move(key);
     cache.plans[h] = CacheEnt<IbPlan>{std::move(plan), ++ctx->cache_tick};
@@ -288,81 +313,85 @@ struct CellSet {
     }
 };
 
+static int log2_edge(int B) { return B == 4 ? 2 : B == 8 ? 3 : 4; }   // force systems have B in {4, 8, 16}
+
 // The spread operator of plan p with its cells numbered on the set cs (which
-// holds p's blocks).  c = G^T u has face (n, k) add to c(n) and subtract from
-// c(n - e_k), so G^T R has two entries for each one of R, one where the cell
-// below lies outside cs.  low (nullable) receives that cell per entry of I.
-static int build_spread(const IbPlan &p, const CellSet &cs, int64_t ncell, SpreadOp &op, std::vector<int32_t> *low_out) {
-    const int B = p.B, B3 = B * B * B;
+// holds p's blocks, in order in `blocks`).  c = G^T u has face (n, k) add to c(n)
+// and subtract from c(n - e_k), so G^T R has two entries for each one of R, one
+// where the cell below lies outside cs.  low (nullable) receives that cell per
+// entry of I.  h: the plan's I, read back from the device if empty.
+static int build_spread(const IbPlan &p, const int32_t *blocks, const CellSet &cs, int64_t ncell, IbHost &h,
+                        SpreadOp &op, std::vector<int32_t> *low_out) {
+    const int lb = log2_edge(p.B), B = p.B, B3 = B * B * B;
     const int64_t nc = (int64_t)p.nblk * B3, nrows = 3ll * p.NL;
     const size_t nnz = (size_t)p.nnz;
     if (ncell + 3 * nc > INT32_MAX - 1 || 3 * (int64_t)nnz > INT32_MAX - 1)
         return fail(LGFIB_ERANGE, "IB operator too large");
-    std::vector<int32_t> iptr(nrows + 1), icol(std::max<size_t>(nnz, 1)), own(std::max<size_t>(nnz, 1)),
-        low(std::max<size_t>(nnz, 1), -1), blk(3 * (size_t)p.nblk), rptr(3 * nc + 1), dptr(ncell + 1, 0);
-    std::vector<double> ival(std::max<size_t>(nnz, 1));
-    LGF_HIP(hipMemcpy(iptr.data(), p.i_ptr.p, 4 * iptr.size(), hipMemcpyDeviceToHost));
-    LGF_HIP(hipMemcpy(icol.data(), p.i_col.p, 4 * icol.size(), hipMemcpyDeviceToHost));
-    LGF_HIP(hipMemcpy(ival.data(), p.i_val.p, 8 * ival.size(), hipMemcpyDeviceToHost));
-    LGF_HIP(hipMemcpy(rptr.data(), p.r_ptr.p, 4 * rptr.size(), hipMemcpyDeviceToHost));
-    if (p.nblk) LGF_HIP(hipMemcpy(blk.data(), p.blocks.p, 4 * blk.size(), hipMemcpyDeviceToHost));
-    const int step[3] = {1, B, B * B};
+    if (h.iptr.empty()) {
+        h.iptr.resize(nrows + 1);
+        h.icol.resize(std::max<size_t>(nnz, 1));
+        h.ival.resize(h.icol.size());
+        LGF_HIP(hipMemcpy(h.iptr.data(), p.i_ptr.p, 4 * h.iptr.size(), hipMemcpyDeviceToHost));
+        LGF_HIP(hipMemcpy(h.icol.data(), p.i_col.p, 4 * h.icol.size(), hipMemcpyDeviceToHost));
+        LGF_HIP(hipMemcpy(h.ival.data(), p.i_val.p, 8 * h.ival.size(), hipMemcpyDeviceToHost));
+    }
+    // slots on cs of each block and its lower neighbours
+    std::vector<std::array<int32_t, 4>> slot((size_t)p.nblk);
+    for (int i = 0; i < p.nblk; ++i) {
+        const int32_t *q = blocks + 3 * (size_t)i;
+        slot[i] = {cs.slot(q[0], q[1], q[2]), cs.slot(q[0] - 1, q[1], q[2]), cs.slot(q[0], q[1] - 1, q[2]),
+                   cs.slot(q[0], q[1], q[2] - 1)};
+    }
+    std::vector<int32_t> own(std::max<size_t>(nnz, 1)), low(std::max<size_t>(nnz, 1), -1), dptr(ncell + 1, 0);
     for (int64_t row = 0; row < nrows; ++row) {
-        const int k = (int)(row % 3);
-        for (int32_t e = iptr[row]; e < iptr[row + 1]; ++e) {
-            const int64_t cell = icol[e] - k * nc;
-            const int loc = (int)(cell % B3);
-            const int32_t *q = &blk[3 * (cell / B3)];
-            own[e] = cs.slot(q[0], q[1], q[2]) * B3 + loc;
-            if (loc / step[k] % B > 0) {
-                low[e] = own[e] - step[k];
-            } else {
-                const int sb = cs.slot(q[0] - (k == 0), q[1] - (k == 1), q[2] - (k == 2));
-                if (sb >= 0) low[e] = sb * B3 + loc + (B - 1) * step[k];
-            }
+        const int k = (int)(row % 3), sh = k * lb, m = B - 1;
+        for (int32_t e = h.iptr[row]; e < h.iptr[row + 1]; ++e) {
+            const int32_t cell = (int32_t)(h.icol[e] - k * nc), loc = cell & (B3 - 1);
+            const auto &sl = slot[cell >> (3 * lb)];
+            own[e] = sl[0] * B3 + loc;
+            if (loc >> sh & m) low[e] = own[e] - (1 << sh);
+            else if (sl[1 + k] >= 0) low[e] = sl[1 + k] * B3 + loc + (m << sh);
             dptr[own[e] + 1]++;
             if (low[e] >= 0) dptr[low[e] + 1]++;
         }
     }
-    for (int64_t c = 0; c < ncell; ++c) dptr[c + 1] += dptr[c];
-    std::vector<int32_t> col(std::max<size_t>(nnz + dptr[ncell], 1)), fill(dptr.begin(), dptr.end() - 1);
-    std::vector<double> val(col.size());
-    if (nnz) {
-        LGF_HIP(hipMemcpy(col.data(), p.r_col.p, 4 * nnz, hipMemcpyDeviceToHost));
-        LGF_HIP(hipMemcpy(val.data(), p.r_val.p, 8 * nnz, hipMemcpyDeviceToHost));
+    std::vector<int32_t> srow(p.face), sptr;
+    sptr.reserve(2 * srow.size() + 1);
+    sptr.push_back(0);
+    sptr.insert(sptr.end(), p.fend.begin(), p.fend.end());
+    op.nfr = (int)srow.size();
+    for (int64_t c = 0; c < ncell; ++c) {
+        const bool any = dptr[c + 1] > 0;
+        dptr[c + 1] += dptr[c];
+        if (any) {
+            srow.push_back((int32_t)(3 * nc + c));
+            sptr.push_back((int32_t)nnz + dptr[c + 1]);
+        }
     }
-    auto put = [&](int32_t cell, int64_t row, double w) {
-        const size_t q = nnz + fill[cell]++;
+    op.nrows = (int)srow.size();
+    std::vector<int32_t> col(std::max<size_t>(dptr[ncell], 1));   // the cells' rows; the faces' are R's
+    std::vector<double> val(col.size());
+    auto put = [&](int32_t cell, int64_t row, double w) {   // dptr[cell]: the next place of the cell
+        const size_t q = dptr[cell]++;
         col[q] = (int32_t)row;
         val[q] = w;
     };
     for (int64_t row = 0; row < nrows; ++row)
-        for (int32_t e = iptr[row]; e < iptr[row + 1]; ++e) {
-            put(own[e], row, ival[e]);
-            if (low[e] >= 0) put(low[e], row, -ival[e]);
+        for (int32_t e = h.iptr[row]; e < h.iptr[row + 1]; ++e) {
+            put(own[e], row, h.ival[e]);
+            if (low[e] >= 0) put(low[e], row, -h.ival[e]);
         }
-    std::vector<int32_t> srow, sptr(1, 0);
-    for (int64_t f = 0; f < 3 * nc; ++f)
-        if (rptr[f + 1] > rptr[f]) {
-            srow.push_back((int32_t)f);
-            sptr.push_back(rptr[f + 1]);
-        }
-    op.nfr = (int)srow.size();
-    for (int64_t c = 0; c < ncell; ++c)
-        if (dptr[c + 1] > dptr[c]) {
-            srow.push_back((int32_t)(3 * nc + c));
-            sptr.push_back((int32_t)nnz + dptr[c + 1]);
-        }
-    op.nrows = (int)srow.size();
     srow.resize(std::max<size_t>(srow.size(), 1));
     int rc;
     if ((rc = op.row.reserve(4 * srow.size())) || (rc = op.ptr.reserve(4 * sptr.size())) ||
-        (rc = op.col.reserve(4 * col.size())) || (rc = op.val.reserve(8 * val.size())))
+        (rc = op.col.reserve(4 * (nnz + col.size()))) || (rc = op.val.reserve(8 * (nnz + val.size()))))
         return rc;
     LGF_HIP(hipMemcpy(op.row.p, srow.data(), 4 * srow.size(), hipMemcpyHostToDevice));
     LGF_HIP(hipMemcpy(op.ptr.p, sptr.data(), 4 * sptr.size(), hipMemcpyHostToDevice));
-    LGF_HIP(hipMemcpy(op.col.p, col.data(), 4 * col.size(), hipMemcpyHostToDevice));
-    LGF_HIP(hipMemcpy(op.val.p, val.data(), 8 * val.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(op.col.p, p.r_col.p, 4 * nnz, hipMemcpyDeviceToDevice));
+    LGF_HIP(hipMemcpy(op.val.p, p.r_val.p, 8 * nnz, hipMemcpyDeviceToDevice));
+    LGF_HIP(hipMemcpy(op.col.as<int>() + nnz, col.data(), 4 * col.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(op.val.as<double>() + nnz, val.data(), 8 * val.size(), hipMemcpyHostToDevice));
     if (low_out) *low_out = std::move(low);
     return LGFIB_OK;
 }
@@ -370,12 +399,14 @@ static int build_spread(const IbPlan &p, const CellSet &cs, int64_t ncell, Sprea
 // The operators of the force Schur complement with the staggered gradient
 // folded in: the spread operator on the plan's own blocks, and for (G d)^(k)(n)
 // = d(n) - d(n - e_k) the cell below each entry of I.
-static int ib_plan_grad(IbPlan &p) {
+static int ib_plan_grad(IbPlan &p, const int32_t *blocks, IbHost &h) {
     if (p.grad) return LGFIB_OK;
-    std::vector<int32_t> map((size_t)p.nb[0] * p.nb[1] * p.nb[2]), low;
-    LGF_HIP(hipMemcpy(map.data(), p.map.p, 4 * map.size(), hipMemcpyDeviceToHost));
+    std::vector<int32_t> map((size_t)p.nb[0] * p.nb[1] * p.nb[2], -1), low;
+    for (int i = 0; i < p.nblk; ++i)
+        map[((size_t)(blocks[3 * i + 2] - p.lo[2]) * p.nb[1] + (blocks[3 * i + 1] - p.lo[1])) * p.nb[0] +
+            (blocks[3 * i] - p.lo[0])] = i;
     int rc;
-    if ((rc = build_spread(p, CellSet{p.lo, p.nb, map}, (int64_t)p.nblk * p.B * p.B * p.B, p.spread, &low)) ||
+    if ((rc = build_spread(p, blocks, CellSet{p.lo, p.nb, map}, (int64_t)p.nblk * p.B * p.B * p.B, h, p.spread, &low)) ||
         (rc = p.i_low.reserve(4 * low.size())))
         return rc;
     LGF_HIP(hipMemcpy(p.i_low.p, low.data(), 4 * low.size(), hipMemcpyHostToDevice));
@@ -846,8 +877,9 @@ extern "C" int ib_system_create(lgfib_ctx *ctx, int kernel, const double *X, int
     s->a = a;
     s->X.assign(X, X + 3 * (size_t)NL);
     s->blocks.assign(blocks, blocks + 3 * (size_t)nblk);
-    if ((rc = build_ib_plan(ctx, kernel, X, NL, B, blocks, nblk, s->plan))) return rc;
-    if ((rc = ib_plan_grad(*s->plan))) return rc;
+    IbHost host;
+    if ((rc = build_ib_plan(ctx, kernel, X, NL, B, blocks, nblk, s->plan, &host))) return rc;
+    if ((rc = ib_plan_grad(*s->plan, blocks, host))) return rc;
     int ext[3];
     for (int q = 0; q < 3; ++q) ext[q] = s->plan->nb[q] * B - 1;
     if ((rc = lgf_table_build(ctx, LGF_KIND_K, a, ext, nullptr, &s->tbl))) return rc;
@@ -1366,9 +1398,8 @@ struct ib_flow {
     DevBuf cmap, cblk;              // block map of the cell blocks
     lgf_table_t tbl = -1;           // G_L over the cell span
     DevBuf c, dstar, w, h, rhs;
-    // R f on the faces and G^T R f on the cells, written by the spread operator
-    // alone (zeros where no marker reaches)
-    SpreadOp spread;
+    // R f on the faces and G^T R f on the cells, written by the plan's
+    // flow_spread alone (zeros where no marker reaches)
     DevBuf rf, cf;
 };
 
@@ -1493,7 +1524,8 @@ extern "C" int ib_flow_create(lgfib_ctx *ctx, ib_system *sys, const int32_t *flo
     f->B = sys->B;
     f->nflow = nflow;
     f->blocks.assign(flow_blocks, flow_blocks + 3 * (size_t)nflow);
-    if ((rc = build_ib_plan(ctx, sys->kernel, sys->X.data(), sys->NL, sys->B, flow_blocks, nflow, f->plan)))
+    IbHost host;
+    if ((rc = build_ib_plan(ctx, sys->kernel, sys->X.data(), sys->NL, sys->B, flow_blocks, nflow, f->plan, &host)))
         return rc;
     // cell blocks: the flow blocks and their lower neighbours, sorted (z, y, x)
     {
@@ -1535,9 +1567,11 @@ extern "C" int ib_flow_create(lgfib_ctx *ctx, ib_system *sys, const int32_t *flo
         if ((rc = f->cmap.reserve(map.size() * 4)) || (rc = f->cblk.reserve(f->cblocks.size() * 4))) return rc;
         LGF_HIP(hipMemcpy(f->cmap.p, map.data(), map.size() * 4, hipMemcpyHostToDevice));
         LGF_HIP(hipMemcpy(f->cblk.p, f->cblocks.data(), f->cblocks.size() * 4, hipMemcpyHostToDevice));
-        if ((rc = build_spread(*f->plan, CellSet{f->clo, f->cnb, map}, (int64_t)f->ncell * f->B * f->B * f->B, f->spread,
-                               nullptr)))
+        IbPlan &p = *f->plan;   // its blocks determine the cells
+        if (!p.flow && (rc = build_spread(p, flow_blocks, CellSet{f->clo, f->cnb, map},
+                                          (int64_t)f->ncell * f->B * f->B * f->B, host, p.flow_spread, nullptr)))
             return rc;
+        p.flow = true;
     }
     int ext[3];
     for (int q = 0; q < 3; ++q) ext[q] = f->cnb[q] * sys->B - 1;
@@ -1570,7 +1604,7 @@ static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, const double *u, double *u_ou
                       const double *g, double *qlam, hipStream_t st) {
     ib_system *sys = fl->sys;
     const IbPlan &P = *fl->plan;
-    const int B = fl->B, lb = B == 4 ? 2 : B == 8 ? 3 : 4;   // force systems have B in {4, 8, 16}
+    const int B = fl->B, lb = log2_edge(B);
     const size_t B3 = (size_t)B * B * B;
     const size_t nfc = (size_t)fl->nflow * B3, nf = 3 * nfc, ncc = (size_t)fl->ncell * B3, nl = 3 * (size_t)sys->NL;
     double *c = fl->c.as<double>(), *d = fl->dstar.as<double>(), *rf = fl->rf.as<double>();
@@ -1605,7 +1639,7 @@ static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, const double *u, double *u_ou
     if (rc && rc != LGFIB_ENOCONV) return rc;
     const int solve_rc = rc;
     // (pc) d = d* + L^{-1} G^T R f
-    if ((rc = launch_spread<double, double>(ctx, fl->spread, f, nullptr, rf, fl->cf.as<double>(), (int)nf, st))) return rc;
+    if ((rc = launch_spread<double, double>(ctx, P.flow_spread, f, nullptr, rf, fl->cf.as<double>(), (int)nf, st))) return rc;
     if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, fl->cf.p, d, 1, (lgfib_stream_t)st)))
         return rc;
     // (vc) u' = E(a)[u - G d - R f]

@@ -364,3 +364,45 @@ def test_force_solve_at_the_rounding_of_its_matvec(ctx, prec):
     r = b - sum(matvec(s * f) / s for s in np.linspace(0.37, 0.93, 100)) / 100
     assert float(r.norm()) <= (0.6 + 1 / 8 + 1 / 10) * eta
     sys.close()
+
+
+def test_flows_of_one_block_set_share_their_operators(ctx, small_sphere):
+    """Flows on the same blocks (different a, one made after another was
+    destroyed, one after the caches were released) take the steps
+    that a context of their own takes, bit for bit."""
+    X, B, alpha, blocks, origin, mask, gk, C = small_sphere
+    flow = np.array([(x, y, z) for z in range(3) for y in range(3) for x in range(3)], dtype=np.int32)
+    g = torch.Generator(device="cuda").manual_seed(21)
+    u0 = torch.randn((3, len(flow), B, B, B), dtype=torch.float64, device="cuda", generator=g)
+    ub = torch.zeros(X.shape, dtype=torch.float64, device="cuda")
+
+    def step(c, fl):
+        u, f = u0.clone(), torch.zeros_like(ub)
+        assert lg.ib_flow_step(c, fl, u, ub, f, rtol=1e-11, maxit=2000, prec=lg.LGF_F64)["converged"]
+        return u, f
+
+    def make(c, a):
+        s = lg.ib_system_create(c, lg.IB_ROMA3, X, B, blocks, a)
+        return s, lg.ib_flow_create(c, s, flow)
+
+    ref = []
+    for a in (alpha, 2 * alpha):
+        own = lg.Context(0)
+        s, fl = make(own, a)
+        ref.append(step(own, fl))
+        fl.close()
+        s.close()
+        own.close()
+    (s1, f1), (s2, f2) = make(ctx, alpha), make(ctx, 2 * alpha)
+    got = [step(ctx, f1), step(ctx, f2), step(ctx, f1)]
+    f1.close()
+    got.append(step(ctx, f2))
+    f3 = lg.ib_flow_create(ctx, s1, flow)
+    got.append(step(ctx, f3))
+    lg.lgfib_cache_release(ctx)
+    f4 = lg.ib_flow_create(ctx, s2, flow)
+    got += [step(ctx, f3), step(ctx, f4)]
+    for (u, f), r in zip(got, (0, 1, 0, 1, 0, 0, 1)):
+        assert torch.equal(u, ref[r][0]) and torch.equal(f, ref[r][1])
+    for h in (f2, f3, f4, s1, s2):
+        h.close()

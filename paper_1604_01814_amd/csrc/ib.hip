@@ -78,8 +78,8 @@ static inline void support_range(int kernel, double X, double c, long long *lo, 
 }
 
 // R and G^T R as one sparse operator on marker vectors: the rows are the nfr
-// faces and then the cells that some marker reaches; row[q] is row q's face, or
-// the number of faces plus its cell.
+// faces and then the cells that some marker reaches; row[q] is row q's face or
+// cell.  Up to three entries for each one of I, so ptr holds 64 bits.
 struct SpreadOp {
     int nfr = 0, nrows = 0;
     DevBuf row, ptr, col, val;
@@ -325,8 +325,7 @@ static int build_spread(const IbPlan &p, const int32_t *blocks, const CellSet &c
     const int lb = log2_edge(p.B), B = p.B, B3 = B * B * B;
     const int64_t nc = (int64_t)p.nblk * B3, nrows = 3ll * p.NL;
     const size_t nnz = (size_t)p.nnz;
-    if (ncell + 3 * nc > INT32_MAX - 1 || 3 * (int64_t)nnz > INT32_MAX - 1)
-        return fail(LGFIB_ERANGE, "IB operator too large");
+    if (ncell > INT32_MAX - 1) return fail(LGFIB_ERANGE, "IB operator too large");
     if (h.iptr.empty()) {
         h.iptr.resize(nrows + 1);
         h.icol.resize(std::max<size_t>(nnz, 1));
@@ -342,7 +341,8 @@ static int build_spread(const IbPlan &p, const int32_t *blocks, const CellSet &c
         slot[i] = {cs.slot(q[0], q[1], q[2]), cs.slot(q[0] - 1, q[1], q[2]), cs.slot(q[0], q[1] - 1, q[2]),
                    cs.slot(q[0], q[1], q[2] - 1)};
     }
-    std::vector<int32_t> own(std::max<size_t>(nnz, 1)), low(std::max<size_t>(nnz, 1), -1), dptr(ncell + 1, 0);
+    std::vector<int32_t> own(std::max<size_t>(nnz, 1)), low(std::max<size_t>(nnz, 1), -1);
+    std::vector<int64_t> dptr(ncell + 1, 0);
     for (int64_t row = 0; row < nrows; ++row) {
         const int k = (int)(row % 3), sh = k * lb, m = B - 1;
         for (int32_t e = h.iptr[row]; e < h.iptr[row + 1]; ++e) {
@@ -355,7 +355,8 @@ static int build_spread(const IbPlan &p, const int32_t *blocks, const CellSet &c
             if (low[e] >= 0) dptr[low[e] + 1]++;
         }
     }
-    std::vector<int32_t> srow(p.face), sptr;
+    std::vector<int32_t> srow(p.face);
+    std::vector<int64_t> sptr;
     sptr.reserve(2 * srow.size() + 1);
     sptr.push_back(0);
     sptr.insert(sptr.end(), p.fend.begin(), p.fend.end());
@@ -364,8 +365,8 @@ static int build_spread(const IbPlan &p, const int32_t *blocks, const CellSet &c
         const bool any = dptr[c + 1] > 0;
         dptr[c + 1] += dptr[c];
         if (any) {
-            srow.push_back((int32_t)(3 * nc + c));
-            sptr.push_back((int32_t)nnz + dptr[c + 1]);
+            srow.push_back((int32_t)c);
+            sptr.push_back((int64_t)nnz + dptr[c + 1]);
         }
     }
     op.nrows = (int)srow.size();
@@ -383,11 +384,11 @@ static int build_spread(const IbPlan &p, const int32_t *blocks, const CellSet &c
         }
     srow.resize(std::max<size_t>(srow.size(), 1));
     int rc;
-    if ((rc = op.row.reserve(4 * srow.size())) || (rc = op.ptr.reserve(4 * sptr.size())) ||
+    if ((rc = op.row.reserve(4 * srow.size())) || (rc = op.ptr.reserve(8 * sptr.size())) ||
         (rc = op.col.reserve(4 * (nnz + col.size()))) || (rc = op.val.reserve(8 * (nnz + val.size()))))
         return rc;
     LGF_HIP(hipMemcpy(op.row.p, srow.data(), 4 * srow.size(), hipMemcpyHostToDevice));
-    LGF_HIP(hipMemcpy(op.ptr.p, sptr.data(), 4 * sptr.size(), hipMemcpyHostToDevice));
+    LGF_HIP(hipMemcpy(op.ptr.p, sptr.data(), 8 * sptr.size(), hipMemcpyHostToDevice));
     LGF_HIP(hipMemcpy(op.col.p, p.r_col.p, 4 * nnz, hipMemcpyDeviceToDevice));
     LGF_HIP(hipMemcpy(op.val.p, p.r_val.p, 8 * nnz, hipMemcpyDeviceToDevice));
     LGF_HIP(hipMemcpy(op.col.as<int>() + nnz, col.data(), 4 * col.size(), hipMemcpyHostToDevice));
@@ -536,24 +537,24 @@ struct CgDir {
 // as R r + beta R p_old so that beta's sums are off the gathers' path, and
 // stored for the update.
 template <bool DIR, typename In, typename Out>
-__global__ __launch_bounds__(256) void k_spread(const int *__restrict__ ptr, const int *__restrict__ col,
+__global__ __launch_bounds__(256) void k_spread(const long *__restrict__ ptr, const int *__restrict__ col,
                                                 const double *__restrict__ val, const int *__restrict__ out,
                                                 const In *__restrict__ x, CgDir dir, Out *__restrict__ faces,
-                                                Out *__restrict__ c, int nrows, int nf) {
+                                                Out *__restrict__ c, int nrows, int nfr) {
     constexpr int L = 8;
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    const int row = t / L, lane = t % L;
+    const long t = (long)blockIdx.x * 256 + threadIdx.x;
+    const int row = (int)(t / L), lane = threadIdx.x % L;
     const bool live = row < nrows;
     double acc = 0.0, old = 0.0, rs = 0.0, ro = 0.0, r0 = 0.0, p0 = 0.0;
     if constexpr (DIR) {   // these loads run ahead of the gathers
         rs = part_lane(dir.rs, dir.nred);
         ro = part_lane(dir.rs_old, dir.nred);
-        r0 = dir.r[min(t, dir.n - 1)];
-        p0 = dir.p_old[min(t, dir.n - 1)];
+        r0 = dir.r[min(t, (long)dir.n - 1)];
+        p0 = dir.p_old[min(t, (long)dir.n - 1)];
     }
     if (live) {
-        const int e1 = ptr[row + 1];
-        for (int e = ptr[row] + lane; e < e1; e += L) {
+        const long e1 = ptr[row + 1];
+        for (long e = ptr[row] + lane; e < e1; e += L) {
             const int j = col[e];
             const double w = val[e];
             if constexpr (DIR) {
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(256) void k_spread(const int *__restrict__ ptr, con
         ro = wave_sum(ro);
         const double beta = ro > 0.0 ? rs / ro : 0.0;
         if (t < dir.n) dir.p[t] = beta == 0.0 ? r0 : r0 + beta * p0;
-        for (int i = t + gridDim.x * 256; i < dir.n; i += gridDim.x * 256)
+        for (long i = t + gridDim.x * 256l; i < dir.n; i += gridDim.x * 256l)
             dir.p[i] = beta == 0.0 ? dir.r[i] : dir.r[i] + beta * dir.p_old[i];
         if (beta != 0.0) acc += beta * old;
     }
@@ -577,8 +578,8 @@ __global__ __launch_bounds__(256) void k_spread(const int *__restrict__ ptr, con
     for (int m = L / 2; m > 0; m >>= 1) acc += __shfl_xor(acc, m, L);
     if (live && lane == 0) {
         const int o = out[row];
-        if (o < nf) faces[o] = (Out)acc;
-        else c[o - nf] = (Out)acc;
+        if (row < nfr) faces[o] = (Out)acc;
+        else c[o] = (Out)acc;
     }
 }
 
@@ -660,19 +661,19 @@ static int launch_interpolate(lgfib_ctx *ctx, const IbPlan &p, const In *faces, 
     return LGFIB_OK;
 }
 
-// faces = R x, c = G^T R x (faces and c hold zeros where no marker reaches; nf
-// the number of faces); dir: the CG's direction
+// faces = R x, c = G^T R x (faces and c hold zeros where no marker reaches);
+// dir: the CG's direction
 template <typename In, typename Out>
-static int launch_spread(lgfib_ctx *ctx, const SpreadOp &op, const In *x, const CgDir *dir, Out *faces, Out *c, int nf,
+static int launch_spread(lgfib_ctx *ctx, const SpreadOp &op, const In *x, const CgDir *dir, Out *faces, Out *c,
                          hipStream_t st) {
     ProfScope ps(ctx, "k_spread", st);
     const dim3 grid(std::max(1u, nblocks(8 * (size_t)op.nrows, 256)));
     if (dir)
-        hipLaunchKernelGGL((k_spread<true, In, Out>), grid, dim3(256), 0, st, op.ptr.as<int>(), op.col.as<int>(),
-                           op.val.as<double>(), op.row.as<int>(), x, *dir, faces, c, op.nrows, nf);
+        hipLaunchKernelGGL((k_spread<true, In, Out>), grid, dim3(256), 0, st, op.ptr.as<long>(), op.col.as<int>(),
+                           op.val.as<double>(), op.row.as<int>(), x, *dir, faces, c, op.nrows, op.nfr);
     else
-        hipLaunchKernelGGL((k_spread<false, In, Out>), grid, dim3(256), 0, st, op.ptr.as<int>(), op.col.as<int>(),
-                           op.val.as<double>(), op.row.as<int>(), x, CgDir{}, faces, c, op.nrows, nf);
+        hipLaunchKernelGGL((k_spread<false, In, Out>), grid, dim3(256), 0, st, op.ptr.as<long>(), op.col.as<int>(),
+                           op.val.as<double>(), op.row.as<int>(), x, CgDir{}, faces, c, op.nrows, op.nfr);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
 }
@@ -845,7 +846,7 @@ static int schur_apply_t(ib_system *s, const VIn *x, VOut *y, hipStream_t st, co
     const int prec = pi ? LGF_F64 : LGF_F32;
     Real *g = s->g[pi].as<Real>(), *af = s->af[pi].as<Real>(), *c = s->c[pi].as<Real>(), *d = s->d[pi].as<Real>();
     int rc;
-    if ((rc = launch_spread<VIn, Real>(ctx, s->plan->spread, x, dir, g, c, 3 * s->nblk * s->B * s->B * s->B, st))) return rc;
+    if ((rc = launch_spread<VIn, Real>(ctx, s->plan->spread, x, dir, g, c, st))) return rc;
     if ((rc = lgf_if_apply(ctx, s->a, s->B, s->blocks.data(), s->nblk, s->blocks.data(), s->nblk, 3, prec, g, af,
                            (lgfib_stream_t)st)))
         return rc;
@@ -1639,7 +1640,7 @@ static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, const double *u, double *u_ou
     if (rc && rc != LGFIB_ENOCONV) return rc;
     const int solve_rc = rc;
     // (pc) d = d* + L^{-1} G^T R f
-    if ((rc = launch_spread<double, double>(ctx, P.flow_spread, f, nullptr, rf, fl->cf.as<double>(), (int)nf, st))) return rc;
+    if ((rc = launch_spread<double, double>(ctx, P.flow_spread, f, nullptr, rf, fl->cf.as<double>(), st))) return rc;
     if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, fl->cf.p, d, 1, (lgfib_stream_t)st)))
         return rc;
     // (vc) u' = E(a)[u - G d - R f]
@@ -1681,8 +1682,7 @@ static int schur_dense_cols(ib_system *s, int j0, int K, double *C, long ld, hip
     for (int k = 0; k < K; ++k) {
         hipLaunchKernelGGL(k_unit, dim3(nblocks(n, 256)), dim3(256), 0, st, e + (size_t)k * n, n, j0 + k);
         LGF_HIP(hipGetLastError());
-        if ((rc = launch_spread<double, double>(ctx, P.spread, e + (size_t)k * n, nullptr, g + k * nf, c + k * nc,
-                                                (int)nf, st)))
+        if ((rc = launch_spread<double, double>(ctx, P.spread, e + (size_t)k * n, nullptr, g + k * nf, c + k * nc, st)))
             return rc;
     }
     for (int c0 = 0; c0 < 3 * K; c0 += 8) {

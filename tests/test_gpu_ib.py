@@ -406,3 +406,25 @@ def test_flows_of_one_block_set_share_their_operators(ctx, small_sphere):
         assert torch.equal(u, ref[r][0]) and torch.equal(f, ref[r][1])
     for h in (f2, f3, f4, s1, s2):
         h.close()
+
+
+@pytest.mark.parametrize("prec", [lg.LGF_F64, lg.LGF_F32])
+@pytest.mark.parametrize("NL,diameter,rtol", [
+    (4000, 0.0, 1e-4),       # all in one cell: far more unknowns than faces and cells they reach
+    (22000, 100.0, 1e-3)])   # more unknowns than one workgroup's sums take (65,536)
+def test_force_solve_of_many_markers(ctx, NL, diameter, rtol, prec):
+    """The CG's direction where the spread's rows do not cover the unknowns, its
+    updates with several elements a thread and its sums over 256 workgroups:
+    velocities in the operator's range (it is singular where thousands of
+    markers share a cell), judged by an FP64 matvec of the library."""
+    B, g = 8, np.random.Generator(np.random.PCG64(31))
+    X = g.uniform(12.1, 12.9, (NL, 3)) if not diameter else workloads.sphere_markers(diameter, NL, (80.4, 80.2, 80.1))
+    sys = lg.ib_system_create(ctx, lg.IB_ROMA3, X, B, lg.ib_body_blocks(lg.IB_ROMA3, X, B), 0.05)
+    x = torch.from_numpy(g.standard_normal((NL, 3))).cuda()
+    b, y, f = torch.zeros_like(x), torch.zeros_like(x), torch.zeros_like(x)
+    lg.ib_schur_apply(ctx, sys, x, b)
+    st = lg.ib_force_solve(ctx, sys, b, f, rtol=rtol, maxit=4000, prec=prec)
+    assert st["converged"] and st["rel_residual"] <= rtol
+    lg.ib_schur_apply(ctx, sys, f, y)
+    assert float((b - y).norm()) <= 1.01 * rtol * float(b.norm())
+    sys.close()

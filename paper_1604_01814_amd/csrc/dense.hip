@@ -559,7 +559,7 @@ int chol_factor_f64(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long 
     if (ns) {   // without room for T its products are formed in S
         if (ctx->dense_ws.reserve((ns + nt) * sizeof(double)) == LGFIB_OK)
             ws.T = ctx->dense_ws.as<double>() + ns;
-        else if ((void)hipGetLastError(), (rc = ctx->dense_ws.reserve(ns * sizeof(double))))
+        else if ((rc = ctx->dense_ws.reserve(ns * sizeof(double))))
             return rc;
         ws.S = ctx->dense_ws.as<double>();
     }

@@ -44,6 +44,7 @@ struct DevBuf {
         if (n <= bytes) return LGFIB_OK;
         release();
         if (hipMalloc(&p, n) != hipSuccess) {
+            (void)hipGetLastError();   // reported here, not by the next launch
             p = nullptr;
             return fail(LGFIB_ENOMEM, "hipMalloc of " + std::to_string(n) + " bytes failed");
         }

@@ -402,6 +402,7 @@ static int mlp_reserve(ib_mlp *m, int M) {
     if (M <= m->cap) return LGFIB_OK;
     int rc;
     const size_t f = sizeof(float);
+    m->cap = 0;   // a buffer that cannot grow is gone
     if ((rc = m->xh.reserve((size_t)M * mlp_pad(m->nin) * f)) || (rc = m->th.reserve((size_t)M * m->nout * f)) ||
         (rc = m->h1.reserve((size_t)M * m->nh * f)) || (rc = m->h2.reserve((size_t)M * m->nh * f)) ||
         (rc = m->o.reserve((size_t)M * m->nout * f)) || (rc = m->dO.reserve((size_t)M * mlp_pad(m->nout) * f)) ||

@@ -287,3 +287,20 @@ def test_training_gathers_the_shuffled_rows(ctx):
     assert np.array_equal(lg.ib_mlp_get_params(a), lg.ib_mlp_get_params(b))
     a.close()
     b.close()
+
+
+def test_network_after_a_refused_growth(ctx):
+    """A call that asks for more activations than the card holds (2^31 - 1 rows of
+    4096: 35 TB) is refused before any kernel, and leaves a network that works:
+    the same values as before it."""
+    nin, nh, nout, M = 1, 4096, 1, 50
+    p, x, t, nm = _problem(nin, nh, nout, M, 16)
+    net = _make(ctx, nin, nh, nout, p, nm)
+    xd = torch.from_numpy(x).cuda()
+    y0, y1 = torch.zeros((M, nout), device="cuda"), torch.zeros((M, nout), device="cuda")
+    lg.ib_mlp_forward(ctx, net, xd, y0)
+    rc = lg.load_library().ib_mlp_forward(ctx.handle, net.handle, xd.data_ptr(), 2 ** 31 - 1, y1.data_ptr(), None)
+    assert rc == lg.LGFIB_ENOMEM
+    lg.ib_mlp_forward(ctx, net, xd, y1)
+    assert torch.equal(y0, y1)
+    net.close()

@@ -28,8 +28,7 @@ constexpr int kKT = 32;     // K slice staged in LDS per GEMM step (16 and 64 me
 // C = alpha op(A) op(B) + beta C with op(A)(m, k) = A[m lda + k] and
 // op(B)(k, n) = TB ? B[n ldb + k] : B[k ldb + n].  Tile (32 FM)^2 per
 // workgroup of four waves, each wave (16 FM)^2 as FM x FM blocks of 16 x 16.
-// lower != 0 skips tiles that lie strictly above the diagonal m = n.  tri
-// names an operand that is lower triangular (zero above its diagonal), whose
+// tri names the operand that is lower triangular (zero above its diagonal), whose
 // zero part a tile then skips along k: kTriBtLower, op(B)(k, n) = B[n][k]
 // with k <= n; kTriBLower, op(B)(k, n) = B[k][n] with k >= n; kTriALower,
 // op(A)(m, k) = A[m][k] with k <= m.  The skipped entries must be zero.
@@ -110,7 +109,7 @@ __device__ __forceinline__ void gemm_f64_tile(Lds &As, Lds &Bs, int m0, int n0, 
     const int nslice = (ke - kb + kKT - 1) / kKT;
     for (int s = 0; s < nslice; ++s) {
         const int buf = s & 1;
-        fetch(kb + (s + 1) * kKT);   // zeros after the last slice
+        fetch(kb + (s + 1) * kKT);   // after the last slice: not used
 #pragma unroll
         for (int ks = 0; ks < kKT; ks += 4) {
             double a[FM], b[FM];
@@ -145,7 +144,7 @@ __device__ __forceinline__ void gemm_f64_tile(Lds &As, Lds &Bs, int m0, int n0, 
 template <int FM, bool TB>
 __global__ __launch_bounds__(256) void k_gemm_f64(int M, int N, int K, double alpha, const double *__restrict__ A,
                                                   long lda, const double *__restrict__ Bm, long ldb, double beta,
-                                                  double *__restrict__ C, long ldc, int lower, int tri) {
+                                                  double *__restrict__ C, long ldc, int tri) {
     constexpr int T = 32 * FM;
     // two LDS buffers: slice s + 1 is staged while slice s is multiplied
     __shared__ double As[2][T][kKT + 1];    // [m][k]
@@ -156,17 +155,16 @@ __global__ __launch_bounds__(256) void k_gemm_f64(int M, int N, int K, double al
     int bx = blockIdx.x, by = blockIdx.y;
     if (tri == kTriALower) {
         by = gridDim.y - 1 - by;
-    } else if (tri != kTriNone) {
+    } else {
         const int id = by * gridDim.x + bx;
         bx = id / gridDim.y;
         by = id % gridDim.y;
         if (tri == kTriBtLower) bx = gridDim.x - 1 - bx;
     }
     const int m0 = by * T, n0 = bx * T;
-    if (lower && n0 > m0 + T - 1) return;
     // k range of the tile (tile edges are multiples of kKT)
     const int kb = tri == kTriBLower ? min(n0, K) : 0;
-    const int ke = tri == kTriBtLower ? min(n0 + T, K) : (tri == kTriALower ? min(m0 + T, K) : K);
+    const int ke = tri == kTriBtLower ? min(n0 + T, K) : tri == kTriALower ? min(m0 + T, K) : K;
     // offsets of the inner form: 32 bits for the rows one step covers
     const bool inner = m0 + T <= M && n0 + T <= N && ke > kb && (ke - kb) % kKT == 0 && max(lda, ldb) < (1l << 24);
     if (inner)
@@ -176,7 +174,7 @@ __global__ __launch_bounds__(256) void k_gemm_f64(int M, int N, int K, double al
 }
 
 int gemm_f64(int M, int N, int K, double alpha, const double *A, long lda, const double *B, long ldb, bool tb,
-             double beta, double *C, long ldc, bool lower, int tri, hipStream_t st) {
+             double beta, double *C, long ldc, int tri, hipStream_t st) {
     if (M <= 0 || N <= 0) return LGFIB_OK;
     if (K <= 0) return fail(LGFIB_EINVAL, "gemm_f64: empty inner dimension");
     // 64-edge tiles for every product: the 128-edge form (FM = 4) measured
@@ -184,13 +182,12 @@ int gemm_f64(int M, int N, int K, double alpha, const double *A, long lda, const
     // workgroups in flight)
     constexpr int T = 64;
     const dim3 grid((N + T - 1) / T, (M + T - 1) / T);
-    const int lw = lower ? 1 : 0;
     if (tb)
         hipLaunchKernelGGL((k_gemm_f64<2, true>), grid, dim3(256), 0, st, M, N, K, alpha, A, lda, B, ldb, beta, C,
-                           ldc, lw, tri);
+                           ldc, tri);
     else
         hipLaunchKernelGGL((k_gemm_f64<2, false>), grid, dim3(256), 0, st, M, N, K, alpha, A, lda, B, ldb, beta, C,
-                           ldc, lw, tri);
+                           ldc, tri);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
 }
@@ -215,7 +212,7 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
 //   L_ip = A_ip W_pp^T for the blocks below it, one wavefront each, and
 //   A_ij -= L_ip L_jp^T for the blocks to its right, on the matrix cores;
 // then, for i - j = 1, 2, 3, W_ij = -W_ii sum_k L_ik W_kj, whose inner sum comes
-// out of the matrix cores in the operand layout of the outer product.  15
+// out of the matrix cores in the operand layout of the outer product.  14
 // barriers a leaf.  The form with one column of all 64 rows per barrier took
 // 43 us (128 barriers), this one 23; a 128-row node 107 -> 65 us.
 // A pivot that is not positive sets *bad; the factor then holds NaN.
@@ -521,7 +518,7 @@ static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long 
     {
         ProfScope ps(ctx, "k_gemm_f64", st);
         // S = L21 = A21 W11^T
-        if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, true, 0.0, ws.S, lds, false, kTriBtLower, st)))
+        if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, true, 0.0, ws.S, lds, kTriBtLower, st)))
             return rc;
         const unsigned t1 = n1 / 64, t2 = (n2 + 63) / 64;
         hipLaunchKernelGGL(k_chol_trail, dim3(t2 * (t2 + 1) / 2 + (early ? 2 : 1) * t1 * t2), dim3(256), 0, st, n1, n2,
@@ -534,11 +531,11 @@ static int chol_rec(lgfib_ctx *ctx, int n, double *A, long lda, double *W, long 
         // W21 = -W22 (L21 W11)
         const double *T = early;
         if (!T) {
-            if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, false, 0.0, ws.S, lds, false, kTriBLower, st)))
+            if ((rc = gemm_f64(n2, n1, n1, 1.0, A21, lda, W, ldw, false, 0.0, ws.S, lds, kTriBLower, st)))
                 return rc;
             T = ws.S;
         }
-        if ((rc = gemm_f64(n2, n1, n2, -1.0, W22, ldw, T, lds, false, 0.0, W21, ldw, false, kTriALower, st)))
+        if ((rc = gemm_f64(n2, n1, n2, -1.0, W22, ldw, T, lds, false, 0.0, W21, ldw, kTriALower, st)))
             return rc;
     }
     return LGFIB_OK;

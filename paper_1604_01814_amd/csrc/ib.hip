@@ -445,8 +445,7 @@ struct BlockMapDev {
 // Block sums of a grid-wide reduction go to part[block]; the last block to
 // finish (a device-scope counter) adds them in block order, so the result
 // does not depend on which block finishes last.  One launch per reduction.
-__device__ inline void grid_sum_to(double s, double *part, unsigned *counter, double *out,
-                                   double *host_out = nullptr) {
+__device__ inline void grid_sum_to(double s, double *part, unsigned *counter, double *out) {
     __shared__ double sh[256];
     __shared__ bool last;
     sh[threadIdx.x] = s;
@@ -473,7 +472,6 @@ __device__ inline void grid_sum_to(double s, double *part, unsigned *counter, do
     }
     if (threadIdx.x == 0) {
         *out = sh[0];
-        if (host_out) *host_out = sh[0];   // pinned host memory, read after an event
         *counter = 0u;
     }
 }

@@ -15,8 +15,9 @@
 //         p^3 x p^3 node matrix with the gathered charges on the matrix
 //         cores, tiles of 128 pairs added atomically into Phi (one target
 //         receives several displacements);
-//   L2L   per target cluster below the top: Phi(c) = parent's Phi
-//         interpolated at c's nodes (a plain store that precedes M2L);
+//   L2L   per target cluster below the top, level by level downwards: Phi(c) +=
+//         parent's Phi interpolated at c's nodes (after M2L, which starts from
+//         zeroed Phi and takes the pairs of every level in one launch);
 //   leaf  per target block: L2P (Phi interpolated at the cells) plus the exact
 //         sum over the neighbouring source blocks.  For B = 8 that sum runs on
 //         the matrix cores, in the even and odd parts of the blocks along each
@@ -201,9 +202,11 @@ __global__ __launch_bounds__(256) void k_ml_kmat(const double *__restrict__ tab,
     }
 }
 
-__global__ void k_ml_zero(double *__restrict__ p, size_t n) {
+// p = 0 and, where given, *flag = 0
+__global__ void k_ml_zero(double *__restrict__ p, size_t n, int *__restrict__ flag) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0.0;
+    if (i == 0 && flag) *flag = 0;
 }
 
 // exact sum of one neighbouring source block into a row of B target cells;
@@ -368,7 +371,7 @@ __device__ __forceinline__ int near_place(int c) {
 }
 // Fp = T f for every source block, and zeros in every target block of Yp.
 // bad[s]: a folded value of block s is no finite R (an infinity or NaN in f, or
-// a sum of finite cells that overflows)
+// a sum of finite cells that overflows); bad[nsrc]: of any block
 template <typename R>
 __global__ __launch_bounds__(256) void k_ml_fold(const double *__restrict__ f, double *__restrict__ Fp,
                                                   double *__restrict__ Yp, int *__restrict__ bad, int nsrc, int ntgt) {
@@ -388,7 +391,10 @@ __global__ __launch_bounds__(256) void k_ml_fold(const double *__restrict__ f, d
         fin = fin && isfinite((R)b[c]);
     }
     const int any = __syncthreads_or(!fin);
-    if (t == 0) bad[s] = any;
+    if (t == 0) {
+        bad[s] = any;
+        if (any) bad[nsrc] = 1;
+    }
 }
 
 // The neighbour sum of target block t as it stands, without the parities:
@@ -424,15 +430,19 @@ __device__ __noinline__ void near_direct(const double *__restrict__ f, const dou
 template <typename R>
 __global__ __launch_bounds__(256) void k_ml_unfold(const double *__restrict__ Yp, double *__restrict__ u, double scale,
                                                     const int *__restrict__ near_off, const int2 *__restrict__ near_ent,
-                                                    const int *__restrict__ bad, const double *__restrict__ f,
+                                                    const int *__restrict__ bad, int nsrc, const double *__restrict__ f,
                                                     const double *__restrict__ tab, int e1, int e2, int e3) {
     __shared__ double b[512];
-    const int t = threadIdx.x, n0 = near_off[blockIdx.x], n = near_off[blockIdx.x + 1] - n0;   // n <= 27
+    const int t = threadIdx.x;
     const size_t o = (size_t)blockIdx.x * 512;
     for (int c = t; c < 512; c += 256) b[c] = Yp[o + near_place(c)];
-    if (__syncthreads_or(t < n && bad[near_ent[n0 + t].x])) {
-        near_direct<R>(f, tab, e1, e2, e3, near_ent + n0, n, u + o, scale, b);
-        return;
+    __syncthreads();
+    if (bad[nsrc]) {
+        const int n0 = near_off[blockIdx.x], n = near_off[blockIdx.x + 1] - n0;   // n <= 27
+        if (__syncthreads_or(t < n && bad[near_ent[n0 + t].x])) {
+            near_direct<R>(f, tab, e1, e2, e3, near_ent + n0, n, u + o, scale, b);
+            return;
+        }
     }
     near_fold_axis(b, 1, true);
     near_fold_axis(b, 8, true);
@@ -620,7 +630,7 @@ struct lgf_ml {
     DevBuf W0, Wup, kids, par, tasks, pairs, K, near_off, near_ent, M, Phi, dinfo, nodes;
     int nntask[2] = {0, 0};             // B = 8: neighbour products on the matrix cores, 128 and 64 columns wide
     int pair_prec = LGF_F64;            // precision of the pair products (M2L, neighbour sums)
-    DevBuf nbr_tasks, nbr_pairs, Kn, folded, bad;   // folded: sources, then targets; bad: by source block
+    DevBuf nbr_tasks, nbr_pairs, Kn, folded, bad;   // folded: sources, then targets; bad: by source block, then any
 };
 
 namespace {
@@ -648,7 +658,8 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
             LGF_HIP(hipGetLastError());
         }
         const size_t nphi = (pl->t_off[pl->top] + pl->nt[pl->top]) * P3;
-        hipLaunchKernelGGL(k_ml_zero, dim3((unsigned)((nphi + 255) / 256)), dim3(256), 0, st, Phi, nphi);
+        hipLaunchKernelGGL(k_ml_zero, dim3((unsigned)((nphi + 255) / 256)), dim3(256), 0, st, Phi, nphi,
+                           pl->bad.p ? pl->bad.as<int>() + pl->nsrc : nullptr);
         LGF_HIP(hipGetLastError());
         if (pl->nm2l > 0) {
             ProfScope ps(ctx, "k_ml_m2l", st);
@@ -688,7 +699,7 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
                 if (g0.x) hipLaunchKernelGGL((k_ml_near<128, R>), g0, dim3(512), 0, st, tk, pr, Fp, Kn, Yp);
                 if (g1.x) hipLaunchKernelGGL((k_ml_near<64, R>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
                 hipLaunchKernelGGL(k_ml_unfold<R>, dim3(pl->ntgt), b, 0, st, Yp, uc, dx * dx, pl->near_off.as<int>(),
-                                   pl->near_ent.as<int2>(), pl->bad.as<int>(), fc, tb.g.as<double>(), tb.ext[0],
+                                   pl->near_ent.as<int2>(), pl->bad.as<int>(), pl->nsrc, fc, tb.g.as<double>(), tb.ext[0],
                                    tb.ext[1], tb.ext[2]);
             };
             if (pl->pair_prec == LGF_F64) run(pl->Kn.as<double>());
@@ -958,7 +969,7 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
         return rc;
     if (pl->nntask[0] + pl->nntask[1] > 0) {
         if ((rc = pl->folded.reserve(((size_t)nsrc + ntgt) * 512 * sizeof(double))) ||
-            (rc = pl->bad.reserve((size_t)nsrc * sizeof(int))))
+            (rc = pl->bad.reserve(((size_t)nsrc + 1) * sizeof(int))))
             return rc;
         const bool f64 = pair_prec == LGF_F64;
         if ((rc = pl->Kn.reserve((size_t)27 * 512 * 512 * (f64 ? sizeof(double) : sizeof(float))))) return rc;

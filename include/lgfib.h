@@ -562,10 +562,10 @@ int lgf_pair_apply_noalloc(lgfib_ctx *ctx, lgf_table_t tbl, int B, const int32_t
  * lgf_ml_apply evaluates: f DEVICE double [ncomp][nsrc][B^3] (cells z, y, x
  *   within a block, blocks in list order), u DEVICE double
  *   [ncomp][ntgt][B^3], overwritten; 1 <= ncomp <= 8; dx > 0; f and u must
- *   not overlap; u must be ordinary (coarse-grained) device memory, since
- *   the pair products add into it with hardware floating-point atomics.
- *   Asynchronous on `stream`; one apply at a time per plan (the plan holds
- *   the node values).  Results differ from run to run in the last bits
+ *   not overlap.  Asynchronous on `stream`; one apply at a time per plan (the
+ *   plan holds the node values and, for B = 8, the sources and the neighbour
+ *   sums in parities, 4 KiB per source and target block).  An infinity or NaN in
+ *   a cell reaches its neighbouring blocks as in the plain sum.  Results differ from run to run in the last bits
  *   (pair products are accumulated atomically).
  * lgf_ml_info: levels above the blocks (top), source and target clusters
  *   over all levels, node-to-node pairs, neighbour block pairs and distinct

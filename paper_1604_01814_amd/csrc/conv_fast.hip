@@ -1,8 +1,8 @@
-// conv_fast.hip -- FP32 box-FFT passes specialised at compile time on the FFT
-// length of their axis (the hot path of lgf_poisson_apply).  Same five passes,
-// data layout and arithmetic as the generic kernels in conv.hip; the lengths
-// 32..1024 with radices {2,3,4,5,8,16} are instantiated, other boxes fall back
-// to the generic kernels.
+// conv_fast.hip -- box-FFT passes specialised at compile time on the FFT length
+// of their axis, FP32 and FP64 (the hot path of lgf_poisson_apply).  Same five
+// passes and data layout as the generic kernels in conv.hip; the lengths of
+// fft_static.h's radix lists, 16 to 1024 points with radices up to 30, are
+// instantiated, other boxes fall back to the generic kernels.
 #include <algorithm>
 #include <cstdlib>
 
@@ -306,7 +306,7 @@ template <typename C, int P, int NP> struct ZMul {
 //
 // Taken where the pass alone measured faster (three components of a cubic box,
 // us, on the stages in LDS -> here):
-//   FP32   48: 7.0 -> 5.7    64: 8.2 -> 6.9    96: 14.6 -> 14.1  128: 18.6 -> 15.9
+//   FP32   32: 6.9 -> 5.4    48: 7.0 -> 5.7    64: 8.2 -> 6.9    96: 14.6 -> 14.1  128: 18.6 -> 15.9
 //         160: 33.0 -> 29.8  192: 49.5 -> 47.5 240: 68.6 -> 64.0
 //   FP64   32: 8.9 -> 6.8    48: 21.1 -> 15.3  64: 21.8 -> 16.7   80: 23.2 -> 18.1
 //          96: 25.0 -> 20.3  128: 29.2 -> 24.1 144: 37.5 -> 30.8 192: 72.8 -> 64.1

@@ -4,11 +4,17 @@
 //
 // Everything that decides an address is a template constant (P, NP, the LDS
 // strides, the radix of every stage and its Ns), so index arithmetic folds to
-// shifts and multiplies.  Stages use radices up to 16 (three LDS round trips
-// for the 384- and 640-point transforms of the benchmark box).  Twiddles come
-// from a P/2-entry table in LDS (the other half by symmetry): a butterfly reads
-// the exact powers w^1, w^2, w^4, w^8 and forms the others with at most two
-// complex products.
+// shifts and multiplies.  Stages use radices up to 16, the first one, which has
+// no twiddles, up to 30 (two LDS round trips for the 384-point and three for the
+// 640-point transforms of the benchmark box).  Twiddles come from a P/2-entry
+// table in LDS (the other half by symmetry): a butterfly reads the exact powers
+// w^1, w^2, w^4, w^8 and forms the others with at most two complex products, or
+// reads all of them from a table of the last stage.
+//
+// Rounding against the former lists of more stages (rms error against extended
+// precision, 40 random inputs a length on each axis): FP64 0.97 to 1.02 of theirs,
+// 1.10 along z at 192 points (a cube of it 0.96); FP32 0.97 to 1.02, 1.02 to 1.07 at
+// 96 and 1.05 to 1.09 at 288 points.
 #pragma once
 
 #include <type_traits>

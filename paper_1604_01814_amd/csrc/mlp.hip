@@ -15,7 +15,7 @@
 // (bias, tanh and the squared-error gradient in their epilogues), two backward
 // products (the tanh derivative in the epilogue), and one launch for the three
 // weight gradients and the bias gradients with Adam applied as they are stored.
-// 4096 rows of 12-256-256-3: 1.70 -> 0.08 ms a step.
+// 4096 rows of 12-256-256-3: 1.70 -> 0.097 ms a step.
 #include <algorithm>
 #include <cmath>
 #include <cstring>

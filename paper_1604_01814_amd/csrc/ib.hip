@@ -84,6 +84,13 @@ struct SpreadOp {
     int nfr = 0, nrows = 0;
     DevBuf row, ptr, col, val;
 };
+// The operators of a force system with the gradient folded in: the spread on the
+// plan's own blocks, and the cell below the face of entry e of I along its
+// component, -1 outside the blocks (i_low[e])
+struct GradOps {
+    SpreadOp spread;
+    DevBuf i_low;
+};
 
 struct IbPlan {
     int kernel = 0, NL = 0, B = 0, nblk = 0;
@@ -98,16 +105,10 @@ struct IbPlan {
     // on the host: the faces that some marker reaches, and the end of each one's
     // row of R
     std::vector<int32_t> face, fend;
-    // with the gradient folded in (ib_plan_grad, built for force systems):
-    // i_low[e]: the cell below entry e's face along its component, -1 outside
-    // the blocks
-    bool grad = false;
-    DevBuf i_low;
-    SpreadOp spread;
-    // the same with the cells of a flow on these blocks (ib_flow_create), which
-    // every flow of the plan uses
-    bool flow = false;
-    SpreadOp flow_spread;
+    // what the plan's force systems share (ib_plan_grad), and its flows (the
+    // spread with the flow's cells, ib_flow_create), as long as one of them lives
+    std::weak_ptr<GradOps> grad;
+    std::weak_ptr<SpreadOp> flow;
 };
 
 // I of a plan on the host, as build_ib_plan leaves it
@@ -400,18 +401,19 @@ static int build_spread(const IbPlan &p, const int32_t *blocks, const CellSet &c
 // The operators of the force Schur complement with the staggered gradient
 // folded in: the spread operator on the plan's own blocks, and for (G d)^(k)(n)
 // = d(n) - d(n - e_k) the cell below each entry of I.
-static int ib_plan_grad(IbPlan &p, const int32_t *blocks, IbHost &h) {
-    if (p.grad) return LGFIB_OK;
+static int ib_plan_grad(IbPlan &p, const int32_t *blocks, IbHost &h, std::shared_ptr<GradOps> &out) {
+    if ((out = p.grad.lock())) return LGFIB_OK;
     std::vector<int32_t> map((size_t)p.nb[0] * p.nb[1] * p.nb[2], -1), low;
     for (int i = 0; i < p.nblk; ++i)
         map[((size_t)(blocks[3 * i + 2] - p.lo[2]) * p.nb[1] + (blocks[3 * i + 1] - p.lo[1])) * p.nb[0] +
             (blocks[3 * i] - p.lo[0])] = i;
+    auto g = std::make_shared<GradOps>();
     int rc;
-    if ((rc = build_spread(p, blocks, CellSet{p.lo, p.nb, map}, (int64_t)p.nblk * p.B * p.B * p.B, h, p.spread, &low)) ||
-        (rc = p.i_low.reserve(4 * low.size())))
+    if ((rc = build_spread(p, blocks, CellSet{p.lo, p.nb, map}, (int64_t)p.nblk * p.B * p.B * p.B, h, g->spread, &low)) ||
+        (rc = g->i_low.reserve(4 * low.size())))
         return rc;
-    LGF_HIP(hipMemcpy(p.i_low.p, low.data(), 4 * low.size(), hipMemcpyHostToDevice));
-    p.grad = true;
+    LGF_HIP(hipMemcpy(g->i_low.p, low.data(), 4 * low.size(), hipMemcpyHostToDevice));
+    p.grad = out = std::move(g);
     return LGFIB_OK;
 }
 
@@ -680,11 +682,11 @@ static unsigned gather_blocks(int NL) { return nblocks(16 * 3 * (size_t)NL, 256)
 
 // y = I (a + G d); with dot_p the blocks' shares of dot_p . y go to part
 template <typename In, typename Out>
-static int launch_gather(lgfib_ctx *ctx, const IbPlan &p, const In *a, const In *d, Out *y, const double *dot_p,
-                         double *part, hipStream_t st) {
+static int launch_gather(lgfib_ctx *ctx, const IbPlan &p, const GradOps &g, const In *a, const In *d, Out *y,
+                         const double *dot_p, double *part, hipStream_t st) {
     ProfScope ps(ctx, "k_gather", st);
     hipLaunchKernelGGL((k_gather<In, Out>), dim3(gather_blocks(p.NL)), dim3(256), 0, st, p.i_ptr.as<int>(),
-                       p.i_col.as<int>(), p.i_low.as<int>(), p.i_val.as<double>(), a, d, y, 3 * p.NL,
+                       p.i_col.as<int>(), g.i_low.as<int>(), p.i_val.as<double>(), a, d, y, 3 * p.NL,
                        p.nblk * p.B * p.B * p.B, dot_p, part);
     LGF_HIP(hipGetLastError());
     return LGFIB_OK;
@@ -809,6 +811,7 @@ struct ib_system {
     std::vector<int32_t> blocks;
     lgf_table_t tbl = -1;
     std::shared_ptr<IbPlan> plan;   // held: pinned in the context's cache
+    std::shared_ptr<GradOps> grad;
     // work fields per precision: faces g, faces a, cells c, cells d; g and c are
     // written by k_spread alone
     DevBuf g[2], af[2], c[2], d[2];
@@ -844,14 +847,14 @@ static int schur_apply_t(ib_system *s, const VIn *x, VOut *y, hipStream_t st, co
     const int prec = pi ? LGF_F64 : LGF_F32;
     Real *g = s->g[pi].as<Real>(), *af = s->af[pi].as<Real>(), *c = s->c[pi].as<Real>(), *d = s->d[pi].as<Real>();
     int rc;
-    if ((rc = launch_spread<VIn, Real>(ctx, s->plan->spread, x, dir, g, c, st))) return rc;
+    if ((rc = launch_spread<VIn, Real>(ctx, s->grad->spread, x, dir, g, c, st))) return rc;
     if ((rc = lgf_if_apply(ctx, s->a, s->B, s->blocks.data(), s->nblk, s->blocks.data(), s->nblk, 3, prec, g, af,
                            (lgfib_stream_t)st)))
         return rc;
     if ((rc = lgf_poisson_apply(ctx, s->tbl, s->B, s->blocks.data(), s->nblk, s->blocks.data(), s->nblk, 1, prec, 1.0,
                                 c, d, 0, (lgfib_stream_t)st)))
         return rc;
-    return launch_gather<Real, VOut>(ctx, *s->plan, af, d, y, dir ? dir->p : nullptr,
+    return launch_gather<Real, VOut>(ctx, *s->plan, *s->grad, af, d, y, dir ? dir->p : nullptr,
                                      s->red.as<double>() + 2 * kRedBlocks, st);
 }
 
@@ -878,7 +881,7 @@ extern "C" int ib_system_create(lgfib_ctx *ctx, int kernel, const double *X, int
     s->blocks.assign(blocks, blocks + 3 * (size_t)nblk);
     IbHost host;
     if ((rc = build_ib_plan(ctx, kernel, X, NL, B, blocks, nblk, s->plan, &host))) return rc;
-    if ((rc = ib_plan_grad(*s->plan, blocks, host))) return rc;
+    if ((rc = ib_plan_grad(*s->plan, blocks, host, s->grad))) return rc;
     int ext[3];
     for (int q = 0; q < 3; ++q) ext[q] = s->plan->nb[q] * B - 1;
     if ((rc = lgf_table_build(ctx, LGF_KIND_K, a, ext, nullptr, &s->tbl))) return rc;
@@ -1397,8 +1400,9 @@ struct ib_flow {
     DevBuf cmap, cblk;              // block map of the cell blocks
     lgf_table_t tbl = -1;           // G_L over the cell span
     DevBuf c, dstar, w, h, rhs;
-    // R f on the faces and G^T R f on the cells, written by the plan's
-    // flow_spread alone (zeros where no marker reaches)
+    // R f on the faces and G^T R f on the cells, written by the spread operator
+    // alone (zeros where no marker reaches)
+    std::shared_ptr<SpreadOp> spread;   // shared by the plan's flows
     DevBuf rf, cf;
 };
 
@@ -1566,11 +1570,13 @@ extern "C" int ib_flow_create(lgfib_ctx *ctx, ib_system *sys, const int32_t *flo
         if ((rc = f->cmap.reserve(map.size() * 4)) || (rc = f->cblk.reserve(f->cblocks.size() * 4))) return rc;
         LGF_HIP(hipMemcpy(f->cmap.p, map.data(), map.size() * 4, hipMemcpyHostToDevice));
         LGF_HIP(hipMemcpy(f->cblk.p, f->cblocks.data(), f->cblocks.size() * 4, hipMemcpyHostToDevice));
-        IbPlan &p = *f->plan;   // its blocks determine the cells
-        if (!p.flow && (rc = build_spread(p, flow_blocks, CellSet{f->clo, f->cnb, map},
-                                          (int64_t)f->ncell * f->B * f->B * f->B, host, p.flow_spread, nullptr)))
-            return rc;
-        p.flow = true;
+        if (!(f->spread = f->plan->flow.lock())) {   // the plan's blocks determine the cells
+            auto op = std::make_shared<SpreadOp>();
+            if ((rc = build_spread(*f->plan, flow_blocks, CellSet{f->clo, f->cnb, map},
+                                   (int64_t)f->ncell * f->B * f->B * f->B, host, *op, nullptr)))
+                return rc;
+            f->plan->flow = f->spread = std::move(op);
+        }
     }
     int ext[3];
     for (int q = 0; q < 3; ++q) ext[q] = f->cnb[q] * sys->B - 1;
@@ -1638,7 +1644,7 @@ static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, const double *u, double *u_ou
     if (rc && rc != LGFIB_ENOCONV) return rc;
     const int solve_rc = rc;
     // (pc) d = d* + L^{-1} G^T R f
-    if ((rc = launch_spread<double, double>(ctx, P.flow_spread, f, nullptr, rf, fl->cf.as<double>(), st))) return rc;
+    if ((rc = launch_spread<double, double>(ctx, *fl->spread, f, nullptr, rf, fl->cf.as<double>(), st))) return rc;
     if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, fl->cf.p, d, 1, (lgfib_stream_t)st)))
         return rc;
     // (vc) u' = E(a)[u - G d - R f]
@@ -1680,7 +1686,7 @@ static int schur_dense_cols(ib_system *s, int j0, int K, double *C, long ld, hip
     for (int k = 0; k < K; ++k) {
         hipLaunchKernelGGL(k_unit, dim3(nblocks(n, 256)), dim3(256), 0, st, e + (size_t)k * n, n, j0 + k);
         LGF_HIP(hipGetLastError());
-        if ((rc = launch_spread<double, double>(ctx, P.spread, e + (size_t)k * n, nullptr, g + k * nf, c + k * nc, st)))
+        if ((rc = launch_spread<double, double>(ctx, s->grad->spread, e + (size_t)k * n, nullptr, g + k * nf, c + k * nc, st)))
             return rc;
     }
     for (int c0 = 0; c0 < 3 * K; c0 += 8) {
@@ -1693,7 +1699,7 @@ static int schur_dense_cols(ib_system *s, int j0, int K, double *C, long ld, hip
                                 1.0, c, d, 0, (lgfib_stream_t)st)))
         return rc;
     for (int k = 0; k < K; ++k) {
-        if ((rc = launch_gather<double, double>(ctx, P, af + k * nf, d + k * nc, y + (size_t)k * n, nullptr, nullptr,
+        if ((rc = launch_gather<double, double>(ctx, P, *s->grad, af + k * nf, d + k * nc, y + (size_t)k * n, nullptr, nullptr,
                                                 st)))
             return rc;
         hipLaunchKernelGGL(k_put_column, dim3(nblocks(n, 256)), dim3(256), 0, st, C, ld, j0 + k,

@@ -139,3 +139,32 @@ def test_ib_system_survives_cache_cycling():
         sys_.close()
     finally:
         ctx.close()
+
+
+def test_cached_plans_give_back_what_their_systems_held():
+    """Force systems made and closed at 12 positions leave their plans cached: 24
+    bytes a weight of I and R and 4 a face of the blocks (half as much again
+    allowed, and 2 MiB a plan for the allocator's pages), not the operators that
+    a living system adds."""
+    ctx = lg.Context(0)
+    try:
+        B, n = 8, 12
+        X0 = workloads.sphere_markers(32.0, 4000)
+
+        def make(k):
+            X = X0 + 0.01 * k
+            s = lg.ib_system_create(ctx, lg.IB_ROMA3, X, B, blocks, 0.05)
+            s.close()
+
+        blocks = oracle.body_blocks(np.concatenate([X0, X0 + 0.01 * (n + 1)]), ROMA3, B)
+        make(0)   # the table, kernels and one plan
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        for k in range(1, n + 1):
+            make(k)
+        held = free - torch.cuda.mem_get_info()[0]
+        assert lg.lgfib_cache_info(ctx)["ib_plans"] == n + 1
+        plan = 24 * 3 * len(X0) * 27 + 4 * 3 * len(blocks) * B ** 3
+        assert held <= n * (1.5 * plan + (2 << 20))
+    finally:
+        ctx.close()

@@ -91,6 +91,13 @@ struct GradOps {
     SpreadOp spread;
     DevBuf i_low;
 };
+// The spread operator of a flow (the plan's faces, the flow's cells) and its
+// outputs, R f and G^T R f, which nothing else writes: zeros where no marker
+// reaches.  A step of a flow is done with them before it returns.
+struct FlowOps {
+    SpreadOp spread;
+    DevBuf rf, cf;
+};
 
 struct IbPlan {
     int kernel = 0, NL = 0, B = 0, nblk = 0;
@@ -105,10 +112,10 @@ struct IbPlan {
     // on the host: the faces that some marker reaches, and the end of each one's
     // row of R
     std::vector<int32_t> face, fend;
-    // what the plan's force systems share (ib_plan_grad), and its flows (the
-    // spread with the flow's cells, ib_flow_create), as long as one of them lives
+    // what the plan's force systems share (ib_plan_grad), and its flows
+    // (ib_flow_create), as long as one of them lives
     std::weak_ptr<GradOps> grad;
-    std::weak_ptr<SpreadOp> flow;
+    std::weak_ptr<FlowOps> flow;
 };
 
 // I of a plan on the host, as build_ib_plan leaves it
@@ -1400,10 +1407,7 @@ struct ib_flow {
     DevBuf cmap, cblk;              // block map of the cell blocks
     lgf_table_t tbl = -1;           // G_L over the cell span
     DevBuf c, dstar, w, h, rhs;
-    // R f on the faces and G^T R f on the cells, written by the spread operator
-    // alone (zeros where no marker reaches)
-    std::shared_ptr<SpreadOp> spread;   // shared by the plan's flows
-    DevBuf rf, cf;
+    std::shared_ptr<FlowOps> ops;   // shared by the plan's flows
 };
 
 namespace lgfib {
@@ -1570,12 +1574,17 @@ extern "C" int ib_flow_create(lgfib_ctx *ctx, ib_system *sys, const int32_t *flo
         if ((rc = f->cmap.reserve(map.size() * 4)) || (rc = f->cblk.reserve(f->cblocks.size() * 4))) return rc;
         LGF_HIP(hipMemcpy(f->cmap.p, map.data(), map.size() * 4, hipMemcpyHostToDevice));
         LGF_HIP(hipMemcpy(f->cblk.p, f->cblocks.data(), f->cblocks.size() * 4, hipMemcpyHostToDevice));
-        if (!(f->spread = f->plan->flow.lock())) {   // the plan's blocks determine the cells
-            auto op = std::make_shared<SpreadOp>();
-            if ((rc = build_spread(*f->plan, flow_blocks, CellSet{f->clo, f->cnb, map},
-                                   (int64_t)f->ncell * f->B * f->B * f->B, host, *op, nullptr)))
+        if (!(f->ops = f->plan->flow.lock())) {   // the plan's blocks determine the cells
+            auto o = std::make_shared<FlowOps>();
+            const size_t ncc = (size_t)f->ncell * f->B * f->B * f->B, nf = 3 * (size_t)nflow * f->B * f->B * f->B;
+            if ((rc = build_spread(*f->plan, flow_blocks, CellSet{f->clo, f->cnb, map}, (int64_t)ncc, host, o->spread,
+                                   nullptr)) ||
+                (rc = o->cf.reserve(ncc * 8)) || (rc = o->rf.reserve(nf * 8)))
                 return rc;
-            f->plan->flow = f->spread = std::move(op);
+            LGF_HIP(hipMemset(o->cf.p, 0, ncc * 8));
+            LGF_HIP(hipMemset(o->rf.p, 0, nf * 8));
+            LGF_HIP(hipStreamSynchronize(nullptr));
+            f->plan->flow = f->ops = std::move(o);
         }
     }
     int ext[3];
@@ -1583,13 +1592,9 @@ extern "C" int ib_flow_create(lgfib_ctx *ctx, ib_system *sys, const int32_t *flo
     if ((rc = lgf_table_build(ctx, LGF_KIND_L, 0.0, ext, nullptr, &f->tbl))) return rc;
     const size_t B3 = (size_t)sys->B * sys->B * sys->B;
     const size_t nfc = (size_t)nflow * B3, ncc = (size_t)f->ncell * B3;
-    if ((rc = f->c.reserve(ncc * 8)) || (rc = f->dstar.reserve(ncc * 8)) || (rc = f->cf.reserve(ncc * 8)) ||
-        (rc = f->w.reserve(3 * nfc * 8)) || (rc = f->h.reserve(3 * nfc * 8)) || (rc = f->rf.reserve(3 * nfc * 8)) ||
-        (rc = f->rhs.reserve(3 * (size_t)sys->NL * 8)))
+    if ((rc = f->c.reserve(ncc * 8)) || (rc = f->dstar.reserve(ncc * 8)) || (rc = f->w.reserve(3 * nfc * 8)) ||
+        (rc = f->h.reserve(3 * nfc * 8)) || (rc = f->rhs.reserve(3 * (size_t)sys->NL * 8)))
         return rc;
-    LGF_HIP(hipMemset(f->cf.p, 0, ncc * 8));
-    LGF_HIP(hipMemset(f->rf.p, 0, 3 * nfc * 8));
-    LGF_HIP(hipStreamSynchronize(nullptr));
     *out = f.release();
     return LGFIB_OK;
 }
@@ -1612,7 +1617,7 @@ static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, const double *u, double *u_ou
     const int B = fl->B, lb = log2_edge(B);
     const size_t B3 = (size_t)B * B * B;
     const size_t nfc = (size_t)fl->nflow * B3, nf = 3 * nfc, ncc = (size_t)fl->ncell * B3, nl = 3 * (size_t)sys->NL;
-    double *c = fl->c.as<double>(), *d = fl->dstar.as<double>(), *rf = fl->rf.as<double>();
+    double *c = fl->c.as<double>(), *d = fl->dstar.as<double>(), *rf = fl->ops->rf.as<double>();
     double *w = fl->w.as<double>(), *h = fl->h.as<double>(), *rhs = fl->rhs.as<double>();
     const int32_t *bl = fl->blocks.data(), *cb = fl->cblocks.data();
     const int nb = fl->nflow, nc = fl->ncell;
@@ -1644,8 +1649,8 @@ static int flow_stage(lgfib_ctx *ctx, ib_flow *fl, const double *u, double *u_ou
     if (rc && rc != LGFIB_ENOCONV) return rc;
     const int solve_rc = rc;
     // (pc) d = d* + L^{-1} G^T R f
-    if ((rc = launch_spread<double, double>(ctx, *fl->spread, f, nullptr, rf, fl->cf.as<double>(), st))) return rc;
-    if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, fl->cf.p, d, 1, (lgfib_stream_t)st)))
+    if ((rc = launch_spread<double, double>(ctx, fl->ops->spread, f, nullptr, rf, fl->ops->cf.as<double>(), st))) return rc;
+    if ((rc = lgf_poisson_apply(ctx, fl->tbl, B, cb, nc, cb, nc, 1, LGF_F64, 1.0, fl->ops->cf.p, d, 1, (lgfib_stream_t)st)))
         return rc;
     // (vc) u' = E(a)[u - G d - R f]
     hipLaunchKernelGGL(k_grad_cross<true>, dim3(nblocks(nfc, 256)), dim3(256), 0, st, Fm, Am, lb, u, (const double *)d,

@@ -327,26 +327,54 @@ __host__ __device__ inline unsigned near_chunks(int zmask, int sub) {
 }
 
 // K'_D, product by product: product sub of code at code * 512^2 + sub * N^2, row
-// length N = 512 / 2^z.  One workgroup per (row of the folded target, code).
+// length N = 512 / 2^z.  One workgroup per (row of the folded target, code).  An
+// entry is a signed sum over the 64 images of its two cells, which falls into
+// one axis after the other: 8192 and 4096 terms a row for x and y and four an
+// entry for z, instead of 64 (all 27 codes: 143 -> 73 us).
 template <typename R>
 __global__ __launch_bounds__(256) void k_ml_near_mats(const double *__restrict__ tab, int e1, int e2, int e3,
                                                        R *__restrict__ Kn) {
+    __shared__ double fx[16 * 16 * 8];   // [target and source z][target and source y][px sx]
+    __shared__ double fy[16 * 8 * 8];    // [target and source z][py sy][px sx]
     const int code = blockIdx.y, zm = near_zero_axes(code), z = __popc(zm), N = 512 >> z;
-    const int sub = blockIdx.x / N, i = blockIdx.x % N;
+    const int sub = blockIdx.x / N, i = blockIdx.x % N, t = threadIdx.x;
     const unsigned ch = near_chunks(zm, sub);
     const int DX = code % 3 - 1, DY = (code / 3) % 3 - 1, DZ = code / 9 - 1;
     const int pt = ch >> (4 * (i / 64)) & 7, tx = i & 3, ty = (i >> 2) & 3, tz = (i >> 4) & 3;
-    for (int j = threadIdx.x; j < N; j += blockDim.x) {
-        const int ps = ch >> (4 * (j / 64)) & 7, sx = j & 3, sy = (j >> 2) & 3, sz = (j >> 4) & 3;
+    // places of an axis: target image 8 a + source cell; a = 0, 1 is cell t, 7 - t
+    for (int e = t; e < 16 * 16 * 8; e += 256) {
+        const int ps = e >> 2 & 1, sx = e & 3, y = e >> 3 & 15, zz = e >> 7;
+        const int dy = abs((y & 8 ? 7 - ty : ty) - (y & 7) - 8 * DY), dz = abs((zz & 8 ? 7 - tz : tz) - (zz & 7) - 8 * DZ);
+        const double *row = tab + ((size_t)dz * (e2 + 1) + dy) * (e1 + 1);
         double v = 0.0;
-        for (int a = 0; a < 8; ++a)
-            for (int b = 0; b < 8; ++b) {
-                const int dx = abs((a & 1 ? 7 - tx : tx) - (b & 1 ? 7 - sx : sx) - 8 * DX);
-                const int dy = abs((a & 2 ? 7 - ty : ty) - (b & 2 ? 7 - sy : sy) - 8 * DY);
-                const int dz = abs((a & 4 ? 7 - tz : tz) - (b & 4 ? 7 - sz : sz) - 8 * DZ);
-                const double g =
-                    dx <= e1 && dy <= e2 && dz <= e3 ? tab[((size_t)dz * (e2 + 1) + dy) * (e1 + 1) + dx] : 0.0;
-                v += (__popc(a & pt) + __popc(b & ps)) & 1 ? -g : g;
+        for (int a = 0; a < 2; ++a)
+            for (int b = 0; b < 2; ++b) {
+                const int dx = abs((a ? 7 - tx : tx) - (b ? 7 - sx : sx) - 8 * DX);
+                const double g = dx <= e1 && dy <= e2 && dz <= e3 ? row[dx] : 0.0;
+                v += (a & pt) ^ (b & ps) ? -g : g;
+            }
+        fx[e] = v;
+    }
+    __syncthreads();
+    for (int e = t; e < 16 * 8 * 8; e += 256) {
+        const int x = e & 7, sy = e >> 3 & 3, ps = e >> 5 & 1, zz = e >> 6;
+        double v = 0.0;
+        for (int a = 0; a < 2; ++a)
+            for (int b = 0; b < 2; ++b) {
+                const double g = fx[(zz * 16 + 8 * a + (b ? 7 - sy : sy)) * 8 + x];
+                v += (a & pt >> 1) ^ (b & ps) ? -g : g;
+            }
+        fy[e] = v;
+    }
+    __syncthreads();
+    for (int j = t; j < N; j += 256) {
+        const int ps = ch >> (4 * (j / 64)) & 7, sz = (j >> 4) & 3;
+        const int xy = ((ps >> 1 & 1) * 4 + ((j >> 2) & 3)) * 8 + (ps & 1) * 4 + (j & 3);
+        double v = 0.0;
+        for (int a = 0; a < 2; ++a)
+            for (int b = 0; b < 2; ++b) {
+                const double g = fy[(8 * a + (b ? 7 - sz : sz)) * 64 + xy];
+                v += (a & pt >> 2) ^ (b & ps >> 2) ? -g : g;
             }
         Kn[((size_t)code * 512 + (size_t)sub * N * N / 512) * 512 + (size_t)i * N + j] = (R)(0.125 * v);
     }
@@ -630,7 +658,8 @@ struct lgf_ml {
     DevBuf W0, Wup, kids, par, tasks, pairs, K, near_off, near_ent, M, Phi, dinfo, nodes;
     int nntask[2] = {0, 0};             // B = 8: neighbour products on the matrix cores, 128 and 64 columns wide
     int pair_prec = LGF_F64;            // precision of the pair products (M2L, neighbour sums)
-    DevBuf nbr_tasks, nbr_pairs, Kn, folded, bad;   // folded: sources, then targets; bad: by source block, then any
+    DevBuf nbr_tasks, nbr_pairs, Kn, folded;   // folded: sources, targets, then bad
+    int *bad = nullptr;                 // marks by source block, then any
 };
 
 namespace {
@@ -659,7 +688,7 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
         }
         const size_t nphi = (pl->t_off[pl->top] + pl->nt[pl->top]) * P3;
         hipLaunchKernelGGL(k_ml_zero, dim3((unsigned)((nphi + 255) / 256)), dim3(256), 0, st, Phi, nphi,
-                           pl->bad.p ? pl->bad.as<int>() + pl->nsrc : nullptr);
+                           pl->bad ? pl->bad + pl->nsrc : nullptr);
         LGF_HIP(hipGetLastError());
         if (pl->nm2l > 0) {
             ProfScope ps(ctx, "k_ml_m2l", st);
@@ -695,11 +724,11 @@ int ml_run(lgf_ml *pl, int ncomp, double dx, const double *f, double *u, hipStre
                 using R = std::remove_reference_t<decltype(*Kn)>;
                 const dim3 g0(pl->nntask[0]), g1(pl->nntask[1]), b(256);
                 hipLaunchKernelGGL(k_ml_fold<R>, dim3(std::max(pl->nsrc, pl->ntgt)), b, 0, st, fc, Fp, Yp,
-                                   pl->bad.as<int>(), pl->nsrc, pl->ntgt);
+                                   pl->bad, pl->nsrc, pl->ntgt);
                 if (g0.x) hipLaunchKernelGGL((k_ml_near<128, R>), g0, dim3(512), 0, st, tk, pr, Fp, Kn, Yp);
                 if (g1.x) hipLaunchKernelGGL((k_ml_near<64, R>), g1, b, 0, st, tk + g0.x, pr, Fp, Kn, Yp);
                 hipLaunchKernelGGL(k_ml_unfold<R>, dim3(pl->ntgt), b, 0, st, Yp, uc, dx * dx, pl->near_off.as<int>(),
-                                   pl->near_ent.as<int2>(), pl->bad.as<int>(), pl->nsrc, fc, tb.g.as<double>(), tb.ext[0],
+                                   pl->near_ent.as<int2>(), pl->bad, pl->nsrc, fc, tb.g.as<double>(), tb.ext[0],
                                    tb.ext[1], tb.ext[2]);
             };
             if (pl->pair_prec == LGF_F64) run(pl->Kn.as<double>());
@@ -968,9 +997,9 @@ extern "C" int lgf_ml_create(lgfib_ctx *ctx, lgf_table_t tbl, int B, int p, int 
         (rc = upload(pl->nbr_tasks, ntasks[0])) || (rc = upload(pl->nbr_pairs, npairs)))
         return rc;
     if (pl->nntask[0] + pl->nntask[1] > 0) {
-        if ((rc = pl->folded.reserve(((size_t)nsrc + ntgt) * 512 * sizeof(double))) ||
-            (rc = pl->bad.reserve(((size_t)nsrc + 1) * sizeof(int))))
-            return rc;
+        const size_t folded = ((size_t)nsrc + ntgt) * 512 * sizeof(double);
+        if ((rc = pl->folded.reserve(folded + ((size_t)nsrc + 1) * sizeof(int)))) return rc;
+        pl->bad = (int *)((char *)pl->folded.p + folded);
         const bool f64 = pair_prec == LGF_F64;
         if ((rc = pl->Kn.reserve((size_t)27 * 512 * 512 * (f64 ? sizeof(double) : sizeof(float))))) return rc;
         if (f64)

@@ -1148,7 +1148,8 @@ static int true_residual(ib_system *s, const double *b, const double *x, double 
     return read_scal(s, 2, rr, st);
 }
 
-constexpr int kMaxMean = 64;   // matvecs of a true residual, at most
+constexpr int kMaxMean = 64;         // matvecs of a true residual, at most
+constexpr double kMeanReach = 16.0;  // and how far from the target they may help: sqrt(64), and an FP64 sweep's drift
 
 static bool cg_graphs_wanted() {
     const char *e = getenv("LGFIB_CG_GRAPH");
@@ -1317,8 +1318,9 @@ extern "C" int ib_force_solve(lgfib_ctx *ctx, ib_system *sys, int prec, const do
     // matvecs it is formed with (2200 markers on a sphere: 1e-15 to 1.3e-13 of |b|
     // by the velocities).  It is then formed, and the next sweeps start, from the
     // mean of 4, of 16 and at last of 64 of them; where that does not help
-    // either, sweeps go on from single ones up to maxit.  An FP64 solve, which
-    // one sweep takes to its floor, ends there instead.
+    // either, or the target is out of its reach, sweeps go on from single ones
+    // up to maxit.  An FP64 solve, which one sweep takes to its floor, ends
+    // there instead.
     const double target = rtol * bnorm;
     double true_r = sqrt(rr);
     int it = 0, nev = 1;
@@ -1350,13 +1352,13 @@ extern "C" int ib_force_solve(lgfib_ctx *ctx, ib_system *sys, int prec, const do
         }
         const double last = true_r;
         if ((rc = true_residual(sys, b, x, r, nev, &rr, st))) return rc;
-        if (mean && it < maxit && sqrt(rr) > target && !(sqrt(rr) <= 0.5 * last)) {
+        if (mean && it < maxit && sqrt(rr) > target && !(sqrt(rr) <= 0.5 * last) && sqrt(rr) <= kMeanReach * target) {
             mean = nev < kMaxMean;
             nev = mean ? 4 * nev : 1;
             if (mean && (rc = true_residual(sys, b, x, r, nev, &rr, st))) return rc;
         }
         true_r = sqrt(rr);
-        const bool ends = !std::isfinite(true_r) || (prec == LGF_F64 && !mean);
+        const bool ends = !std::isfinite(true_r) || (prec == LGF_F64 && !(mean && true_r <= kMeanReach * target));
         if (prec != LGF_F64 || (true_r > target && it < maxit && !ends)) S->restarts++;
         if (ends) break;
     }

@@ -366,6 +366,19 @@ def test_force_solve_at_the_rounding_of_its_matvec(ctx, prec):
     sys.close()
 
 
+def test_fp64_solve_ends_at_a_target_out_of_reach(ctx, small_sphere):
+    """A tolerance a thousand times below what FP64 matvecs can show is given up
+    after the one sweep that reaches the floor, without further residuals."""
+    X, B, alpha, blocks, origin, mask, gk, C = small_sphere
+    sys = lg.ib_system_create(ctx, lg.IB_ROMA3, X, B, blocks, alpha)
+    b = torch.from_numpy(np.random.Generator(np.random.PCG64(41)).standard_normal(X.shape)).cuda()
+    f = torch.zeros_like(b)
+    st = lg.ib_force_solve(ctx, sys, b, f, rtol=1e-19, maxit=5000, prec=lg.LGF_F64, raise_on_noconv=False)
+    assert not st["converged"] and st["restarts"] == 0 and st["iterations"] < 5000
+    assert 0.0 < st["rel_residual"] < 1e-12
+    sys.close()
+
+
 def test_flows_of_one_block_set_share_their_operators(ctx, small_sphere):
     """Flows on the same blocks (different a, one made after another was
     destroyed, one after the caches were released) take the steps
